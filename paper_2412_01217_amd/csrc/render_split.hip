@@ -3,9 +3,9 @@
 // precision kept by splitting each operand x = hi + lo, hi = bf16(x), lo = bf16(x - hi):
 //   a b ~ a_hi b_hi + a_hi b_lo + a_lo b_hi      (relative error about 2^-16)
 //
-// Forward, per batch of 32 depth-ordered Gaussians and per wave of 64 pixels:
-//   each lane runs its pixel's transmittance recurrence and writes w[p][i] = alpha_i T_i
-//   to LDS, then out^T[c][p] += sum_i F^T[c][i] W^T[i][p] on the matrix cores.
+// Forward, per wave of 64 pixels and per batch of 32 depth-ordered Gaussians that reach them:
+//   each lane runs its pixel's transmittance recurrence, w[p][i] = alpha_i T_i, then
+//   out^T[c][p] += sum_i F^T[c][i] W^T[i][p] on the matrix cores.
 // Backward, per batch (back to front):
 //   GF^T[i][p] = sum_c F[i][c] G^T[c][p]  (g . f of every pixel-Gaussian pair) on the
 //     single-precision matrix cores (v_mfma_f32_16x16x4f32: it decides dL/dalpha, in
@@ -21,6 +21,8 @@
 // 16x16x32 bf16 operand layout (lane l, verified on the device):
 //   A[i][k]: i = l % 16, k = 8 (l / 16) + 0..7     B[k][j]: k = 8 (l / 16) + 0..7, j = l % 16
 //   D[i][j]: j = l % 16, i = 4 (l / 16) + r, r = 0..3
+#include <type_traits>
+
 #include "common.h"
 
 namespace gs {
@@ -194,15 +196,6 @@ __device__ __forceinline__ v4f mma6(const v8bf (&a)[3], const v8bf (&b)[3], v4f 
 }
 __device__ __forceinline__ v4f zero4() { return (v4f){0.0f, 0.0f, 0.0f, 0.0f}; }
 
-// The next (up to) four set bits of a wave-uniform mask, lowest first (-1 past the last).
-__device__ __forceinline__ void pop4(uint32_t& m, int (&q)[4]) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    q[e] = m ? __builtin_ctz(m) : -1;
-    m &= m - 1u;
-  }
-}
-
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -266,13 +259,6 @@ struct SStage {
     float* dst = s_f + q * SShape<NS>::FST + part * CPT;
 #pragma unroll
     for (int j = 0; j < CPT; j += 4) *reinterpret_cast<float4*>(dst + j) = make_float4(f[j], f[j + 1], f[j + 2], f[j + 3]);
-  }
-  // features channel-major: s_f[c][q]
-  __device__ __forceinline__ void commit_cols(float* s_rec, uint32_t* s_f, float ox, float oy) const {
-    const int q = threadIdx.x >> 3, part = threadIdx.x & 7;
-    if (part < 2) stage_rec(s_rec, q, r, part, ox, oy);
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) s_f[(part * CPT + j) * kWs + q] = pack_hl(f[j]);
   }
 };
 
@@ -395,62 +381,235 @@ __global__ __launch_bounds__(256) void k_fwd_trans(gs_config cfg, const float* _
   }
 }
 
-// Compositing of one work item per block: a whole tile list (SEG = false, one block per
-// tile) or, SEG = true, a chunk of up to cfg.fwd_chunk segments of a list taken by persistent
-// blocks from ctl[1], starting from the product of the earlier chunks' P. A split list
-// leaves each segment's colour, end T and blend record in its slot; when the list is one
-// chunk, the block also joins its segments (image, T, n_contrib, suffix colours).
-template <int NS, bool SEG>
-__global__ __launch_bounds__(256, 3) void k_render_fwd_split(gs_config cfg, const float* __restrict__ rgb,
-                                                          const float* __restrict__ sem,
-                                                          const uint16_t* __restrict__ emb, int n_sem,
-                                                          const float* __restrict__ rec,
-                                                          const float* __restrict__ depth, int64_t n,
-                                                          const gs_item* __restrict__ items, int n_items,
-                                                          const uint32_t* __restrict__ vals,
-                                                          const uint32_t* __restrict__ ranges, float* __restrict__ color,
-                                                          float* __restrict__ Tout, uint32_t* __restrict__ ncout,
-                                                          const uint2* __restrict__ work, uint32_t* __restrict__ ctl,
-                                                          FState fs) {
+// Swaps the 4x4 blocks (lane row R, register group X[pb]) -> (lane row pb, group R):
+// permlane32 exchanges rows 0,1 with 2,3, permlane16 rows 0 with 1 and 2 with 3.
+template <int NK>
+__device__ __forceinline__ void block_transpose(uint32_t (&X)[4][NK]) {
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+    auto s02 = __builtin_amdgcn_permlane32_swap(X[0][k], X[2][k], false, false);
+    auto s13 = __builtin_amdgcn_permlane32_swap(X[1][k], X[3][k], false, false);
+    X[0][k] = s02[0];
+    X[2][k] = s02[1];
+    X[1][k] = s13[0];
+    X[3][k] = s13[1];
+    auto s01 = __builtin_amdgcn_permlane16_swap(X[0][k], X[1][k], false, false);
+    auto s23 = __builtin_amdgcn_permlane16_swap(X[2][k], X[3][k], false, false);
+    X[0][k] = s01[0];
+    X[1][k] = s01[1];
+    X[2][k] = s23[0];
+    X[3][k] = s23[1];
+  }
+}
+
+// A wave's 64 pixels are a compact region of the tile: an 8x8 quad (16x4 of a 64x4 tile).
+// Fewer Gaussians reach a quad than a 16x4 band (1.1-1.5 of the four regions per list entry
+// against 1.2-1.6), and more of a reached quad's pixels take them.
+struct Region {
+  int px;                     // this lane's pixel, row-major in the tile
+  float lx, ly;               // its position from the tile's middle pixel
+  float x0, x1, y0, y1;       // the region's corner pixels, likewise
+};
+__device__ __forceinline__ Region wave_region(int tws, int r, int lane) {
+  const int rws = tws == 6 ? 4 : 3, per = 1 << (tws - rws);   // regions side by side in the tile
+  const int x0 = (r & (per - 1)) << rws, y0 = (r / per) * (64 >> rws);
+  const int x = x0 + (lane & ((1 << rws) - 1)), y = y0 + (lane >> rws);
+  const int mx = 1 << (tws - 1), my = 128 >> tws;
+  Region g;
+  g.px = (y << tws) + x;
+  g.lx = (float)(x - mx);
+  g.ly = (float)(y - my);
+  g.x0 = (float)(x0 - mx);
+  g.x1 = g.x0 + (float)((1 << rws) - 1);
+  g.y0 = (float)(y0 - my);
+  g.y1 = g.y0 + (float)((64 >> rws) - 1);
+  return g;
+}
+
+// Where a Gaussian's channels come from. `vec`: semantic rows (or embeddings) are read as
+// 16-byte (8-byte) vectors, which their alignment allows (sem_vec below); else one by one.
+struct FeatSrc {
+  const float *rgb, *sem, *depth;
+  const uint16_t* emb;
+  int n_sem, vec;
+};
+// Rows of n_sem floats start on 16-byte boundaries if the array does and n_sem is a multiple
+// of 4; an embedding row is 32 bytes.
+inline int sem_vec(const gs_gaussians& g, int n_sem) {
+  return g.emb ? (uintptr_t)g.emb % 16 == 0 : (n_sem % 4 == 0 && (uintptr_t)g.sem % 16 == 0);
+}
+
+// A batch's features on their way from memory to F^T in LDS. Neighbouring lanes read the
+// neighbouring quads (four channels) of a row, so that a load touches few cache lines: QL
+// lanes a Gaussian for plain semantics, four for an embedding (8 bytes each). Colour and depth
+// come beside them: lane q < 32 Gaussian q's colour, lane 32 + q its depth.
+template <int NS, bool EMB>
+struct Feats {
+  static constexpr int KP = SShape<NS>::KP;
+  static constexpr int QL = EMB ? 4 : KP / 4, NP = QL / 2;   // lanes a Gaussian, passes over 32 Gaussians
+  float f[EMB ? 1 : 4 * NP];
+  uint2 r[EMB ? NP : 1];
+  float c0, c1, c2;
+
+  // q-th queued Gaussian: its index at Q[8 q + 7] (0 where there is none). Every lane loads
+  // from a valid address; what it should not have is dropped by commit.
+  __device__ __forceinline__ void load(const FeatSrc& s, const float* Q, int64_t foff, int64_t e0, int lane) {
+    uint32_t g[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) g[p] = __float_as_uint(Q[8 * (p * (64 / QL) + lane / QL) + 7]);
+    const uint32_t gc = __float_as_uint(Q[8 * (lane & 31) + 7]);
+    if constexpr (EMB) {
+      const uint16_t* a = s.emb + 4 * (lane % QL);
+      if (s.vec) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) r[p] = *reinterpret_cast<const uint2*>(a + 16 * (int64_t)g[p]);
+      } else {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          const uint16_t* b = a + 16 * (int64_t)g[p];
+          r[p] = make_uint2((uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16));
+        }
+      }
+    } else if (s.n_sem > 0) {
+      const int k = 4 * (lane % QL) < s.n_sem ? 4 * (lane % QL) : 0;
+      const float* a = s.sem + (int64_t)s.n_sem * foff + k;
+      if (s.vec) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          const float4 v = *reinterpret_cast<const float4*>(a + (int64_t)s.n_sem * g[p]);
+          f[4 * p] = v.x;
+          f[4 * p + 1] = v.y;
+          f[4 * p + 2] = v.z;
+          f[4 * p + 3] = v.w;
+        }
+      } else {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int o = k + i < s.n_sem ? i : 0;
+            f[4 * p + i] = a[(int64_t)s.n_sem * g[p] + o];
+          }
+      }
+    }
+    const float* a = lane < 32 ? s.rgb + 3 * ((int64_t)gc + foff) : s.depth + (e0 + gc);
+    c0 = a[0];
+    c1 = c2 = 0.0f;
+    if (lane < 32) {
+      c1 = a[1];
+      c2 = a[2];
+    }
+  }
+  // F^T[channel][Gaussian], packed hi|lo (an embedding value is its own hi part), of cnt
+  // Gaussians; zero for the rest of the batch and past the last channel
+  __device__ __forceinline__ void commit(uint32_t* FT, int n_sem, int cnt, int lane) const {
+    const int k = 4 * (lane % QL);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int q = p * (64 / QL) + lane / QL;
+      uint32_t* d = FT + (4 + k) * kWs + q;
+      if constexpr (EMB) {
+        const uint32_t x = q < cnt ? r[p].x : 0u, y = q < cnt ? r[p].y : 0u;
+        d[0] = x << 16;
+        d[kWs] = x & 0xffff0000u;
+        d[2 * kWs] = y << 16;
+        d[3 * kWs] = y & 0xffff0000u;
+      } else if (k < NS) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[i * kWs] = q < cnt && k + i < n_sem ? pack_hl(f[4 * p + i]) : 0u;
+      }
+    }
+    uint32_t* d = FT + (lane < 32 ? 0 : 3 * kWs) + (lane & 31);
+    const bool live = (lane & 31) < cnt;
+    d[0] = live ? pack_hl(c0) : 0u;
+    if (lane < 32) {
+      d[kWs] = live ? pack_hl(c1) : 0u;
+      d[2 * kWs] = live ? pack_hl(c2) : 0u;
+    }
+  }
+};
+
+// The record of a list entry in the tile's frame (see LRec), from the two halves of gs_projected.rec.
+__device__ __forceinline__ LRec local_rec(const float4 a, const float4 b, float ox, float oy) {
+  LRec r;
+  r.m = make_float4((a.x - ox) + a.z, (a.y - oy) + a.w, -0.5f * kLog2e * b.x, -kLog2e * b.y);
+  r.c = make_float2(-0.5f * kLog2e * b.z, b.w);
+  return r;
+}
+
+// Hides a value's origin: what is computed from the copy is not hoisted out of the loop over
+// work items, where the many channel masks and addresses of an item's end would hold registers.
+__device__ __forceinline__ int opaque(int x) { asm volatile("" : "+s"(x)); return x; }
+__device__ __forceinline__ int opaque_v(int x) { asm volatile("" : "+v"(x)); return x; }
+
+// Compositing. A block takes a work item, a whole tile list (SEG = false, one block per tile)
+// or, SEG = true, a chunk of up to cfg.fwd_chunk segments of a list (persistent blocks, items
+// from ctl[1]), starting from the product of the earlier chunks' P. Each of its waves then
+// walks the list for its own 64 pixels, with nothing shared and no barrier:
+//   64 entries at a time, a lane each, are tested against the wave's region (band_reaches);
+//   the ones that can reach alpha_min in it (27-37 % of them) are appended to the wave's queue
+//   in LDS, in list order. The next 64 entries' records are on their way meanwhile.
+//   Every 32 queued Gaussians make a dense batch: their features are gathered, the 64 pixels'
+//   recurrence runs over them (unrolled, weights in registers), and by then the features have
+//   arrived: F^T goes to LDS and F W to the matrix cores. The weights reach the operand layout
+//   by a block transpose across lane rows, not through LDS.
+// A split list leaves each segment's colour, end T and blend record in its slot; when the list
+// is one chunk, the block also joins its segments (image, T, n_contrib, suffix colours).
+// What bounds it: vector issue (67 % busy) on full chips, one wave's chain of batches (about
+// 4000 cycles of recurrence each) where the longest list sets the time. It replaces a block
+// that staged 32 list entries at a time for all four waves, with two barriers a batch and
+// dense products over entries that mostly miss: 16 full-HD pyramids, embedding 30.7 -> 11.6 ms;
+// eight 636x476 pyramids, 20 classes 3.43 -> 1.77 ms; 1200x680 pyramid, 52 classes
+// 0.39 -> 0.21 ms; a 320x240 pyramid whose longest list has 2100 entries 0.26 -> 0.12 ms.
+// Three waves a SIMD with 32 channels; two with 64, since at three the compiler spills (0.39
+// against 0.21 ms: scratch traffic queues between the gathers).
+constexpr int kQueue = 128;     // a batch's remainder (31), 64 entries and a last batch's filling (32)
+
+template <int NS, bool SEG, bool EMB>
+__global__ __launch_bounds__(256, NS <= 28 ? 3 : 2) void k_render_fwd_split(
+    gs_config cfg, FeatSrc src, const float* __restrict__ rec, int64_t n, const gs_item* __restrict__ items, int n_items,
+    const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, float* __restrict__ color,
+    float* __restrict__ Tout, uint32_t* __restrict__ ncout, const uint2* __restrict__ work, uint32_t* __restrict__ ctl,
+    FState fs) {
   using S = SShape<NS>;
   constexpr int CB = S::CB, KP = S::KP;
-  __shared__ __align__(16) float s_rec[8 * kB];
-  __shared__ __align__(16) uint32_t s_f[KP * kWs];          // F^T, packed hi|lo, [channel][Gaussian]
-  __shared__ __align__(16) float s_w[4][64 * kWs];          // per wave W, [pixel][Gaussian]
+  __shared__ __align__(16) float s_queue[4][8 * kQueue];    // per wave: the record's six floats, list position, Gaussian
+  __shared__ __align__(16) uint32_t s_ft[4][KP * kWs];      // per wave: F^T, packed hi|lo, [channel][Gaussian]
   __shared__ uint32_t s_wi;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l16 = lane & 15, g4 = lane >> 4;
-  const int Kr = 4 + n_sem;
+  const int Kr = 4 + src.n_sem;
   const int tws = tile_shift(cfg);
-  const float lx = (float)((tid & ((1 << tws) - 1)) - (1 << (tws - 1))), ly = (float)((tid >> tws) - (128 >> tws));
+  const Region rg = wave_region(tws, wave, lane);
   const float amin = cfg.alpha_min, amax = cfg.alpha_max, tmin = cfg.t_min;
   const uint32_t n_work = SEG ? ctl[0] : 1u;
-  float* W = s_w[wave];
-  // this wave's band of tile-local pixel positions
-  const float bx0 = (float)(-(1 << (tws - 1))), bx1 = (float)((1 << (tws - 1)) - 1);
-  const float by0 = (float)(((64 * wave) >> tws) - (128 >> tws)), by1 = (float)(((64 * wave + 63) >> tws) - (128 >> tws));
+  float* const Q = s_queue[wave];
+  uint32_t* const FT = s_ft[wave];
+  if constexpr (EMB)   // the channels past the embedding's
+    for (int i = lane; i < (KP - 20) * kWs; i += 64) FT[20 * kWs + i] = 0u;
   for (uint32_t round = 0;; ++round) {
     uint32_t wi = 0;
     int tile, seg = 0, nseg = 1;
     if constexpr (SEG) {
       if (tid == 0) s_wi = atomicAdd(&ctl[1], 1u);
       lds_barrier();
-      wi = s_wi;
+      wi = __builtin_amdgcn_readfirstlane(s_wi);   // the same in every lane: scalar registers
       lds_barrier();
       if (wi >= n_work) break;
       const uint2 wk = work[wi];
-      tile = (int)wk.x;
-      seg = (int)(wk.y & 0xffffu);
-      nseg = (int)(wk.y >> 16);
+      tile = (int)__builtin_amdgcn_readfirstlane(wk.x);
+      const uint32_t sg2 = __builtin_amdgcn_readfirstlane(wk.y);
+      seg = (int)(sg2 & 0xffffu);
+      nseg = (int)(sg2 >> 16);
       if (seg % fwd_chunk(cfg) != 0) continue;   // inside a chunk walked by another item
     } else {
       if (round > 0) break;
       tile = cfg.tile_order ? (int)blockIdx.x : (int)gridDim.x - 1 - (int)blockIdx.x;
     }
     const Ctx c = make_ctx_of(items, n_items, ranges, tile, tws);
-    const int64_t foff = feature_offset(cfg, c.view, n);
+    const int64_t foff = feature_offset(cfg, c.view, n), e0 = (int64_t)c.item * n;
     int u, v;
-    tile_pixel(c, tid, u, v);
+    tile_pixel(c, rg.px, u, v);
     const bool inside = u < c.W && v < c.H;
     const float ox = (float)tile_mid_x(c) + 0.5f, oy = (float)tile_mid_y(c) + 0.5f;
     const bool split = SEG && nseg > 1;
@@ -464,160 +623,167 @@ __global__ __launch_bounds__(256, 3) void k_render_fwd_split(gs_config cfg, cons
       for (int pb = 0; pb < 4; ++pb) acc[cb][pb] = zero4();
     float T = 1.0f;
     if (split)
-      for (int s2 = 0; s2 < seg; s2 += chunk) T *= fs.P[(slot0 + s2) * kTilePx + tid];
+      for (int s2 = 0; s2 < seg; s2 += chunk) T *= fs.P[(slot0 + s2) * kTilePx + rg.px];
     // a pixel whose transmittance in front of the chunk is below t_min stopped earlier
-    bool done = !(inside & (T >= tmin));
+    float Tw = inside & (T >= tmin) ? T : 0.0f;
+    auto alive = [&]() { return Tw >= tmin; };
     uint32_t last = 0;
-    SStage<NS> st;
+
+    // composites the cnt (1..32) queued Gaussians from position o of the queue on
+    auto batch = [&](int o, int cnt) {
+      const float* R0 = Q + 8 * o;
+      Feats<NS, EMB> ft;
+      ft.load(src, R0, foff, e0, lane);
+      // front-to-back recurrence, branch-free; only Tw carries from one Gaussian to the next:
+      // T while the pixel is active, 0 once it has stopped (so that it takes nothing more); `at`
+      // is the batch position + 1 of the last Gaussian taken. The records of the next two
+      // Gaussians are read while two are used.
+      constexpr int kG = KP > 32 || EMB ? 4 : 2;
+      float w[kB];
+      int at = 0;
+      auto half = [&](auto q0_) {
+        constexpr int q0 = decltype(q0_)::value;
+        LRec A[kG], B[kG];
+#pragma unroll
+        for (int e = 0; e < kG; ++e) A[e] = load_rec(R0, q0 + e);
+#pragma unroll
+        for (int q = q0; q < q0 + 16; q += kG) {
+          if (q + kG < q0 + 16)
+#pragma unroll
+            for (int e = 0; e < kG; ++e) B[e] = load_rec(R0, q + kG + e);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int e = 0; e < kG; ++e) {
+            float dx, dy, t;
+            const float araw = A[e].c.y * __builtin_amdgcn_exp2f(local_power2(rg.lx, rg.ly, A[e], dx, dy, t));
+            const bool ok = araw >= amin;
+            const float wq = (ok ? fminf(amax, araw) : 0.0f) * Tw;
+            const float Tn = Tw - wq;
+            const bool low = Tn < tmin;
+            w[q + e] = low ? 0.0f : wq;
+            T = low ? T : Tn;
+            Tw = low ? 0.0f : Tn;
+            at = (ok & !low) ? q + e + 1 : at;
+          }
+#pragma unroll
+          for (int e = 0; e < kG; ++e) A[e] = B[e];
+        }
+      };
+      half(std::integral_constant<int, 0>());
+      if (cnt > 16) {
+        half(std::integral_constant<int, 16>());
+      } else {
+#pragma unroll
+        for (int q = 16; q < kB; ++q) w[q] = 0.0f;
+      }
+      if (__ballot(at > 0) == 0ull) return;
+      if (at > 0) last = __float_as_uint(R0[8 * at - 2]);
+      wave_sync();   // the previous batch's reads of F^T come first
+      ft.commit(FT, src.n_sem, cnt, lane);
+      // W^T operands: X[g] = this pixel's weights of Gaussians 8 g .. 8 g + 7, hi then lo parts; the
+      // transpose leaves lane (row g4, l16) with the weights 8 g4 + 0..7 of pixel 16 pb + l16 in X[pb]
+      uint32_t X[4][8];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        v8bf hi, lo;
+        split8(w + 8 * g, hi, lo);
+        const uint4 h = __builtin_bit_cast(uint4, hi), l = __builtin_bit_cast(uint4, lo);
+        X[g][0] = h.x; X[g][1] = h.y; X[g][2] = h.z; X[g][3] = h.w;
+        X[g][4] = l.x; X[g][5] = l.y; X[g][6] = l.z; X[g][7] = l.w;
+      }
+      block_transpose(X);
+      wave_sync();
+      // out^T[c][p] += F^T[c][i] W^T[i][p]: A = F^T (i = channel 16 cb + l16, k = Gaussian 8 g4 + e),
+      // B = W^T (k = Gaussian, j = pixel 16 pb + l16)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        v8bf ah, al;
+        load_op(FT + (16 * cb + l16) * kWs + 8 * g4, ah, al);
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb) {
+          const v8bf bh = __builtin_bit_cast(v8bf, make_uint4(X[pb][0], X[pb][1], X[pb][2], X[pb][3]));
+          const v8bf bl = __builtin_bit_cast(v8bf, make_uint4(X[pb][4], X[pb][5], X[pb][6], X[pb][7]));
+          if (EMB && cb > 0) acc[cb][pb] = mma(ah, bl, mma(ah, bh, acc[cb][pb]));   // bfloat16 values: no lo part
+          else acc[cb][pb] = mma3(ah, al, bh, bl, acc[cb][pb]);
+        }
+      }
+    };
+
     for (int sg = seg; sg < s_hi; ++sg) {
       const uint32_t a0 = split ? c.start + sg * seglen : c.start;
       const uint32_t b0 = split ? min(c.end, a0 + seglen) : c.end;
-      const bool active = !done;
-      if (a0 < b0) {
-        st.fetch(vals, a0, (int)min((uint32_t)kB, b0 - a0), c.item, n, rec, depth, rgb, sem, emb, n_sem, foff);
-        if (a0 + kB < b0) st.load_ids(vals, a0 + kB, (int)min((uint32_t)kB, b0 - a0 - kB));
-      }
-      for (uint32_t b = a0; b < b0; b += kB) {
-        // every wave is past the previous batch's LDS reads; stop once every pixel has
-        if (__syncthreads_count(!done) == 0) break;
-        st.commit_cols(s_rec, s_f, ox, oy);
-        __syncthreads();
-        const int cnt = (int)min((uint32_t)kB, b0 - b);
-        if (b + kB < b0) {
-          st.fetch_data((int)min((uint32_t)kB, b0 - b - kB), c.item, n, rec, depth, rgb, sem, emb, n_sem, foff);
-          if (b + 2 * kB < b0) st.load_ids(vals, b + 2 * kB, (int)min((uint32_t)kB, b0 - b - 2 * kB));
-        }
-        // front-to-back recurrence, branch-free; only T carries from one Gaussian to the next.
-        // A wave whose pixels have all stopped skips it (and the products), leaving its
-        // SIMD's issue slots to the other waves there while the block's other waves go on.
-        bool took = false;
-        const uint32_t base = b - c.start;
-        // with 32 channels, only the Gaussians that can reach a pixel of the wave's band;
-        // with 64 (whose registers are full) every Gaussian of the batch
-        if constexpr (KP <= 32) {
-          if (__ballot(!done) != 0ull) {
-            // the batch's Gaussians that can reach alpha_min somewhere in this wave's band of
-            // pixels (lane q < 32 tests Gaussian q); the others take no pixel of the band
-            bool hit = false;
-            if (lane < kB && lane < cnt) hit = band_reaches(load_rec(s_rec, lane), bx0, bx1, by0, by1, amin);
-            uint32_t m = (uint32_t)__ballot(hit);
-            // their weights only; the rest of the row is zero
-  #pragma unroll
-            for (int q4 = 0; q4 < kB; q4 += 4)
-              *reinterpret_cast<float4*>(W + lane * kWs + q4) = make_float4(0.f, 0.f, 0.f, 0.f);
-            // four at a time in list order, the next four's records read while these are used
-            // (two register sets taking turns)
-            auto load4 = [&](const int (&q)[4], LRec (&R)[4]) {
-  #pragma unroll
-              for (int e = 0; e < 4; ++e) R[e] = load_rec(s_rec, q[e] < 0 ? 0 : q[e]);
-            };
-            auto run4 = [&](const int (&q)[4], const LRec (&R)[4]) {
-  #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                if (q[e] < 0) break;   // uniform: the last group's missing entries
-                float dx, dy, t;
-                const float araw = R[e].c.y * __builtin_amdgcn_exp2f(local_power2(lx, ly, R[e], dx, dy, t));
-                const bool ok = !done & (araw >= amin);
-                const float w = fminf(amax, araw) * T;
-                const float Tn = T - w;
-                const bool stop = ok & (Tn < tmin);
-                const bool take = ok & !stop;
-                W[lane * kWs + q[e]] = take ? w : 0.0f;
-                T = take ? Tn : T;
-                done = done | stop;
-                last = take ? base + q[e] + 1 : last;
-                took |= take;
-              }
-            };
-            int qa[4], qb[4];
-            LRec RA[4], RB[4];
-            pop4(m, qa);
-            load4(qa, RA);
-            for (;;) {
-              if (qa[0] < 0) break;
-              pop4(m, qb);
-              if (qb[0] >= 0) load4(qb, RB);
-              run4(qa, RA);
-              if (qb[0] < 0) break;
-              pop4(m, qa);
-              if (qa[0] >= 0) load4(qa, RA);
-              run4(qb, RB);
-            }
+      const bool active = alive();
+      if (__ballot(alive()) != 0ull && a0 < b0) {
+        // this lane's entry of the 64 at hand (ra, rb: its record) and the next 64 entries' ids
+        auto load_id = [&](uint32_t b) -> uint32_t { return b + lane < b0 ? vals[b + lane] : 0u; };
+        auto load_half = [&](uint32_t b, uint32_t g, int part) -> float4 {
+          return b + lane < b0 ? reinterpret_cast<const float4*>(rec + kRecFloats * (e0 + g))[part]
+                               : make_float4(0.f, 0.f, 0.f, 0.f);
+        };
+        uint32_t gid = load_id(a0);
+        float4 ra = load_half(a0, gid, 0), rb = load_half(a0, gid, 1);
+        uint32_t gnext = a0 + 64 < b0 ? load_id(a0 + 64) : 0u;
+        int qn = 0;   // queued Gaussians
+        for (uint32_t b = a0;; b += 64) {
+          const LRec r = local_rec(ra, rb, ox, oy);
+          const bool hit = b + lane < b0 && band_reaches(r, rg.x0, rg.x1, rg.y0, rg.y1, amin);
+          const uint64_t m = __ballot(hit);
+          if (hit) {
+            const int at = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            float4* d = reinterpret_cast<float4*>(Q + 8 * at);
+            d[0] = r.m;
+            d[1] = make_float4(r.c.x, r.c.y, __uint_as_float(b + lane + 1 - c.start), __uint_as_float(gid));
           }
-        } else {
-          if (__ballot(!done) != 0ull) {
-            // records of the next four Gaussians are read while the current four are used
-            LRec R[4];
-  #pragma unroll
-            for (int e = 0; e < 4; ++e) R[e] = load_rec(s_rec, e);
-  #pragma unroll
-            for (int q4 = 0; q4 < kB; q4 += 4) {
-              LRec N[4];
-              if (q4 + 4 < kB)
-  #pragma unroll
-                for (int e = 0; e < 4; ++e) N[e] = load_rec(s_rec, q4 + 4 + e);
-              __builtin_amdgcn_sched_barrier(0);
-              float wq[4];
-  #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const int q = q4 + e;
-                float dx, dy, t;
-                const float araw = R[e].c.y * __builtin_amdgcn_exp2f(local_power2(lx, ly, R[e], dx, dy, t));
-                const bool ok = (q < cnt) & !done & (araw >= amin);
-                const float w = fminf(amax, araw) * T;
-                const float Tn = T - w;
-                const bool stop = ok & (Tn < tmin);
-                const bool take = ok & !stop;
-                wq[e] = take ? w : 0.0f;
-                T = take ? Tn : T;
-                done = done | stop;
-                last = take ? base + q + 1 : last;
-                took |= take;
-              }
-              *reinterpret_cast<float4*>(W + lane * kWs + q4) = make_float4(wq[0], wq[1], wq[2], wq[3]);
-              if (q4 + 4 < kB)
-  #pragma unroll
-                for (int e = 0; e < 4; ++e) R[e] = N[e];
-            }
+          qn += __builtin_popcountll(m);
+          const bool more = b + 64 < b0;   // else the remainder is composited too
+          if (more) {
+            gid = gnext;
+            ra = load_half(b + 64, gid, 0);
+            rb = load_half(b + 64, gid, 1);
+            gnext = b + 128 < b0 ? load_id(b + 128) : 0u;
           }
+          // a last batch's missing entries: a negative opacity, so no alpha reaches the threshold
+          if (!more) reinterpret_cast<float4*>(Q + 8 * qn)[lane] = make_float4(0.f, (lane & 1) ? -1.f : 0.f, 0.f, 0.f);
+          wave_sync();
+          int o = 0;
+          while (qn - o >= (more ? kB : 1) && __ballot(alive()) != 0ull) {
+            batch(o, min(kB, qn - o));
+            o += kB;
+          }
+          if (!more || __ballot(alive()) == 0ull) break;
+          if (o > 0 && qn > o) {   // the remainder (at most 31) moves to the front
+            const float4* s4 = reinterpret_cast<const float4*>(Q + 8 * o);
+            const float4 t = lane < 2 * (qn - o) ? s4[lane] : make_float4(0.f, 0.f, 0.f, 0.f);
+            wave_sync();
+            if (lane < 2 * (qn - o)) reinterpret_cast<float4*>(Q)[lane] = t;
+          }
+          qn -= o;
+          wave_sync();
         }
         wave_sync();
-        if (__ballot(took) == 0ull) continue;
-        // out^T[c][p] += F^T[c][i] W^T[i][p]: A = F^T (i = channel 16 cb + l16, k = Gaussian 8 g4 + e),
-        // B = W^T (k = Gaussian, j = pixel 16 pb + l16)
-        v8bf ah[CB], al[CB];
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) load_op(s_f + (16 * cb + l16) * kWs + 8 * g4, ah[cb], al[cb]);
-#pragma unroll
-        for (int pb = 0; pb < 4; ++pb) {
-          const float* src = W + (16 * pb + l16) * kWs + 8 * g4;
-          const float4 w0 = *reinterpret_cast<const float4*>(src), w1 = *reinterpret_cast<const float4*>(src + 4);
-          const float x[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-          v8bf bh, bl;
-          split8(x, bh, bl);
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) acc[cb][pb] = mma3(ah[cb], al[cb], bh, bl, acc[cb][pb]);
-        }
       }
       if (split) {
         // the segment's slot; D[c][p]: lane holds pixel 16 pb + l16 of this wave, channels
         // 16 cb + 4 g4 + r
         const int64_t sl = slot0 + sg;
-        float* dst = fs.CS + sl * Kr * kTilePx + wave * 64 + l16;
+        const int K2 = opaque(Kr), la = opaque_v(lane), li = la & 15, gi = 4 * (la >> 4);
+        float* dst = fs.CS + sl * K2 * kTilePx;
 #pragma unroll
-        for (int pb = 0; pb < 4; ++pb)
+        for (int pb = 0; pb < 4; ++pb) {
+          const int px = wave_region(tws, wave, 16 * pb + li).px;
 #pragma unroll
           for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const int ch = 16 * cb + 4 * g4 + r;
-              if (ch < Kr) dst[ch * kTilePx + 16 * pb] = acc[cb][pb][r];
+              const int ch = 16 * cb + gi + r;
+              if (ch < K2) dst[ch * kTilePx + px] = acc[cb][pb][r];
               acc[cb][pb][r] = 0.0f;
             }
-        const int64_t o = sl * kTilePx + tid;
+        }
+        const int64_t o = sl * kTilePx + rg.px;
         fs.Te[o] = T;
         const uint32_t lseg = last > (uint32_t)(sg * seglen) ? last : 0u;
-        fs.info[o] = lseg | (active ? kInfoActive : 0u) | ((active && done) ? kInfoStopped : 0u);
+        fs.info[o] = lseg | (active ? kInfoActive : 0u) | ((active && !alive()) ? kInfoStopped : 0u);
       }
     }
     if (split && nseg > chunk) continue;   // joined by k_fwd_combine
@@ -629,40 +795,42 @@ __global__ __launch_bounds__(256, 3) void k_render_fwd_split(gs_config cfg, cons
     // D[c][p] (the image), or for a split list the sum of its segments' colours taken back
     // to front, each slot left holding the sum of the ones after it (acc, zero after the
     // last flush, carries the running sum; every value read here was written by this lane)
+    const int K2 = opaque(Kr), la = opaque_v(lane), li = la & 15, gi = 4 * (la >> 4);
 #pragma unroll
     for (int pb = 0; pb < 4; ++pb) {
+      const int px = wave_region(tws, wave, 16 * pb + li).px;
       if (split) {
-        float* p = fs.CS + slot0 * Kr * kTilePx + wave * 64 + 16 * pb + l16;
+        float* p = fs.CS + slot0 * K2 * kTilePx + px;
         for (int s2 = nseg - 1; s2 >= 0; --s2) {
-          float* ps = p + (int64_t)s2 * Kr * kTilePx;
+          float* ps = p + (int64_t)s2 * K2 * kTilePx;
           float cs[CB][4];
 #pragma unroll
           for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const int ch = 16 * cb + 4 * g4 + r;
-              cs[cb][r] = ch < Kr ? ps[ch * kTilePx] : 0.0f;
+              const int ch = 16 * cb + gi + r;
+              cs[cb][r] = ch < K2 ? ps[ch * kTilePx] : 0.0f;
             }
 #pragma unroll
           for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const int ch = 16 * cb + 4 * g4 + r;
-              if (ch < Kr) ps[ch * kTilePx] = acc[cb][pb][r];
+              const int ch = 16 * cb + gi + r;
+              if (ch < K2) ps[ch * kTilePx] = acc[cb][pb][r];
               acc[cb][pb][r] += cs[cb][r];
             }
         }
       }
       int pu, pv;
-      tile_pixel(c, wave * 64 + 16 * pb + l16, pu, pv);
+      tile_pixel(c, px, pu, pv);
       if (pu >= c.W || pv >= c.H) continue;
-      const int64_t pbase = c.pixel_base * Kr + (int64_t)pv * c.W + pu;
+      const int64_t pbase = c.pixel_base * K2 + (int64_t)pv * c.W + pu;
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int ch = 16 * cb + 4 * g4 + r;
-          if (ch < Kr) color[pbase + ch * c.HW] = acc[cb][pb][r];
+          const int ch = 16 * cb + gi + r;
+          if (ch < K2) color[pbase + ch * c.HW] = acc[cb][pb][r];
         }
     }
   }
@@ -726,27 +894,6 @@ __global__ __launch_bounds__(256) void k_fwd_combine(const gs_item* __restrict__
 }
 
 // ------------------------------------------------------------------------- backward
-// Swaps the 4x4 blocks (lane row R, register group X[pb]) -> (lane row pb, group R):
-// permlane32 exchanges rows 0,1 with 2,3, permlane16 rows 0 with 1 and 2 with 3.
-template <int NK>
-__device__ __forceinline__ void block_transpose(uint32_t (&X)[4][NK]) {
-#pragma unroll
-  for (int k = 0; k < NK; ++k) {
-    auto s02 = __builtin_amdgcn_permlane32_swap(X[0][k], X[2][k], false, false);
-    auto s13 = __builtin_amdgcn_permlane32_swap(X[1][k], X[3][k], false, false);
-    X[0][k] = s02[0];
-    X[2][k] = s02[1];
-    X[1][k] = s13[0];
-    X[3][k] = s13[1];
-    auto s01 = __builtin_amdgcn_permlane16_swap(X[0][k], X[1][k], false, false);
-    auto s23 = __builtin_amdgcn_permlane16_swap(X[2][k], X[3][k], false, false);
-    X[0][k] = s01[0];
-    X[1][k] = s01[1];
-    X[2][k] = s23[0];
-    X[3][k] = s23[1];
-  }
-}
-
 // Walking a segment of a split list backwards needs, per pixel, the transmittance after
 // it and the suffix sum over every later Gaussian of w (g . f). Without the forward's
 // saved state, a summary pass gives every segment s of a long list, per pixel,
@@ -1423,14 +1570,14 @@ FLayout state_of(const gs_images& im, int n_tiles, int K, int seg) {
   return w;
 }
 
-template <int NS>
+template <int NS, bool EMB>
 int launch_fwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items, int n_items,
                  int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& out, hipStream_t s) {
   const FLayout w = state_of(out, n_tiles, 4 + cfg.n_sem, seg_len(cfg));
+  const FeatSrc src{g.rgb, g.sem, p.depth, g.emb, cfg.n_sem, sem_vec(g, cfg.n_sem)};
   if (!w.fs.tcnt) {
-    hipLaunchKernelGGL((k_render_fwd_split<NS, false>), dim3(n_tiles), dim3(256), 0, s, cfg, g.rgb, g.sem, g.emb,
-                       cfg.n_sem, p.rec, p.depth, g.n, items, n_items, vals, ranges, out.color, out.T, out.n_contrib,
-                       nullptr, nullptr, w.fs);
+    hipLaunchKernelGGL((k_render_fwd_split<NS, false, EMB>), dim3(n_tiles), dim3(256), 0, s, cfg, src, p.rec, g.n, items,
+                       n_items, vals, ranges, out.color, out.T, out.n_contrib, nullptr, nullptr, w.fs);
     return launch_status();
   }
   const unsigned tb = (unsigned)ceil_div(n_tiles, 256);
@@ -1442,14 +1589,13 @@ int launch_fwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   hipLaunchKernelGGL(k_seg_list, dim3(tb), dim3(256), 0, s, w.cnt, w.base, w.total, n_tiles, cfg.tile_order,
                      w.max_segs, w.work, w.ctl, w.fs.tcnt, w.fs.tbase);
   const int grid_t = resident_blocks(k_fwd_trans, 256, 0);
-  const int grid_f = resident_blocks(k_render_fwd_split<NS, true>, 256, 0);
+  const int grid_f = resident_blocks(k_render_fwd_split<NS, true, EMB>, 256, 0);
   if (!grid_t || !grid_f) return GS_ERR_HIP;
   if (cfg.fwd_chunk > 0)
     hipLaunchKernelGGL(k_fwd_trans, dim3(grid_t), dim3(256), 0, s, cfg, p.rec, g.n, items, n_items, vals, ranges,
                        w.work, w.ctl, w.fs.P);
-  hipLaunchKernelGGL((k_render_fwd_split<NS, true>), dim3(grid_f), dim3(256), 0, s, cfg, g.rgb, g.sem, g.emb, cfg.n_sem,
-                     p.rec, p.depth, g.n, items, n_items, vals, ranges, out.color, out.T, out.n_contrib, w.work, w.ctl,
-                     w.fs);
+  hipLaunchKernelGGL((k_render_fwd_split<NS, true, EMB>), dim3(grid_f), dim3(256), 0, s, cfg, src, p.rec, g.n, items, n_items,
+                     vals, ranges, out.color, out.T, out.n_contrib, w.work, w.ctl, w.fs);
   if (cfg.fwd_chunk > 0)
     hipLaunchKernelGGL(k_fwd_combine<NS>, dim3(n_tiles), dim3(256), 0, s, items, n_items, ranges, 4 + cfg.n_sem,
                        cfg.fwd_chunk, tile_shift(cfg), w.fs, out.color, out.T, out.n_contrib);
@@ -1506,8 +1652,9 @@ int launch_render_fwd_split(const gs_config& cfg, const gs_gaussians& g, const g
                             int n_items, int n_tiles, const uint32_t* vals, const uint32_t* ranges,
                             const gs_images& out, hipStream_t s) {
   const int ns = cfg.n_sem;
-  if (ns <= 28) return launch_fwd_s<28>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
-  if (ns <= 60) return launch_fwd_s<60>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
+  if (g.emb) return launch_fwd_s<28, true>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
+  if (ns <= 28) return launch_fwd_s<28, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
+  if (ns <= 60) return launch_fwd_s<60, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
   return GS_ERR_UNSUPPORTED;
 }
 
