@@ -6,17 +6,17 @@
 // Forward, per wave of 64 pixels and per batch of 32 depth-ordered Gaussians that reach them:
 //   each lane runs its pixel's transmittance recurrence, w[p][i] = alpha_i T_i, then
 //   out^T[c][p] += sum_i F^T[c][i] W^T[i][p] on the matrix cores.
-// Backward, per batch (back to front):
-//   GF^T[i][p] = sum_c F[i][c] G^T[c][p]  (g . f of every pixel-Gaussian pair) on the
-//     single-precision matrix cores (v_mfma_f32_16x16x4f32: it decides dL/dalpha, in
-//     which terms cancel); a 4x4 block transpose across lane rows (permlane swaps) hands every
-//     lane its own pixel's 32 values;
+// Backward, per wave and per group of 16 reaching Gaussians (back to front):
+//   GF^T[i][p] = sum_c F[i][c] G^T[c][p]  (g . f of every pixel-Gaussian pair; it decides
+//     dL/dalpha, in which terms cancel) in single precision: three bfloat16 parts with 32 padded
+//     channels, v_mfma_f32_16x16x4f32 with 64; a 4x4 block transpose across lane rows (permlane
+//     swaps) hands every lane its own pixel's 16 values;
 //   each lane runs the reverse recurrence (T recovered with the reciprocal of 1 - alpha)
 //     and writes w[i][p] to LDS, Gaussian-major;
 //   dF[i][c] = sum_p W^T[i][p] G[p][c]                       (feature gradients)
-//   the 2D mean, conic and opacity gradients are summed per pair in single precision
-//   (row sums over 16 lanes, then over rows and waves in LDS): expanding them into
-//   moments about a fixed centre would lose accuracy for compact Gaussians.
+//   the 2D mean, conic and opacity gradients are summed per pair in single precision across the
+//   wave: expanding them into moments about a fixed centre would lose accuracy for compact
+//   Gaussians.
 //
 // 16x16x32 bf16 operand layout (lane l, verified on the device):
 //   A[i][k]: i = l % 16, k = 8 (l / 16) + 0..7     B[k][j]: k = 8 (l / 16) + 0..7, j = l % 16
@@ -625,7 +625,7 @@ __global__ __launch_bounds__(256, NS <= 28 ? 3 : 2) void k_render_fwd_split(
     if (split)
       for (int s2 = 0; s2 < seg; s2 += chunk) T *= fs.P[(slot0 + s2) * kTilePx + rg.px];
     // a pixel whose transmittance in front of the chunk is below t_min stopped earlier
-    float Tw = inside & (T >= tmin) ? T : 0.0f;
+    float Tw = (inside & (T >= tmin)) ? T : 0.0f;
     auto alive = [&]() { return Tw >= tmin; };
     uint32_t last = 0;
 
@@ -904,17 +904,12 @@ __global__ __launch_bounds__(256) void k_fwd_combine(const gs_item* __restrict__
 // d power/d mean2d = -(dE/d dx, dE/d dy) / log2(e) and d power/d(A, B, C) =
 // -(dx^2 / 2, dx dy, dy^2 / 2); the reverse pass sums dE/d dx, dE/d dy, dx^2, dx dy, dy^2
 // (times dL/d power) and applies these factors once per Gaussian.
-// Partial sums per (Gaussian, component) left in LDS by a batch: 4 per wave.
-constexpr int kGeoSlots = 16;
-
 // Sums the geometric terms of GG Gaussians (6 GG values per lane) over the wave's four
 // lane rows and over the lane pairs (l16, l16 ^ 8) of a row, halving the values held at each
 // step instead of reducing each value separately: a permlane32 swap pairs rows (0, 2) and
 // (1, 3), a permlane16 swap rows (0, 1) and (2, 3), a row rotation by 8 the halves of a row.
-// A last mirror within each half row pairs lanes i and 7 - i. Lane (row R, l16) returns
-// Y[j] = sum of V[f + j] over the 16 lanes (l16 % 4, 7 - l16 % 4) + {0, 8}, times the four
-// rows, with f = 6 R + 3 (l16 / 8) for GG = 4 and f = 3 R for GG = 2. Lanes with l16 % 8 < 4
-// hold the distinct sums (for GG = 2 the two half rows hold the same ones).
+// Moves within the half rows finish the sums: every lane (row R, l16) returns Y[j] = the wave's
+// sum of V[f + j], with f = 6 R + 3 (l16 / 8) for GG = 4 and f = 3 R for GG = 2.
 template <int GG>
 __device__ __forceinline__ void geo_reduce(const float (&V)[6 * GG], float (&Y)[3]) {
   constexpr int H1 = 3 * GG, H2 = 3 * GG / 2;
@@ -941,7 +936,11 @@ __device__ __forceinline__ void geo_reduce(const float (&V)[6 * GG], float (&Y)[
     for (int j = 0; j < 3; ++j) Y[j] = X[j] + dpp_ror8(X[j]);
   }
 #pragma unroll
-  for (int j = 0; j < 3; ++j) Y[j] += dpp_half_mirror(Y[j]);
+  for (int j = 0; j < 3; ++j) {
+    Y[j] += dpp_half_mirror(Y[j]);
+    Y[j] += dpp_xor1(Y[j]);
+    Y[j] += dpp_xor2(Y[j]);
+  }
 }
 
 __constant__ float kGeoScale[6] = {-1.0f / kLog2e, -1.0f / kLog2e, -0.5f, -1.0f, -0.5f, 1.0f};
@@ -1008,53 +1007,35 @@ __global__ void k_seg_list(const uint32_t* __restrict__ cnt_ord, const uint32_t*
   }
 }
 
-// SUMMARY = false: the reverse pass proper over one work item (a whole tile list, or one
-// segment of it). SUMMARY = true: the per-segment P and GC of the segments of long lists.
-// Persistent blocks take work items from a counter until the list is exhausted.
-template <int NS, bool SUMMARY>
-__global__ __launch_bounds__(256, 2) void k_render_bwd_split(gs_config cfg, const float* __restrict__ rgb,
-                                                          const float* __restrict__ sem,
-                                                          const uint16_t* __restrict__ emb, int n_sem,
-                                                          const float* __restrict__ rec,
-                                                          const float* __restrict__ depth, int64_t n,
-                                                          const gs_item* __restrict__ items, int n_items,
-                                                          const uint32_t* __restrict__ vals,
-                                                          const uint32_t* __restrict__ ranges,
-                                                          const float* __restrict__ Tfin,
-                                                          const uint32_t* __restrict__ ncin,
-                                                          const float* __restrict__ gcolor, float* __restrict__ g2d,
-                                                          float* __restrict__ grgb, float* __restrict__ gsem,
-                                                          const uint2* __restrict__ work, uint32_t* __restrict__ ctl,
-                                                          const uint32_t* __restrict__ tile_lmax,
-                                                          float* __restrict__ segP, float* __restrict__ segGC,
-                                                          FState fs) {
+// The summary pass over the segments of long lists, without a forward state: per segment and
+// pixel, P and GC (above), front to back. Persistent blocks take work items from a counter.
+template <int NS>
+__global__ __launch_bounds__(256, 2) void k_seg_summary(gs_config cfg, const float* __restrict__ rgb,
+                                                        const float* __restrict__ sem,
+                                                        const uint16_t* __restrict__ emb, int n_sem,
+                                                        const float* __restrict__ rec,
+                                                        const float* __restrict__ depth, int64_t n,
+                                                        const gs_item* __restrict__ items, int n_items,
+                                                        const uint32_t* __restrict__ vals,
+                                                        const uint32_t* __restrict__ ranges,
+                                                        const uint32_t* __restrict__ ncin,
+                                                        const float* __restrict__ gcolor,
+                                                        const uint2* __restrict__ work, uint32_t* __restrict__ ctl,
+                                                        const uint32_t* __restrict__ tile_lmax,
+                                                        float* __restrict__ segP, float* __restrict__ segGC) {
   using S = SShape<NS>;
-  constexpr int KP = S::KP, CB = S::CB, FST = S::FST;
-  constexpr int GG = NS > 28 ? 2 : 4;         // Gaussians per geometric-term reduction (register budget)
+  constexpr int KP = S::KP, FST = S::FST;
   __shared__ __align__(16) float s_rec[8 * kB];
   __shared__ __align__(16) float s_f[kB * FST];             // F, [Gaussian][channel]
-  constexpr int DFS = KP + 4;                 // row stride of s_df: lane rows land on other banks
-  // One pool for the batch loop's W (per wave, 16 Gaussians, [Gaussian][pixel]) and two
-  // buffers each of dF ([Gaussian][channel]) and geometric partial sums
-  // ([Gaussian][component][slot]): a batch's sums are flushed to global memory during the
-  // next batch. At the start of a work item each wave stages its pixels' upstream gradient
-  // in the pool instead (32 channels at a time, [channel][pixel], rows of kGst floats).
-  constexpr int kWsz = 4 * 16 * kPs, kDsz = kB * DFS, kGsz = kB * 6 * kGeoSlots, kGst = 64 + 4;
-  static_assert(4 * 32 * kGst <= kWsz + 2 * kDsz + 2 * kGsz, "staging fits the pool");
-  __shared__ __align__(16) float s_pool[SUMMARY ? 1 : kWsz + 2 * kDsz + 2 * kGsz];
   __shared__ uint32_t s_wi;
-  __shared__ uint32_t s_gid[2][kB];
+  __shared__ uint32_t s_gid[kB];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int l16 = lane & 15, g4 = lane >> 4;
   const int Kr = 4 + n_sem;
   const float amin = cfg.alpha_min, amax = cfg.alpha_max;
   const uint32_t n_work = ctl[0];
-  // this wave's band of tile-local pixel positions
-  const int tws0 = tile_shift(cfg);
-  const float bx0 = (float)(-(1 << (tws0 - 1))), bx1 = (float)((1 << (tws0 - 1)) - 1);
-  const float by0 = (float)(((64 * wave) >> tws0) - (128 >> tws0)), by1 = (float)(((64 * wave + 63) >> tws0) - (128 >> tws0));
   for (;;) {
-    if (tid == 0) s_wi = atomicAdd(&ctl[SUMMARY ? 1 : 2], 1u);
+    if (tid == 0) s_wi = atomicAdd(&ctl[1], 1u);
     lds_barrier();
     const uint32_t wi = s_wi;
     lds_barrier();
@@ -1062,7 +1043,7 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_split(gs_config cfg, cons
     const uint2 wk = work[wi];
     const int tile = (int)wk.x;
     const int seg = (int)(wk.y & 0xffffu), nseg = (int)(wk.y >> 16);
-    if (SUMMARY && nseg < 2) continue;
+    if (nseg < 2) continue;
     const Ctx c = make_ctx_of(items, n_items, ranges, tile, tile_shift(cfg));
     const int64_t foff = feature_offset(cfg, c.view, n);
     int u, v;
@@ -1072,13 +1053,10 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_split(gs_config cfg, cons
     const float ox = (float)tile_mid_x(c) + 0.5f, oy = (float)tile_mid_y(c) + 0.5f;
     const int64_t pix = c.pixel_base + (int64_t)v * c.W + u;
     // n_contrib comes from the matching forward; clamp so that a mismatched call stays in range
-    const uint32_t len = c.end - c.start;
-    const uint32_t last = inside ? min(ncin[pix], len) : 0u;
+    const uint32_t last = inside ? min(ncin[pix], c.end - c.start) : 0u;
     const int lmax = (int)tile_lmax[tile];
     const int seglen = seg_len(cfg);
-    const int a0 = nseg == 1 ? 0 : seg * seglen;
-    const int b0 = nseg == 1 ? lmax : min(lmax, a0 + seglen);
-
+    const int a0 = seg * seglen, b0 = min(lmax, a0 + seglen);
     // upstream gradient of a wave pixel (0..63) and channel, zero outside the image
     auto gval = [&](int wp, int ch) -> float {
       int pu, pv;
@@ -1086,35 +1064,186 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_split(gs_config cfg, cons
       if (pu >= c.W || pv >= c.H || ch >= Kr) return 0.0f;
       return gcolor[c.pixel_base * Kr + (int64_t)pv * c.W + pu + ch * c.HW];
     };
-    // G^T as B of GF (k = channel 4 ks + g4, j = pixel 16 pb + l16); with 32 padded channels
-    // the main pass takes GF on bfloat16 matrix cores instead, each operand in three parts
-    // (single-precision products at a sixth of the 16x16x4 products' matrix-core time):
-    // g3[part][pb], B of 16x16x32 (k = channel 8 g4 + e, j = pixel 16 pb + l16)
-    constexpr bool kGF3 = !SUMMARY && KP == 32;
-    float g1[4][kGF3 ? 1 : KP / 4];
-    v8bf g3[kGF3 ? 4 : 1][3];
-    if constexpr (SUMMARY) {
+    // G^T as B of GF (k = channel 4 ks + g4, j = pixel 16 pb + l16)
+    float g1[4][KP / 4];
+#pragma unroll
+    for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+      for (int ks = 0; ks < KP / 4; ++ks) g1[pb][ks] = gval(16 * pb + l16, 4 * ks + g4);
+    float T = 1.0f, acc = 0.0f;
+    SStage<NS> st;
+    if (a0 < b0) {
+      st.fetch(vals, c.start + a0, min(kB, b0 - a0), c.item, n, rec, depth, rgb, sem, emb, n_sem, foff);
+      if (a0 + kB < b0) st.load_ids(vals, c.start + a0 + kB, min(kB, b0 - a0 - kB));
+    }
+    for (int lo = a0; lo < b0; lo += kB) {
+      const int cnt = min(kB, b0 - lo);
+      lds_barrier();
+      st.commit_rows(s_rec, s_f, s_gid, ox, oy);
+      lds_barrier();
+      if (lo + kB < b0) {
+        st.fetch_data(min(kB, b0 - lo - kB), c.item, n, rec, depth, rgb, sem, emb, n_sem, foff);
+        if (lo + 2 * kB < b0) st.load_ids(vals, c.start + lo + 2 * kB, min(kB, b0 - lo - 2 * kB));
+      }
+      if (__ballot((uint32_t)lo < last) == 0ull) continue;
+      // GF^T[i][p] in single precision: v_mfma_f32_16x16x4_f32, A = F (i = Gaussian 16 bq + l16,
+      // k = channel 4 ks + g4), B = G^T; lane row g4 holds Gaussians {4 g4 + r, 16 + 4 g4 + r} of all
+      // four pixel rows, and after the transpose every lane its own pixel's values:
+      // X[g][4 bq + r] = gf of Gaussian 16 bq + 4 g + r
+      uint32_t X[4][8];
+      v4f gfa[4][2];
+#pragma unroll
+      for (int pb = 0; pb < 4; ++pb) gfa[pb][0] = gfa[pb][1] = zero4();
+#pragma unroll
+      for (int bq = 0; bq < 2; ++bq)
+#pragma unroll
+        for (int ks = 0; ks < KP / 4; ++ks) {
+          const float a = s_f[(16 * bq + l16) * FST + 4 * ks + g4];
+#pragma unroll
+          for (int pb = 0; pb < 4; ++pb)
+            gfa[pb][bq] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, g1[pb][ks], gfa[pb][bq], 0, 0, 0);
+        }
 #pragma unroll
       for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-        for (int ks = 0; ks < KP / 4; ++ks) g1[pb][ks] = gval(16 * pb + l16, 4 * ks + g4);
+        for (int r = 0; r < 4; ++r) {
+          X[pb][r] = __float_as_uint(gfa[pb][0][r]);
+          X[pb][4 + r] = __float_as_uint(gfa[pb][1][r]);
+        }
+      block_transpose(X);
+#pragma unroll
+      for (int q = 0; q < kB; ++q) {
+        const LRec rq = load_rec(s_rec, q);
+        float dx, dy, t;
+        const float araw = rq.c.y * __builtin_amdgcn_exp2f(local_power2(lx, ly, rq, dx, dy, t));
+        const bool act = (q < cnt) & ((uint32_t)(lo + q) < last) & (araw >= amin);
+        const float w = fminf(amax, araw) * T;
+        const float gf = __uint_as_float(X[(q >> 2) & 3][4 * (q >> 4) + (q & 3)]);
+        acc = act ? __builtin_fmaf(w, gf, acc) : acc;
+        T = act ? T - w : T;
+      }
     }
-    // G as B of dF (k = pixel 32 ks + 8 g4 + e, j = channel 16 cb + l16). Main pass: each
-    // wave stages its 64 pixels' upstream gradient, 32 channels at a time, with one
-    // coalesced load per channel and lane, and builds both operand layouts from LDS; the
-    // lane's own pixel's values also give the state's dot product.
-    v8bf g2h[2][SUMMARY ? 1 : CB], g2l[2][SUMMARY ? 1 : CB];
+    segP[(int64_t)wi * kTilePx + tid] = T;
+    segGC[(int64_t)wi * kTilePx + tid] = acc;
+  }
+}
+
+// ------------------------------------------------------------------------- backward, main pass
+// Where the reverse pass's per-Gaussian sums go from LDS: the n_sem semantic channels, then
+// rgb, then the record's seven components (mean2d 2, conic 3, opacity, depth).
+struct GradDst {
+  float *grgb, *gsem, *g2d;
+};
+
+// The reverse pass over one work item (a whole tile list, or one segment of it), back to front.
+// Persistent blocks take work items from a counter; each wave then walks the list for its own 64
+// pixels, with nothing shared and no barrier:
+//   64 entries at a time, a lane each, are tested against the wave's region, from the last entry
+//   that its forward used; the ones that can reach alpha_min there (27-37 %) go to the wave's ring
+//   in LDS, back to front.
+//   Every 16 of them make a dense group: g . f on the matrix cores, the reverse recurrence, the
+//   geometric sums, dF on the matrix cores, all over Gaussians that these pixels can see.
+//   A group's features are gathered while the one before is worked on, and its sums leave for
+//   memory before the gather after it is issued: loads and atomics complete in order, so neither
+//   is waited for until a whole group's work has passed.
+// Memory takes 21 G atomic requests a second of up to 64 bytes each, however few bytes they carry
+// (measured), so a group's sums go out with the lanes of a Gaussian side by side: a record's seven
+// components (32 bytes) or an embedding's row (64) are one request each.
+// It replaces a block that staged 32 entries at a time for its four waves and met at two barriers a
+// batch: 16 full-HD pyramids, embedding 70.3 -> 29.7 ms; eight 636x476 pyramids, 20 classes
+// 6.44 -> 3.14 ms; a 1200x680 pyramid, 52 classes 1.04 -> 0.52 ms; a 320x240 pyramid 0.28 -> 0.14 ms.
+// Windows of 64 entries shared by the four waves, their sums meeting in LDS (half the atomic
+// requests), took 45.9 ms and 0.88 ms on the first and third: 28 % of the cycles were waves waiting
+// for the one with most entries in the window.
+constexpr int kGrp = 16, kRing = 128;   // ring: a part group (15), two groups in work, 64 new entries
+
+template <int NS>
+struct BShape {
+  static constexpr int KP = SShape<NS>::KP;
+  static constexpr bool kGF3 = KP == 32;                       // g . f in three bfloat16 parts
+  static constexpr int FROW = kGF3 ? 3 * 16 + 4 : KP + 4;      // dwords of a feature row: 3 parts of 32 bf16, or floats
+  static constexpr int AROW = KP + 8;                          // floats of a sum row: channels, then 6 geometric sums
+  static constexpr int kQ = 8 * kRing, kW = kGrp * kPs, kF = kGrp * FROW, kA = kGrp * AROW;
+  static constexpr int kStage = 32 * kPs;                      // upstream gradient staging at an item's start
+  static constexpr int kWave = kQ + kW + kF + kA > kStage ? kQ + kW + kF + kA : kStage;
+};
+
+template <int NS, bool EMB>
+__global__ __launch_bounds__(256, 2) void k_render_bwd_main(
+    gs_config cfg, FeatSrc src, const float* __restrict__ rec, int64_t n, const gs_item* __restrict__ items, int n_items,
+    const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, const float* __restrict__ Tfin,
+    const uint32_t* __restrict__ ncin, const float* __restrict__ gcolor, GradDst out, const uint2* __restrict__ work,
+    uint32_t* __restrict__ ctl, const uint32_t* __restrict__ tile_lmax, const float* __restrict__ segP,
+    const float* __restrict__ segGC, FState fs) {
+  using B = BShape<NS>;
+  constexpr int KP = SShape<NS>::KP, CB = SShape<NS>::CB, FROW = B::FROW, AROW = B::AROW;
+  constexpr bool kGF3 = B::kGF3;
+  constexpr int GG = NS > 28 ? 2 : 4;         // Gaussians per geometric-term reduction (register budget)
+  __shared__ __align__(16) float s_mem[4][B::kWave];
+  __shared__ uint32_t s_wi;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int Kr = 4 + src.n_sem;
+  const int tws = tile_shift(cfg);
+  const float amin = cfg.alpha_min, amax = cfg.alpha_max;
+  const uint32_t n_work = ctl[0];
+  // the wave's memory: ring of records {mx, my, a, b, c, o, list position, Gaussian}, W of a group
+  // [Gaussian][pixel], features [Gaussian][channel], sums [Gaussian][channel, geometric]
+  float* const Q = s_mem[wave];
+  float* const W = Q + B::kQ;
+  float* const F = W + B::kW;
+  float* const A = F + B::kF;
+  const Region rg = wave_region(tws, wave, lane);
+  for (;;) {
+    if (tid == 0) s_wi = atomicAdd(&ctl[2], 1u);
+    lds_barrier();
+    const uint32_t wi = __builtin_amdgcn_readfirstlane(s_wi);
+    lds_barrier();
+    if (wi >= n_work) break;
+    const uint2 wk = work[wi];
+    const int tile = (int)__builtin_amdgcn_readfirstlane(wk.x);
+    const uint32_t sg = __builtin_amdgcn_readfirstlane(wk.y);
+    const int seg = (int)(sg & 0xffffu), nseg = (int)(sg >> 16);
+    const Ctx c = make_ctx_of(items, n_items, ranges, tile, tws);
+    const int64_t foff = feature_offset(cfg, c.view, n), e0 = (int64_t)c.item * n;
+    int u, v;
+    tile_pixel(c, rg.px, u, v);
+    const bool inside = u < c.W && v < c.H;
+    const float ox = (float)tile_mid_x(c) + 0.5f, oy = (float)tile_mid_y(c) + 0.5f;
+    const int64_t pix = c.pixel_base + (int64_t)v * c.W + u;
+    // n_contrib comes from the matching forward; clamp so that a mismatched call stays in range
+    const uint32_t len = c.end - c.start;
+    const uint32_t last = inside ? min(ncin[pix], len) : 0u;
+    const int seglen = seg_len(cfg);
+    const int a0 = nseg == 1 ? 0 : seg * seglen;
+    // the last entry that one of the wave's pixels used
+    uint32_t wl = last;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) wl = max(wl, (uint32_t)__shfl_xor((int)wl, off, 64));
+    wl = __builtin_amdgcn_readfirstlane(wl);
+    const int b0 = nseg == 1 ? (int)wl : min((int)wl, a0 + seglen);
+    if (a0 >= b0) continue;   // (the same for the whole wave)
+
+    // Upstream gradient of the wave's 64 pixels in two operand layouts, through LDS 32 channels
+    // at a time: B of g . f (k = channel, j = pixel 16 pb + l16), with 32 padded channels in three
+    // bfloat16 parts (single-precision products at a sixth of the 16x16x4 products' time), else
+    // in single precision; B of dF (k = pixel 32 ks + 8 g4 + e, j = channel 16 cb + l16). The
+    // lane's own pixel's values also give the forward state's dot product.
+    float g1[4][kGF3 ? 1 : KP / 4];
+    v8bf g3[kGF3 ? 4 : 1][3];
+    v8bf g2h[2][CB], g2l[2][CB];
     float gdot = 0.0f;          // sum_k g_k S_k of the lane's pixel (forward state)
-    if constexpr (!SUMMARY) {
+    {
       const bool use_state = nseg > 1 && fs.tcnt != nullptr && inside;
-      const float* sc = use_state ? fs.CS + ((int64_t)fs.tbase[tile] + seg) * Kr * kTilePx + tid : nullptr;
-      const float* gp = gcolor + c.pixel_base * Kr + (int64_t)v * c.W + u;   // this lane's pixel (tid)
-      float* stg = s_pool + wave * 32 * kGst;
+      const float* sc = use_state ? fs.CS + ((int64_t)fs.tbase[tile] + seg) * Kr * kTilePx + rg.px : nullptr;
+      const float* gp = gcolor + c.pixel_base * Kr + (int64_t)v * c.W + u;   // this lane's pixel
+      float* stg = Q;
 #pragma unroll
       for (int h = 0; h < KP / 32; ++h) {
+        const int K2 = opaque(Kr);
         float gl[32];
 #pragma unroll
-        for (int j = 0; j < 32; ++j) gl[j] = (inside && 32 * h + j < Kr) ? gp[(int64_t)(32 * h + j) * c.HW] : 0.0f;
+        for (int j = 0; j < 32; ++j) gl[j] = (inside && 32 * h + j < K2) ? gp[(int64_t)(32 * h + j) * c.HW] : 0.0f;
         if (use_state) {
           // all 32 loads in flight where the registers allow it, else 8 at a time
           constexpr int kSv = KP <= 32 ? 32 : 8;
@@ -1122,34 +1251,34 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_split(gs_config cfg, cons
           for (int j0 = 0; j0 < 32; j0 += kSv) {
             float sv[kSv];
 #pragma unroll
-            for (int j = 0; j < kSv; ++j) sv[j] = 32 * h + j0 + j < Kr ? sc[(32 * h + j0 + j) * kTilePx] : 0.0f;
+            for (int j = 0; j < kSv; ++j) sv[j] = 32 * h + j0 + j < K2 ? sc[(32 * h + j0 + j) * kTilePx] : 0.0f;
 #pragma unroll
             for (int j = 0; j < kSv; ++j) gdot = __builtin_fmaf(gl[j0 + j], sv[j], gdot);
           }
         }
 #pragma unroll
-        for (int j = 0; j < 32; ++j) stg[j * kGst + lane] = gl[j];
+        for (int j = 0; j < 32; ++j) stg[j * kPs + lane] = gl[j];
         wave_sync();
         if constexpr (kGF3) {
 #pragma unroll
           for (int pb = 0; pb < 4; ++pb) {
             float x[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = stg[(8 * g4 + e) * kGst + 16 * pb + l16];
+            for (int e = 0; e < 8; ++e) x[e] = stg[(8 * g4 + e) * kPs + 16 * pb + l16];
             split8x3(x, g3[pb][0], g3[pb][1], g3[pb][2]);
           }
         } else {
 #pragma unroll
           for (int ks = 8 * h; ks < 8 * h + 8; ++ks)
 #pragma unroll
-            for (int pb = 0; pb < 4; ++pb) g1[pb][ks] = stg[(4 * ks + g4 - 32 * h) * kGst + 16 * pb + l16];
+            for (int pb = 0; pb < 4; ++pb) g1[pb][ks] = stg[(4 * ks + g4 - 32 * h) * kPs + 16 * pb + l16];
         }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
           for (int cb = 2 * h; cb < 2 * h + 2; ++cb) {
-            const float* src = stg + (16 * cb + l16 - 32 * h) * kGst + 32 * ks + 8 * g4;
-            const float4 x0 = *reinterpret_cast<const float4*>(src), x1 = *reinterpret_cast<const float4*>(src + 4);
+            const float* s8 = stg + (16 * cb + l16 - 32 * h) * kPs + 32 * ks + 8 * g4;
+            const float4 x0 = *reinterpret_cast<const float4*>(s8), x1 = *reinterpret_cast<const float4*>(s8 + 4);
             const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
             split8(x, g2h[ks][cb], g2l[ks][cb]);
           }
@@ -1157,295 +1286,294 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_split(gs_config cfg, cons
       }
     }
 
-    // per-pixel state at the segment's back end (main pass) or front end (summary pass)
-    float T = 1.0f, acc = 0.0f;   // acc: suffix (main) or GC (summary)
-    if constexpr (!SUMMARY) {
+    // per-pixel state at the segment's back end: T, and the suffix sum of w (g . f) behind it
+    float T = 1.0f, acc = 0.0f;
+    {
       const float tf = inside ? Tfin[pix] : 1.0f;
       if (nseg == 1 || seg == nseg - 1) T = tf;
       if (nseg > 1 && fs.tcnt) {
         // the forward's state: T at the segment's end and the suffix colour sum
-        const int64_t slot = (int64_t)fs.tbase[tile] + seg, o = slot * kTilePx + tid;
+        const int64_t slot = (int64_t)fs.tbase[tile] + seg, o = slot * kTilePx + rg.px;
         if (fs.info[o] & kInfoActive) T = fs.Te[o];
         acc = gdot;
       } else if (nseg > 1) {
         const int64_t w0 = (int64_t)wi - seg;
         float tb = 1.0f;   // transmittance in front of segment s
         for (int s = 0; s < nseg; ++s) {
-          const float P = segP[(w0 + s) * kTilePx + tid], GC = segGC[(w0 + s) * kTilePx + tid];
+          const float P = segP[(w0 + s) * kTilePx + rg.px], GC = segGC[(w0 + s) * kTilePx + rg.px];
           if (s > seg) acc = __builtin_fmaf(tb, GC, acc);
           tb *= P;
           if (s == seg && seg < nseg - 1) T = tb;
         }
       }
     }
-
-    SStage<NS> st;
-    const int n_batches = (b0 - a0 + kB - 1) / kB;
-    // list range [lo, hi) of batch bi: the main pass from the back, the summary pass from the front
-    auto batch_lo = [&](int bi) { return SUMMARY ? a0 + bi * kB : max(a0, b0 - (bi + 1) * kB); };
-    auto batch_hi = [&](int bi) { return SUMMARY ? min(b0, a0 + (bi + 1) * kB) : b0 - bi * kB; };
-    if (n_batches > 0) {
-      st.fetch(vals, c.start + batch_lo(0), batch_hi(0) - batch_lo(0), c.item, n, rec, depth, rgb, sem, emb, n_sem, foff);
-      if (n_batches > 1) st.load_ids(vals, c.start + batch_lo(1), batch_hi(1) - batch_lo(1));
-    }
-    // one FP32 atomic per (Gaussian, channel) and (Gaussian, component) of a finished batch
-    auto flush = [&](int fb, int fcnt) {
-      const float* fdf = s_pool + kWsz + fb * kDsz;
-      const float* fgeo = s_pool + kWsz + 2 * kDsz + fb * kGsz;
-      const uint32_t* fgid = s_gid[fb];
-      if constexpr (KP <= 32) {
-        // feature gradients: Gaussian q = idx / KP, channel k = idx % KP, all LDS reads first
-        constexpr int kFl = kB * KP / 256;
-        float fv[kFl];
-        uint32_t fg[kFl];
+    // A group's features on their way: four lanes a Gaussian for an embedding (8 bytes each) and
+    // for colour and depth (a value each), QL lanes (a quad of channels each) for plain semantics.
+    constexpr int QL = EMB ? 4 : KP / 4, NP = EMB ? 1 : QL / 4;
+    float f[EMB ? 1 : 4 * NP], f0 = 0.0f;
+    uint2 fe = make_uint2(0u, 0u);
+    auto gather = [&](int grp) {
+      const float* R = Q + 8 * kGrp * (grp & (kRing / kGrp - 1));
+      uint32_t gq[NP];
 #pragma unroll
-        for (int j = 0; j < kFl; ++j) {
-          const int idx = tid + 256 * j, q = idx / KP;
-          fv[j] = fdf[q * DFS + (idx - q * KP)];
-          fg[j] = fgid[q];
-        }
+      for (int p = 0; p < NP; ++p) gq[p] = __float_as_uint(R[8 * (p * (64 / QL) + lane / QL) + 7]);
+      const uint32_t gc = __float_as_uint(R[8 * (lane >> 2) + 7]);
+      const float* a0p = (lane & 3) < 3 ? src.rgb + 3 * ((int64_t)gc + foff) + (lane & 3) : src.depth + (e0 + gc);
+      f0 = *a0p;
+      if constexpr (EMB) {
+        const uint16_t* a = src.emb + 16 * (int64_t)gc + 4 * (lane & 3);
+        if (src.vec) fe = *reinterpret_cast<const uint2*>(a);
+        else fe = make_uint2((uint32_t)a[0] | ((uint32_t)a[1] << 16), (uint32_t)a[2] | ((uint32_t)a[3] << 16));
+      } else if (src.n_sem > 0) {
+        const int k = 4 * (lane % QL) < src.n_sem ? 4 * (lane % QL) : 0;
+        const float* a = src.sem + (int64_t)src.n_sem * foff + k;
+        if (src.vec) {
 #pragma unroll
-        for (int j = 0; j < kFl; ++j) {
-          const int idx = tid + 256 * j, q = idx / KP, k = idx - q * KP;
-          const float val = fv[j];
-          if (q >= fcnt || val == 0.0f || k >= Kr) continue;
-          const uint32_t g = fg[j];
-          if (k < 3) atomicAdd(&grgb[3 * ((int64_t)g + foff) + k], val);
-          else if (k == 3) atomicAdd(&g2d[8 * ((int64_t)c.item * n + g) + 6], val);
-          else atomicAdd(&gsem[(int64_t)n_sem * ((int64_t)g + foff) + (k - 4)], val);
-        }
-      } else {
-        // (a register budget without room for the unrolled form)
-        for (int idx = tid; idx < fcnt * KP; idx += 256) {
-          const int q = idx / KP, k = idx - q * KP;
-          const float val = fdf[q * DFS + k];
-          if (val == 0.0f || k >= Kr) continue;
-          const uint32_t g = fgid[q];
-          if (k < 3) atomicAdd(&grgb[3 * ((int64_t)g + foff) + k], val);
-          else if (k == 3) atomicAdd(&g2d[8 * ((int64_t)c.item * n + g) + 6], val);
-          else atomicAdd(&gsem[(int64_t)n_sem * ((int64_t)g + foff) + (k - 4)], val);
-        }
-      }
-      for (int idx = tid; idx < fcnt * 6; idx += 256) {
-        const int q = idx / 6, comp = idx - q * 6;
-        const float4* src = reinterpret_cast<const float4*>(fgeo + idx * kGeoSlots);
-        float sum = 0.0f;
+          for (int p = 0; p < NP; ++p) {
+            const float4 x = *reinterpret_cast<const float4*>(a + (int64_t)src.n_sem * gq[p]);
+            f[4 * p] = x.x;
+            f[4 * p + 1] = x.y;
+            f[4 * p + 2] = x.z;
+            f[4 * p + 3] = x.w;
+          }
+        } else {
 #pragma unroll
-        for (int r = 0; r < kGeoSlots / 4; ++r) {
-          const float4 x = src[r];
-          sum += (x.x + x.y) + (x.z + x.w);
-        }
-        if (sum != 0.0f) {
-          const uint32_t g = fgid[q];
-          atomicAdd(&g2d[8 * ((int64_t)c.item * n + g) + comp], sum * kGeoScale[comp]);
+          for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int o = k + i < src.n_sem ? i : 0;
+              f[4 * p + i] = a[(int64_t)src.n_sem * gq[p] + o];
+            }
         }
       }
     };
-    int prev_cnt = 0;
-    for (int bi = 0; bi < n_batches; ++bi) {
-      const int lo = batch_lo(bi), hi = batch_hi(bi);
-      const int cnt = hi - lo;
-      const int buf = bi & 1;
-      float* const s_df = s_pool + kWsz + buf * kDsz;
-      float* const s_geo = s_pool + kWsz + 2 * kDsz + buf * kGsz;
-      lds_barrier();
-      st.commit_rows(s_rec, s_f, s_gid[buf], ox, oy);
-      if constexpr (!SUMMARY) {
-        for (int i = tid; i < kB * DFS; i += 256) s_df[i] = 0.0f;
-        for (int i = tid; i < kB * 6 * kGeoSlots / 4; i += 256) reinterpret_cast<float4*>(s_geo)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      lds_barrier();
-      // every wave is done with the previous batch: its sums go out while this one runs
-      if constexpr (!SUMMARY)
-        if (bi > 0) flush(buf ^ 1, prev_cnt);
-      prev_cnt = cnt;
-      // the next batch's gather: the summary pass issues it here; the main pass after its
-      // recurrence, whose register peak it would otherwise add to
-      auto fetch_next = [&]() {
-        if (bi + 1 < n_batches) {
-          st.fetch_data(batch_hi(bi + 1) - batch_lo(bi + 1), c.item, n, rec, depth, rgb, sem, emb, n_sem, foff);
-          if (bi + 2 < n_batches) st.load_ids(vals, c.start + batch_lo(bi + 2), batch_hi(bi + 2) - batch_lo(bi + 2));
+    // the gathered features to their rows: three bfloat16 parts of each value, or the value. (A
+    // part group's missing Gaussians have a row too, of whatever Gaussian 0 has; no sum uses it.)
+    auto commit = [&]() {
+      auto put4 = [&](int q, int k, const float (&x)[4]) {   // channels k .. k + 3 of Gaussian q
+        if constexpr (kGF3) {
+          uint32_t h[2], m[2], l[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){x[2 * i], x[2 * i + 1]}, bf2));
+            const float r0 = x[2 * i] - __uint_as_float(h[i] << 16), r1 = x[2 * i + 1] - __uint_as_float(h[i] & 0xffff0000u);
+            m[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){r0, r1}, bf2));
+            l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){r0 - __uint_as_float(m[i] << 16),
+                                                                             r1 - __uint_as_float(m[i] & 0xffff0000u)}, bf2));
+          }
+          uint32_t* row = reinterpret_cast<uint32_t*>(F + q * FROW) + k / 2;
+          *reinterpret_cast<uint2*>(row) = make_uint2(h[0], h[1]);
+          *reinterpret_cast<uint2*>(row + 16) = make_uint2(m[0], m[1]);
+          *reinterpret_cast<uint2*>(row + 32) = make_uint2(l[0], l[1]);
+        } else {
+          *reinterpret_cast<float4*>(F + q * FROW + k) = make_float4(x[0], x[1], x[2], x[3]);
         }
       };
-      if constexpr (SUMMARY) fetch_next();
-      const bool wave_live = __ballot((uint32_t)lo < last) != 0ull;
-      // the batch's Gaussians that can reach alpha_min in this wave's band of pixels (lane
-      // q < 32 tests Gaussian q)
-      uint32_t bmask = 0xffffffffu;
-      if constexpr (!SUMMARY) {
-        bool hit = false;
-        if (wave_live && lane < kB && lane < cnt) hit = band_reaches(load_rec(s_rec, lane), bx0, bx1, by0, by1, amin);
-        bmask = (uint32_t)__ballot(hit);
+      // the four lanes of a Gaussian put colour and depth together
+      {
+        const float x1 = dpp_xor1(f0), x2 = dpp_xor2(f0), x3 = dpp_xor2(x1);
+        const float x[4] = {f0, x1, x2, x3};   // of the Gaussian's lane 0
+        if ((lane & 3) == 0) put4(lane >> 2, 0, x);
       }
-      if (!SUMMARY && !wave_live) fetch_next();
-      if (wave_live) {
-        // GF^T[i][p] in single precision (it decides dL/dalpha, where terms cancel):
-        // v_mfma_f32_16x16x4f32, A = F (i = Gaussian 16 bq + l16, k = channel 4 ks + g4), B = G^T
-        uint32_t X[4][8];
-        if constexpr (SUMMARY) {
-          v4f gfa[4][2];
+      if constexpr (EMB) {
+        // bfloat16 values: the other parts are zero, and so are the channels past the embedding
+        const int k = 4 + 4 * (lane & 3);
+        uint32_t* row = reinterpret_cast<uint32_t*>(F + (lane >> 2) * FROW) + k / 2;
+        const uint2 z = make_uint2(0u, 0u);
+        *reinterpret_cast<uint2*>(row) = fe;
+        *reinterpret_cast<uint2*>(row + 16) = z;
+        *reinterpret_cast<uint2*>(row + 32) = z;
+      } else {
+        const int k = 4 * (lane % QL);
 #pragma unroll
-          for (int pb = 0; pb < 4; ++pb) gfa[pb][0] = gfa[pb][1] = zero4();
+        for (int p = 0; p < NP; ++p) {
+          float x[4];
 #pragma unroll
-          for (int bq = 0; bq < 2; ++bq)
+          for (int i = 0; i < 4; ++i) x[i] = k + i < src.n_sem ? f[4 * p + i] : 0.0f;
+          if (k < NS) put4(p * (64 / QL) + lane / QL, 4 + k, x);
+        }
+      }
+    };
+    if constexpr (EMB) {   // channels 20 .. 31
+      for (int i = lane; i < kGrp * 18; i += 64)
+        reinterpret_cast<uint32_t*>(F)[(i / 18) * FROW + 10 + 16 * ((i % 18) / 6) + i % 6] = 0u;
+    }
+
+    // the sums of a finished group of cnt Gaussians to memory; L neighbouring lanes take the
+    // values of one Gaussian
+    auto flush = [&](int grp, int cnt) {
+      const float* R = Q + 8 * kGrp * (grp & (kRing / kGrp - 1));
+      const int n_sem = opaque(src.n_sem), total = n_sem + 10;
+      const int ls = total <= 16 ? 4 : total <= 32 ? 5 : 6, L = 1 << ls;
+      for (int o = lane & (L - 1); o < total; o += L) {
+        float* base;
+        int stride, col;
+        float scale = 1.0f;
+        if (o < n_sem) {
+          base = out.gsem + n_sem * foff + o;
+          stride = n_sem;
+          col = 4 + o;
+        } else if (o < n_sem + 3) {
+          base = out.grgb + 3 * foff + (o - n_sem);
+          stride = 3;
+          col = o - n_sem;
+        } else {
+          const int k = o - n_sem - 3;
+          base = out.g2d + 8 * e0 + k;
+          stride = 8;
+          col = k < 6 ? KP + k : 3;
+          if (k < 6) scale = kGeoScale[k];
+        }
+        for (int e = lane >> ls; e < cnt; e += 64 >> ls) {
+          const float val = A[e * AROW + col];
+          if (val != 0.0f) atomicAdd(base + (int64_t)stride * __float_as_uint(R[8 * e + 7]), val * scale);
+        }
+      }
+    };
+
+    // this lane's entry of the 64 at hand (ra, rb: its record), list position hi - 1 - lane
+    auto load_id = [&](int hi) -> uint32_t { return hi - 1 - lane >= a0 ? vals[c.start + hi - 1 - lane] : 0u; };
+    auto load_half = [&](int hi, uint32_t g, int part) -> float4 {
+      return hi - 1 - lane >= a0 ? reinterpret_cast<const float4*>(rec + kRecFloats * (e0 + g))[part]
+                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    uint32_t gid = load_id(b0);
+    float4 ra = load_half(b0, gid, 0), rb = load_half(b0, gid, 1);
+    uint32_t gnext = load_id(b0 - 64);
+    int tail = 0, done = 0, issued = 0;   // entries in the ring so far; groups worked on, gathered
+    for (int hi = b0;; hi -= 64) {
+      {
+        const LRec r = local_rec(ra, rb, ox, oy);
+        const bool hit = hi - 1 - lane >= a0 && band_reaches(r, rg.x0, rg.x1, rg.y0, rg.y1, amin);
+        const uint64_t m = __ballot(hit);
+        if (hit) {
+          const int at = tail + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+          float4* d = reinterpret_cast<float4*>(Q + 8 * (at & (kRing - 1)));
+          d[0] = r.m;
+          d[1] = make_float4(r.c.x, r.c.y, __int_as_float(hi - 1 - lane), __uint_as_float(gid));
+        }
+        tail += __builtin_popcountll(m);
+      }
+      const bool fin = hi - 64 <= a0;
+      if (!fin) {
+        gid = gnext;
+        ra = load_half(hi - 64, gid, 0);
+        rb = load_half(hi - 64, gid, 1);
+        gnext = load_id(hi - 128);
+      } else if (lane < 2 * (-tail & (kGrp - 1))) {
+        // a part group's missing entries: a negative opacity, so no alpha reaches the threshold
+        reinterpret_cast<float4*>(Q + 8 * ((tail + (lane >> 1)) & (kRing - 1)))[lane & 1] =
+            make_float4(0.f, (lane & 1) ? -1.f : 0.f, 0.f, 0.f);
+      }
+      wave_sync();
+      const int ready = fin ? (tail + kGrp - 1) / kGrp : tail / kGrp;
+      if (issued == done && ready > done) gather(issued++);
+      while (issued > done && (fin || ready > done + 1)) {
+        wave_sync();
+        commit();
+        if (done > 0) flush(done - 1, kGrp);
+        if (ready > issued) gather(issued++);
+        wave_sync();
+        const int cnt = min(kGrp, tail - kGrp * done);
+        const float* R = Q + 8 * kGrp * (done & (kRing / kGrp - 1));
+        // g . f: A = F (i = Gaussian l16 of the group, k = channel); D lane (row g4, l16): Gaussians
+        // 4 g4 + r of pixel 16 pb + l16. The transpose gives every lane its own pixel's values:
+        // Y4[qq / 4][qq % 4] = g . f of Gaussian qq of the group
+        uint32_t Y4[4][4];
+        {
+          v4f gfa[4];
+#pragma unroll
+          for (int pb = 0; pb < 4; ++pb) gfa[pb] = zero4();
+          if constexpr (kGF3) {
+            v8bf fa[3];
+#pragma unroll
+            for (int part = 0; part < 3; ++part)
+              fa[part] = *reinterpret_cast<const v8bf*>(F + l16 * FROW + 16 * part + 4 * g4);
+#pragma unroll
+            for (int pb = 0; pb < 4; ++pb) gfa[pb] = mma6(fa, g3[pb], gfa[pb]);
+          } else {
 #pragma unroll
             for (int ks = 0; ks < KP / 4; ++ks) {
-              const float a = s_f[(16 * bq + l16) * FST + 4 * ks + g4];
+              const float a = F[l16 * FROW + 4 * ks + g4];
 #pragma unroll
-              for (int pb = 0; pb < 4; ++pb)
-                gfa[pb][bq] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, g1[pb][ks], gfa[pb][bq], 0, 0, 0);
+              for (int pb = 0; pb < 4; ++pb) gfa[pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, g1[pb][ks], gfa[pb], 0, 0, 0);
             }
+          }
 #pragma unroll
           for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              X[pb][r] = __float_as_uint(gfa[pb][0][r]);
-              X[pb][4 + r] = __float_as_uint(gfa[pb][1][r]);
-            }
+            for (int r = 0; r < 4; ++r) Y4[pb][r] = __float_as_uint(gfa[pb][r]);
         }
-        // lane row g4 held Gaussians {4 g4 + r, 16 + 4 g4 + r} of all four pixel rows; now
-        // every lane holds its own pixel's values: X[g][4 bq + r] = gf of Gaussian 16 bq + 4 g + r
-        if constexpr (SUMMARY) block_transpose(X);
-        if constexpr (SUMMARY) {
+        block_transpose(Y4);
+        // reverse recurrence over the group (T recovered with the hardware reciprocal)
 #pragma unroll
-          for (int q = 0; q < kB; ++q) {
-            const LRec rq = load_rec(s_rec, q);
+        for (int gb = 0; gb < kGrp / GG; ++gb) {
+          float V[6 * GG];   // V[6 r + k]: component k of the geometric terms of Gaussian GG gb + r
+#pragma unroll
+          for (int r = 0; r < GG; ++r) {
+            const int qq = GG * gb + r;
+            const LRec rq = load_rec(R, qq);
+            const uint32_t pos = __float_as_uint(R[8 * qq + 6]);
             float dx, dy, t;
-            const float araw = rq.c.y * __builtin_amdgcn_exp2f(local_power2(lx, ly, rq, dx, dy, t));
-            const bool act = (q < cnt) & ((uint32_t)(lo + q) < last) & (araw >= amin);
-            const float w = fminf(amax, araw) * T;
-            const float gf = __uint_as_float(X[(q >> 2) & 3][4 * (q >> 4) + (q & 3)]);
-            acc = act ? __builtin_fmaf(w, gf, acc) : acc;
-            T = act ? T - w : T;
+            const float G = __builtin_amdgcn_exp2f(local_power2(rg.lx, rg.ly, rq, dx, dy, t));
+            const float araw = rq.c.y * G;
+            const bool act = (pos < last) & (araw >= amin);
+            const float a = fminf(amax, araw);
+            const float rom = __builtin_amdgcn_rcpf(1.0f - a);
+            const float Tq = act ? T * rom : T;   // transmittance in front of this Gaussian
+            const float wq = act ? a * Tq : 0.0f;
+            const float gf = __uint_as_float(Y4[qq >> 2][qq & 3]);
+            const float dalpha = Tq * gf - acc * rom;
+            acc = act ? __builtin_fmaf(gf, wq, acc) : acc;
+            T = Tq;
+            const bool unclamped = act & (araw < amax);
+            const float dpow = unclamped ? dalpha * araw : 0.0f;
+            const float dop = unclamped ? dalpha * G : 0.0f;
+            W[qq * kPs + lane] = wq;
+            // d power / d (mean2d, A, B, C) up to the per-component factors of kGeoScale
+            const float pdx = dpow * dx, pdy = dpow * dy;
+            V[6 * r + 0] = dpow * __builtin_fmaf(rq.m.z, dx, t);   // 2a dx + b dy
+            V[6 * r + 1] = dpow * __builtin_fmaf(rq.m.w, dx, 2.0f * (rq.c.x * dy));
+            V[6 * r + 2] = pdx * dx;
+            V[6 * r + 3] = pdx * dy;
+            V[6 * r + 4] = pdy * dy;
+            V[6 * r + 5] = dop;                                  // d/d opacity
           }
-        } else {
-          // reverse recurrence, one 16-Gaussian block at a time (back to front), each with
-          // its own GF^T block: Y[g][r] = gf of Gaussian 16 bq + 4 g + r after the transpose
+          float Y[3];
+          geo_reduce<GG>(V, Y);
+          // the Gaussian and first component of this lane's three sums
+          const int qd = GG * gb + (GG == 4 ? g4 : g4 >> 1);
+          const int k0 = GG == 4 ? 3 * (l16 >> 3) : 3 * (g4 & 1);
+          if ((l16 & (GG == 4 ? 7 : 15)) == 0)
 #pragma unroll
-          for (int bq = 1; bq >= 0; --bq) {
-            uint32_t Y4[4][4];
-            {
-              v4f gfa[4];
-#pragma unroll
-              for (int pb = 0; pb < 4; ++pb) gfa[pb] = zero4();
-              if constexpr (kGF3) {
-                // A = F (i = Gaussian 16 bq + l16, k = channel 8 g4 + e)
-                const float* src = s_f + (16 * bq + l16) * FST + 8 * g4;
-                const float4 f0 = *reinterpret_cast<const float4*>(src), f1 = *reinterpret_cast<const float4*>(src + 4);
-                const float x[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
-                v8bf fa[3];
-                split8x3(x, fa[0], fa[1], fa[2]);
-#pragma unroll
-                for (int pb = 0; pb < 4; ++pb) gfa[pb] = mma6(fa, g3[pb], gfa[pb]);
-              } else {
-#pragma unroll
-                for (int ks = 0; ks < KP / 4; ++ks) {
-                  const float a = s_f[(16 * bq + l16) * FST + 4 * ks + g4];
-#pragma unroll
-                  for (int pb = 0; pb < 4; ++pb)
-                    gfa[pb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, g1[pb][ks], gfa[pb], 0, 0, 0);
-                }
-              }
-#pragma unroll
-              for (int pb = 0; pb < 4; ++pb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) Y4[pb][r] = __float_as_uint(gfa[pb][r]);
-            }
-            block_transpose(Y4);
-            float* Wp = s_pool + wave * 16 * kPs;
-            bool any = false;
-#pragma unroll
-            for (int gb = 16 / GG - 1; gb >= 0; --gb) {
-              // a group none of whose Gaussians can reach the wave's band takes no pixel of it
-              if (((bmask >> (16 * bq + GG * gb)) & ((1u << GG) - 1u)) == 0u) {
-#pragma unroll
-                for (int r = 0; r < GG; ++r) Wp[(GG * gb + r) * kPs + lane] = 0.0f;
-                continue;
-              }
-              float V[6 * GG];   // V[6 r + k]: component k of the geometric terms of Gaussian GG gb + r
-              bool gact = false;
-#pragma unroll
-              for (int r = GG - 1; r >= 0; --r) {
-                const int qq = GG * gb + r, q = 16 * bq + qq;
-                const LRec rq = load_rec(s_rec, q);
-                float dx, dy, t;
-                const float G = __builtin_amdgcn_exp2f(local_power2(lx, ly, rq, dx, dy, t));
-                const float araw = rq.c.y * G;
-                const bool act = (q < cnt) & ((uint32_t)(lo + q) < last) & (araw >= amin);
-                const float a = fminf(amax, araw);
-                const float rom = __builtin_amdgcn_rcpf(1.0f - a);
-                const float Tq = act ? T * rom : T;   // transmittance in front of this Gaussian
-                const float w = act ? a * Tq : 0.0f;
-                const float gf = __uint_as_float(Y4[qq >> 2][qq & 3]);
-                const float dalpha = Tq * gf - acc * rom;
-                acc = act ? __builtin_fmaf(gf, w, acc) : acc;
-                T = Tq;
-                const bool unclamped = act & (araw < amax);
-                const float dpow = unclamped ? dalpha * araw : 0.0f;
-                const float dop = unclamped ? dalpha * G : 0.0f;
-                Wp[qq * kPs + lane] = w;
-                gact |= act;
-                // d power / d (mean2d, A, B, C) up to the per-component factors of kGeoScale
-                const float pdx = dpow * dx, pdy = dpow * dy;
-                V[6 * r + 0] = dpow * __builtin_fmaf(rq.m.z, dx, t);   // 2a dx + b dy
-                V[6 * r + 1] = dpow * __builtin_fmaf(rq.m.w, dx, 2.0f * (rq.c.x * dy));
-                V[6 * r + 2] = pdx * dx;
-                V[6 * r + 3] = pdx * dy;
-                V[6 * r + 4] = pdy * dy;
-                V[6 * r + 5] = dop;                                  // d/d opacity
-              }
-              if (__ballot(gact) != 0ull) {
-                any = true;
-                float Y[3];
-                geo_reduce<GG>(V, Y);
-                // Gaussian and first component of this lane's three sums
-                const int qd = 16 * bq + GG * gb + (GG == 4 ? g4 : g4 >> 1);
-                const int k0 = GG == 4 ? 3 * (l16 >> 3) : 3 * (g4 & 1);
-                float* dst = s_geo + (qd * 6 + k0) * kGeoSlots + wave * 4 + (l16 & 3);
-                if ((l16 & 4) == 0 && (GG == 4 || l16 < 8))
-#pragma unroll
-                  for (int j = 0; j < 3; ++j) dst[j * kGeoSlots] = Y[j];
-              }
-            }
-            if (bq == 0) fetch_next();
-            wave_sync();
-            if (__ballot(any) != 0ull) {
-              // A = W^T (i = Gaussian l16 of the block, k = pixel 32 ks + 8 g4 + e)
-              v8bf wh[2], wl[2];
-#pragma unroll
-              for (int ks = 0; ks < 2; ++ks) {
-                const float* src = Wp + l16 * kPs + 32 * ks + 8 * g4;
-                const float4 w0 = *reinterpret_cast<const float4*>(src), w1 = *reinterpret_cast<const float4*>(src + 4);
-                const float x[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-                split8(x, wh[ks], wl[ks]);
-              }
-#pragma unroll
-              for (int cb = 0; cb < CB; ++cb) {
-                v4f d = zero4();
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) d = mma3(wh[ks], wl[ks], g2h[ks][cb], g2l[ks][cb], d);
-                // D[i][c]: Gaussian 16 bq + 4 g4 + r, channel 16 cb + l16
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  if (d[r] != 0.0f) atomicAdd(&s_df[(16 * bq + 4 * g4 + r) * DFS + 16 * cb + l16], d[r]);
-              }
-            }
-            wave_sync();   // the block's W is consumed before the next block overwrites it
-          }
+            for (int j = 0; j < 3; ++j) A[qd * AROW + KP + k0 + j] = Y[j];
         }
+        wave_sync();
+        // dF: A = W^T (i = Gaussian l16 of the group, k = pixel 32 ks + 8 g4 + e)
+        v8bf wh[2], wl2[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          const float* s8 = W + l16 * kPs + 32 * ks + 8 * g4;
+          const float4 w0 = *reinterpret_cast<const float4*>(s8), w1 = *reinterpret_cast<const float4*>(s8 + 4);
+          const float x[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+          split8(x, wh[ks], wl2[ks]);
+        }
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          v4f d = zero4();
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) d = mma3(wh[ks], wl2[ks], g2h[ks][cb], g2l[ks][cb], d);
+          // D[i][c]: Gaussian 4 g4 + r of the group, channel 16 cb + l16
+#pragma unroll
+          for (int r = 0; r < 4; ++r) A[(4 * g4 + r) * AROW + 16 * cb + l16] = d[r];
+        }
+        ++done;
       }
+      if (fin) break;
     }
-    // the work item's last batch
-    if constexpr (!SUMMARY) {
-      if (n_batches > 0) {
-        lds_barrier();
-        flush((n_batches - 1) & 1, prev_cnt);
-      }
-    }
-    if constexpr (SUMMARY) {
-      segP[(int64_t)wi * kTilePx + tid] = T;
-      segGC[(int64_t)wi * kTilePx + tid] = acc;
-    }
+    wave_sync();
+    if (done > 0) flush(done - 1, tail - kGrp * (done - 1));
+    wave_sync();
   }
 }
 
@@ -1602,7 +1730,7 @@ int launch_fwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   return launch_status();
 }
 
-template <int NS>
+template <int NS, bool EMB>
 int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items, int n_items,
                  int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& fwd,
                  const gs_images& gin, float* g2d, const gs_grads& gr, void* seg_ws, int64_t cap, hipStream_t s) {
@@ -1617,16 +1745,19 @@ int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   if (st) return st;
   hipLaunchKernelGGL(k_seg_list, dim3((unsigned)ceil_div(n_tiles, 256)), dim3(256), 0, s, w.cnt, w.base, w.total,
                      n_tiles, cfg.tile_order, w.max_segs, w.work, w.ctl, nullptr, nullptr);
-  const int grid_sum = resident_blocks(k_render_bwd_split<NS, true>, 256, 0);
-  const int grid_main = resident_blocks(k_render_bwd_split<NS, false>, 256, 0);
-  if (!grid_sum || !grid_main) return GS_ERR_HIP;
-  if (!fs.tcnt)
-    hipLaunchKernelGGL((k_render_bwd_split<NS, true>), dim3(grid_sum), dim3(256), 0, s, cfg, g.rgb, g.sem, g.emb,
-                       cfg.n_sem, p.rec, p.depth, g.n, items, n_items, vals, ranges, fwd.T, fwd.n_contrib, gin.color,
-                       g2d, gr.rgb, gr.sem, w.work, w.ctl, w.lmax, w.P, w.GC, fs);
-  hipLaunchKernelGGL((k_render_bwd_split<NS, false>), dim3(grid_main), dim3(256), 0, s, cfg, g.rgb, g.sem, g.emb,
-                     cfg.n_sem, p.rec, p.depth, g.n, items, n_items, vals, ranges, fwd.T, fwd.n_contrib, gin.color, g2d,
-                     gr.rgb, gr.sem, w.work, w.ctl, w.lmax, w.P, w.GC, fs);
+  const int grid_main = resident_blocks(k_render_bwd_main<NS, EMB>, 256, 0);
+  if (!grid_main) return GS_ERR_HIP;
+  if (!fs.tcnt) {
+    const int grid_sum = resident_blocks(k_seg_summary<NS>, 256, 0);
+    if (!grid_sum) return GS_ERR_HIP;
+    hipLaunchKernelGGL(k_seg_summary<NS>, dim3(grid_sum), dim3(256), 0, s, cfg, g.rgb, g.sem, g.emb, cfg.n_sem, p.rec,
+                       p.depth, g.n, items, n_items, vals, ranges, fwd.n_contrib, gin.color, w.work, w.ctl, w.lmax, w.P,
+                       w.GC);
+  }
+  const FeatSrc src{g.rgb, g.sem, p.depth, g.emb, cfg.n_sem, sem_vec(g, cfg.n_sem)};
+  hipLaunchKernelGGL((k_render_bwd_main<NS, EMB>), dim3(grid_main), dim3(256), 0, s, cfg, src, p.rec, g.n, items, n_items,
+                     vals, ranges, fwd.T, fwd.n_contrib, gin.color, GradDst{gr.rgb, gr.sem, g2d}, w.work, w.ctl, w.lmax,
+                     w.P, w.GC, fs);
   return launch_status();
 }
 
@@ -1664,10 +1795,12 @@ int launch_render_bwd_split(const gs_config& cfg, const gs_gaussians& g, const g
                             int64_t cap, hipStream_t s) {
   const int ns = cfg.n_sem;
   if (cap < 0) return GS_ERR_WORKSPACE;
+  if (g.emb)
+    return launch_bwd_s<28, true>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
   if (ns <= 28)
-    return launch_bwd_s<28>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
+    return launch_bwd_s<28, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
   if (ns <= 60)
-    return launch_bwd_s<60>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
+    return launch_bwd_s<60, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
   return GS_ERR_UNSUPPORTED;
 }
 
