@@ -20,7 +20,7 @@ int launch_status() { return hip_status(hipGetLastError()); }
 // kernels (other translation units)
 int launch_preprocess(const gs_config&, const gs_gaussians&, const gs_view*, int, const gs_item*, const gs_projected&,
                       hipStream_t);
-int launch_preprocess_bwd(const gs_config&, const gs_gaussians&, const gs_view*, int, const gs_item*, const float*,
+int launch_preprocess_bwd(const gs_config&, const gs_gaussians&, const gs_view*, int, const gs_item*, const double*,
                           const int32_t*, const gs_grads&, hipStream_t);
 size_t bin_sort_workspace(int64_t E, int64_t cap, int64_t n_tiles);
 int launch_bin_sort(const gs_config&, const gs_projected&, const gs_item*, int, int64_t, int, int64_t, void*, uint64_t*,
@@ -30,14 +30,14 @@ int launch_bin_sort(const gs_config&, const gs_projected&, const gs_item*, int, 
       const uint32_t*, const gs_images&, hipStream_t
 #define GS_RENDER_BWD_ARGS                                                                                 \
   const gs_config&, const gs_gaussians&, const gs_projected&, const gs_item*, int, int, const uint32_t*, \
-      const uint32_t*, const gs_images&, const gs_images&, float*, const gs_grads&, hipStream_t
+      const uint32_t*, const gs_images&, const gs_images&, double*, const gs_grads&, hipStream_t
 int launch_render_fwd_valu(GS_RENDER_FWD_ARGS);
 int launch_render_bwd_valu(GS_RENDER_BWD_ARGS);
 int launch_render_fwd_mfma(GS_RENDER_FWD_ARGS);
 int launch_render_bwd_mfma(GS_RENDER_BWD_ARGS);
 int launch_render_fwd_split(GS_RENDER_FWD_ARGS);
 int launch_render_bwd_split(const gs_config&, const gs_gaussians&, const gs_projected&, const gs_item*, int, int,
-                            const uint32_t*, const uint32_t*, const gs_images&, const gs_images&, float*,
+                            const uint32_t*, const uint32_t*, const gs_images&, const gs_images&, double*,
                             const gs_grads&, void*, int64_t, hipStream_t);
 size_t render_seg_workspace(int n_tiles, int64_t dup_capacity, int seg);
 int64_t render_seg_capacity(int n_tiles, int seg, size_t bytes);
@@ -58,7 +58,7 @@ int launch_render_fwd(const gs_config& cfg, const gs_gaussians& g, const gs_proj
 }
 int launch_render_bwd(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items,
                       int n_items, int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& fwd,
-                      const gs_images& gin, float* g2d, const gs_grads& gr, void* seg_ws, int64_t cap,
+                      const gs_images& gin, double* g2d, const gs_grads& gr, void* seg_ws, int64_t cap,
                       hipStream_t s) {
   if (n_tiles == 0) return GS_OK;
   if (cfg.variant == 1)
@@ -90,6 +90,8 @@ int launch_distill(const gs_item*, int, int64_t, int, const float*, const float*
 int launch_agree(const gs_item*, int, int64_t, int, const float*, const float*, unsigned long long*, hipStream_t);
 int launch_fill_f32(float*, int64_t, float, hipStream_t);
 int launch_zero_f32(float* const* p, const int64_t* n, int count, hipStream_t s);
+int launch_zero_grads(double* rec, const int32_t* radius, int64_t entries, float* const* p, const int64_t* n, int count,
+                      hipStream_t s);
 
 namespace {
 
@@ -121,8 +123,6 @@ bool gauss_ok(const gs_gaussians* g, bool need_features) {
   if (need_features && !g->rgb) return false;
   return true;
 }
-
-constexpr int64_t kSortBwdRecord = 8;  // floats per (item, Gaussian) of 2D gradients
 
 }  // namespace
 }  // namespace gs
@@ -217,7 +217,7 @@ int gs_workspace_size(int kind, const gs_config* cfg, int32_t n_items, int64_t n
       *bytes = bin_sort_workspace((int64_t)n_items * n_gauss, dup_capacity, n_tiles);
       return GS_OK;
     case GS_WS_RENDER_BWD:
-      *bytes = align_up(sizeof(float) * kSortBwdRecord * (size_t)n_items * (size_t)n_gauss) + align_up(head_bwd_workspace()) +
+      *bytes = align_up(sizeof(double) * kGradRec * (size_t)n_items * (size_t)n_gauss) + align_up(head_bwd_workspace()) +
                render_seg_workspace(n_tiles, dup_capacity, render_seg_len(*cfg));
       return GS_OK;
     case GS_WS_LOSS:
@@ -389,7 +389,7 @@ int gs_render_bwd(const gs_config* cfg, const gs_gaussians* g, const gs_projecte
     if (fwd->state && render_state_capacity(n_tiles, 4 + cfg->n_sem, render_seg_len(*cfg), fwd->state_bytes) < 0)
       return GS_ERR_WORKSPACE;
   }
-  const size_t rec_bytes = align_up(sizeof(float) * kSortBwdRecord * (size_t)n_items * (size_t)g->n);
+  const size_t rec_bytes = align_up(sizeof(double) * kGradRec * (size_t)n_items * (size_t)g->n);
   const size_t head_bytes = align_up(head_bwd_workspace());
   if (!workspace || ws_bytes < rec_bytes + head_bytes) return GS_ERR_WORKSPACE;
   // the rest holds the segment work list of the reverse pass, sized for a duplicate
@@ -401,10 +401,10 @@ int gs_render_bwd(const gs_config* cfg, const gs_gaussians* g, const gs_projecte
   const int64_t n = g->n;
   gs_grads gr = *grads;
   if (learned) gr.sem = grads->emb;   // the semantic channels' gradient is the embedding's
-  float* const zp[4] = {(float*)workspace, gr.rgb, cfg->n_sem > 0 ? gr.sem : nullptr, gr.pose};
   const int64_t fv = cfg->view_features ? n_views : 1;   // feature blocks (one per view, or shared)
-  const int64_t zn[4] = {kSortBwdRecord * (int64_t)n_items * n, 3 * n * fv, (int64_t)cfg->n_sem * n * fv, 6ll * n_views};
-  int st = launch_zero_f32(zp, zn, 4, s);
+  float* const zp[3] = {gr.rgb, cfg->n_sem > 0 ? gr.sem : nullptr, gr.pose};
+  const int64_t zn[3] = {3 * n * fv, (int64_t)cfg->n_sem * n * fv, 6ll * n_views};
+  int st = launch_zero_grads((double*)workspace, proj->radius, (int64_t)n_items * n, zp, zn, 3, s);
   if (st) return st;
   if (head) {
     st = launch_head_bwd(items_dev, n_items, fwd->n_pixels, 4 + cfg->n_sem, *head, fwd->color, grad_in->logits,
@@ -414,11 +414,11 @@ int gs_render_bwd(const gs_config* cfg, const gs_gaussians* g, const gs_projecte
   }
   if (n == 0) return GS_OK;
   if (render) {
-    st = launch_render_bwd(*cfg, *g, *proj, items_dev, n_items, n_tiles, vals, ranges, *fwd, *grad_in, (float*)workspace,
+    st = launch_render_bwd(*cfg, *g, *proj, items_dev, n_items, n_tiles, vals, ranges, *fwd, *grad_in, (double*)workspace,
                            gr, seg_ws, cap, s);
     if (st) return st;
   }
-  return launch_preprocess_bwd(*cfg, *g, views_dev, n_views, items_dev, (const float*)workspace, proj->radius, gr, s);
+  return launch_preprocess_bwd(*cfg, *g, views_dev, n_views, items_dev, (const double*)workspace, proj->radius, gr, s);
 }
 
 int gs_adam_step(float* param, const float* grad, float* m, float* v, int64_t n, float lr, float beta1, float beta2,

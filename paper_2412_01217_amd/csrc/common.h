@@ -17,6 +17,11 @@ __host__ __device__ inline int tile_shift(const gs_config& cfg) {
   return cfg.tile_w == 8 ? 3 : cfg.tile_w == 32 ? 5 : cfg.tile_w == 64 ? 6 : 4;
 }
 constexpr int kRecFloats = 8;      // per (item, Gaussian) render record
+// Per (item, Gaussian) gradient record of the reverse pass, in double precision: 0-1 mean2d,
+// 2-4 conic, 5 opacity, 6 depth. Single-precision sums of many tiles' parts differ with the order
+// of the atomics, and the projection's backward magnifies that where the conic's parts cancel; 64
+// bytes are one atomic request all the same.
+constexpr int kGradRec = 8;
 
 // Records the last HIP error for gs_last_hip_error(); returns GS_ERR_HIP if e != success.
 int hip_status(hipError_t e);

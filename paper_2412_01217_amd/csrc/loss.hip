@@ -642,7 +642,22 @@ __global__ __launch_bounds__(256) void k_zero_multi(ZeroList z) {
   }
 }
 
-int launch_zero_f32(float* const* p, const int64_t* n, int count, hipStream_t s) {
+// The same, and the gradient records of the visible entries, radius > 0: no other record is added
+// to or read. Four lanes a record, 16 bytes each.
+__global__ __launch_bounds__(256) void k_zero_grads(ZeroList z, float4* __restrict__ rec,
+                                                    const int32_t* __restrict__ radius, int64_t entries) {
+  constexpr int kPer = kGradRec / 2;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x, i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < kPer * entries; i += step)
+    if (radius[i / kPer] > 0) rec[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int64_t tot = z.end[3];
+  for (int64_t i = i0; i < tot; i += step) {
+    const int k = (i >= z.end[0]) + (i >= z.end[1]) + (i >= z.end[2]);
+    z.p[k][i - (k > 0 ? z.end[k - 1] : 0)] = 0.0f;
+  }
+}
+
+static ZeroList zero_list(float* const* p, const int64_t* n, int count) {
   ZeroList z{};
   int64_t run = 0;
   for (int k = 0; k < 4; ++k) {
@@ -651,9 +666,24 @@ int launch_zero_f32(float* const* p, const int64_t* n, int count, hipStream_t s)
     run += use ? n[k] : 0;
     z.end[k] = run;
   }
-  if (run == 0) return GS_OK;
-  const int64_t blocks = std::min<int64_t>(ceil_div(run, 256), 4096);
+  return z;
+}
+
+int launch_zero_f32(float* const* p, const int64_t* n, int count, hipStream_t s) {
+  const ZeroList z = zero_list(p, n, count);
+  if (z.end[3] == 0) return GS_OK;
+  const int64_t blocks = std::min<int64_t>(ceil_div(z.end[3], 256), 4096);
   hipLaunchKernelGGL(k_zero_multi, dim3((unsigned)blocks), dim3(256), 0, s, z);
+  return launch_status();
+}
+
+int launch_zero_grads(double* rec, const int32_t* radius, int64_t entries, float* const* p, const int64_t* n, int count,
+                      hipStream_t s) {
+  const ZeroList z = zero_list(p, n, count);
+  const int64_t most = std::max(z.end[3], kGradRec / 2 * entries);
+  if (most == 0) return GS_OK;
+  const int64_t blocks = std::min<int64_t>(ceil_div(most, 256), 8192);
+  hipLaunchKernelGGL(k_zero_grads, dim3((unsigned)blocks), dim3(256), 0, s, z, (float4*)rec, radius, entries);
   return launch_status();
 }
 

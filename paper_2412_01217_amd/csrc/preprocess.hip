@@ -199,12 +199,12 @@ __global__ __launch_bounds__(256) void k_preprocess(gs_config cfg, gs_gaussians 
   }
 }
 
-// Backward. g2d holds, per (item, Gaussian), the gradient of the loss with respect to
-// mean2d (x, y), conic (A, B, C), opacity and the composited depth channel, [E][8].
+// Backward. g2d holds, per visible (item, Gaussian), the gradient of the loss with respect to
+// mean2d (x, y), conic (A, B, C), opacity and the composited depth channel, [E][kGradRec].
 __global__ __launch_bounds__(256) void k_preprocess_bwd(gs_config cfg, gs_gaussians g,
                                                         const gs_view* __restrict__ views, int n_views,
                                                         const gs_item* __restrict__ items,
-                                                        const float* __restrict__ g2d, const int32_t* __restrict__ radius,
+                                                        const double* __restrict__ g2d, const int32_t* __restrict__ radius,
                                                         gs_grads out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool live = i < g.n;
@@ -231,9 +231,9 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(gs_config cfg, gs_gaussi
         if (radius[e] <= 0) continue;
         const gs_item it = items[k];
         const Lvl L = footprint(cfg, it, c, G.s[0]);
-        const float4 ga = *reinterpret_cast<const float4*>(g2d + 8 * e);
-        const float4 gb = *reinterpret_cast<const float4*>(g2d + 8 * e + 4);
-        const double dmx = ga.x, dmy = ga.y, dA = ga.z, dB = ga.w, dC = gb.x, dO = gb.y, dZ = gb.z;
+        const double2* gr = reinterpret_cast<const double2*>(g2d + kGradRec * e);
+        const double2 g01 = gr[0], g23 = gr[1], g45 = gr[2];
+        const double dmx = g01.x, dmy = g01.y, dA = g23.x, dB = g23.y, dC = g45.x, dO = g45.y, dZ = gr[3].x;
         gop += dO * G.o * (1.0 - G.o);
         // conic = cov^-1: dcov = -Q Gq Q with Gq = [[dA, dB/2], [dB/2, dC]]
         const double Q00 = L.conic[0], Q01 = L.conic[1], Q11 = L.conic[2];
@@ -396,7 +396,7 @@ int launch_preprocess(const gs_config& cfg, const gs_gaussians& g, const gs_view
 }
 
 int launch_preprocess_bwd(const gs_config& cfg, const gs_gaussians& g, const gs_view* views, int n_views,
-                          const gs_item* items, const float* g2d, const int32_t* radius, const gs_grads& out,
+                          const gs_item* items, const double* g2d, const int32_t* radius, const gs_grads& out,
                           hipStream_t s) {
   const int64_t blocks = ceil_div(g.n, 256);
   if (blocks == 0) return GS_OK;

@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(gs_config cfg, const float* 
                                                     const gs_item* __restrict__ items, int n_items,
                                                     const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges,
                                                     const float* __restrict__ Tfin, const uint32_t* __restrict__ ncin,
-                                                    const float* __restrict__ gcolor, float* __restrict__ g2d,
+                                                    const float* __restrict__ gcolor, double* __restrict__ g2d,
                                                     float* __restrict__ grgb, float* __restrict__ gsem) {
   using S = Shape<NS>;
   constexpr int K = S::K, STRIDE = S::STRIDE, BATCH = S::BWD_BATCH, NV = S::NV, NVP = S::NVP;
@@ -231,9 +231,9 @@ __global__ __launch_bounds__(256) void k_render_bwd(gs_config cfg, const float* 
       if (s == 0.0f) continue;
       const uint32_t g = vals[c.start + lo + q];
       const int64_t e = (int64_t)c.item * n + g;
-      if (v < 6) atomicAdd(&g2d[8 * e + v], s);
+      if (v < 6) atomicAdd(&g2d[kGradRec * e + v], (double)s);
       else if (v < 9) atomicAdd(&grgb[3 * ((int64_t)g + foff) + (v - 6)], s);
-      else if (v == 9) atomicAdd(&g2d[8 * e + 6], s);
+      else if (v == 9) atomicAdd(&g2d[kGradRec * e + 6], (double)s);
       else if (v - 10 < n_sem) atomicAdd(&gsem[(int64_t)n_sem * ((int64_t)g + foff) + (v - 10)], s);
     }
   }
@@ -250,7 +250,7 @@ int launch_fwd_t(const gs_config& cfg, const gs_gaussians& g, const gs_projected
 template <int NS>
 int launch_bwd_t(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items, int n_items,
                  int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& fwd,
-                 const gs_images& gin, float* g2d, const gs_grads& gr, hipStream_t s) {
+                 const gs_images& gin, double* g2d, const gs_grads& gr, hipStream_t s) {
   hipLaunchKernelGGL(k_render_bwd<NS>, dim3(n_tiles), dim3(256), 0, s, cfg, g.rgb, g.sem, g.emb, cfg.n_sem, p.rec, p.depth,
                      g.n, items, n_items, vals, ranges, fwd.T, fwd.n_contrib, gin.color, g2d, gr.rgb, gr.sem);
   return launch_status();
@@ -274,7 +274,7 @@ int launch_render_fwd_valu(const gs_config& cfg, const gs_gaussians& g, const gs
 
 int launch_render_bwd_valu(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items,
                       int n_items, int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& fwd,
-                      const gs_images& gin, float* g2d, const gs_grads& gr, hipStream_t s) {
+                      const gs_images& gin, double* g2d, const gs_grads& gr, hipStream_t s) {
   if (n_tiles == 0) return GS_OK;
   const int ns = cfg.n_sem;
   if (ns <= 8) return launch_bwd_t<8>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, s);

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_mfma(gs_config cfg, const fl
                                                          const uint32_t* __restrict__ vals,
                                                          const uint32_t* __restrict__ ranges,
                                                          const float* __restrict__ Tfin, const uint32_t* __restrict__ ncin,
-                                                         const float* __restrict__ gcolor, float* __restrict__ g2d,
+                                                         const float* __restrict__ gcolor, double* __restrict__ g2d,
                                                          float* __restrict__ grgb, float* __restrict__ gsem) {
   using S = MShape<NS>;
   constexpr int K = S::K, KB = S::KB, KP = S::KP, FST = S::FST;
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_mfma(gs_config cfg, const fl
       if (val == 0.0f || k >= Kr) continue;
       const uint32_t g = vals[c.start + lo + q];
       if (k < 3) atomicAdd(&grgb[3 * ((int64_t)g + foff) + k], val);
-      else if (k == 3) atomicAdd(&g2d[8 * ((int64_t)c.item * n + g) + 6], val);
+      else if (k == 3) atomicAdd(&g2d[kGradRec * ((int64_t)c.item * n + g) + 6], (double)val);
       else atomicAdd(&gsem[(int64_t)n_sem * ((int64_t)g + foff) + (k - 4)], val);
     }
     for (int idx = tid; idx < cnt * 6; idx += 256) {
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_mfma(gs_config cfg, const fl
       for (int r = 0; r < 16; ++r) sum += src[r];
       if (sum != 0.0f) {
         const uint32_t g = vals[c.start + lo + q];
-        atomicAdd(&g2d[8 * ((int64_t)c.item * n + g) + comp], sum);
+        atomicAdd(&g2d[kGradRec * ((int64_t)c.item * n + g) + comp], (double)sum);
       }
     }
   }
@@ -355,7 +355,7 @@ int launch_fwd_m(const gs_config& cfg, const gs_gaussians& g, const gs_projected
 template <int NS>
 int launch_bwd_m(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items, int n_items,
                  int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& fwd,
-                 const gs_images& gin, float* g2d, const gs_grads& gr, hipStream_t s) {
+                 const gs_images& gin, double* g2d, const gs_grads& gr, hipStream_t s) {
   hipLaunchKernelGGL(k_render_bwd_mfma<NS>, dim3(n_tiles), dim3(256), 0, s, cfg, g.rgb, g.sem, g.emb, cfg.n_sem, p.rec,
                      p.depth, g.n, items, n_items, vals, ranges, fwd.T, fwd.n_contrib, gin.color, g2d, gr.rgb, gr.sem);
   return launch_status();
@@ -377,7 +377,7 @@ int launch_render_fwd_mfma(const gs_config& cfg, const gs_gaussians& g, const gs
 
 int launch_render_bwd_mfma(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items,
                            int n_items, int n_tiles, const uint32_t* vals, const uint32_t* ranges,
-                           const gs_images& fwd, const gs_images& gin, float* g2d, const gs_grads& gr, hipStream_t s) {
+                           const gs_images& fwd, const gs_images& gin, double* g2d, const gs_grads& gr, hipStream_t s) {
   const int ns = cfg.n_sem;
   if (ns <= 8) return launch_bwd_m<8>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, s);
   if (ns <= 20) return launch_bwd_m<20>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, s);

@@ -537,6 +537,48 @@ __device__ __forceinline__ LRec local_rec(const float4 a, const float4 b, float 
   return r;
 }
 
+// Work items of a block whose waves do not meet at a barrier. Each wave takes the block's items in
+// the same order; the first to need item j takes it from the launch's counter for all four, once
+// they all hold item j - 1: a wave runs at most one item ahead of the slowest. Further ahead, the
+// waves no longer find in the L1 cache what the others gathered from the same list.
+struct BlockItems {
+  uint32_t item, tag;           // the newest item and its number in the block's order + 1
+  uint32_t claimed, taken[4];   // items claimed so far; items each wave has taken
+};
+__device__ __forceinline__ void items_init(BlockItems& b) {
+  if (threadIdx.x < sizeof(b) / 4) reinterpret_cast<uint32_t*>(&b)[threadIdx.x] = 0u;
+  __syncthreads();
+}
+__device__ __forceinline__ uint32_t lds_load(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_store(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// Item j of the block, in every lane of wave `wave`. The waits end: one is for waves that have not
+// taken item j - 1 (they hold an earlier one and go on to take the next), the other for the wave
+// that is fetching item j. A fetched item stays until this wave has taken it too. After the last
+// item every wave sees the same first number past the work and stops there.
+__device__ __forceinline__ uint32_t next_item(BlockItems& b, uint32_t* counter, int wave, uint32_t j) {
+  uint32_t wi = 0;
+  if ((threadIdx.x & 63) == 0) {
+    uint32_t want = j;
+    if (__hip_atomic_compare_exchange_strong(&b.claimed, &want, j + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP)) {
+      for (int w = 0; w < 4; ++w)
+        while (lds_load(&b.taken[w]) < j) __builtin_amdgcn_s_sleep(1);
+      wi = atomicAdd(counter, 1u);
+      lds_store(&b.item, wi);
+      lds_store(&b.tag, j + 1u);
+    } else {
+      while (lds_load(&b.tag) != j + 1u) __builtin_amdgcn_s_sleep(1);
+      wi = lds_load(&b.item);
+    }
+    lds_store(&b.taken[wave], j + 1u);
+  }
+  return __builtin_amdgcn_readfirstlane(wi);
+}
+
 // Hides a value's origin: what is computed from the copy is not hoisted out of the loop over
 // work items, where the many channel masks and addresses of an item's end would hold registers.
 __device__ __forceinline__ int opaque(int x) { asm volatile("" : "+s"(x)); return x; }
@@ -1129,10 +1171,11 @@ __global__ __launch_bounds__(256, 2) void k_seg_summary(gs_config cfg, const flo
 }
 
 // ------------------------------------------------------------------------- backward, main pass
-// Where the reverse pass's per-Gaussian sums go from LDS: the n_sem semantic channels, then
-// rgb, then the record's seven components (mean2d 2, conic 3, opacity, depth).
+// Where the reverse pass's per-Gaussian sums go from LDS: the n_sem semantic channels and rgb in
+// single precision, the record's seven components (kGradRec) in double precision.
 struct GradDst {
-  float *grgb, *gsem, *g2d;
+  float *grgb, *gsem;
+  double* g2d;
 };
 
 // The reverse pass over one work item (a whole tile list, or one segment of it), back to front.
@@ -1148,13 +1191,15 @@ struct GradDst {
 //   is waited for until a whole group's work has passed.
 // Memory takes 21 G atomic requests a second of up to 64 bytes each, however few bytes they carry
 // (measured), so a group's sums go out with the lanes of a Gaussian side by side: a record's seven
-// components (32 bytes) or an embedding's row (64) are one request each.
+// components or an embedding's row (64 bytes) are one request each.
 // It replaces a block that staged 32 entries at a time for its four waves and met at two barriers a
-// batch: 16 full-HD pyramids, embedding 70.3 -> 29.7 ms; eight 636x476 pyramids, 20 classes
-// 6.44 -> 3.14 ms; a 1200x680 pyramid, 52 classes 1.04 -> 0.52 ms; a 320x240 pyramid 0.28 -> 0.14 ms.
+// batch: 16 full-HD pyramids, embedding 70.3 -> 27.1 ms; eight 636x476 pyramids, 20 classes
+// 6.44 -> 2.78 ms; a 1200x680 pyramid, 52 classes 1.04 -> 0.48 ms; a 320x240 pyramid 0.28 -> 0.14 ms
+// (29.7, 3.14, 0.52 and 0.14 ms with a barrier per work item, sums read one by one as they go out
+// and records in single precision; 26.2, 2.73, 0.47, 0.13 with the latter alone).
 // Windows of 64 entries shared by the four waves, their sums meeting in LDS (half the atomic
 // requests), took 45.9 ms and 0.88 ms on the first and third: 28 % of the cycles were waves waiting
-// for the one with most entries in the window.
+// for the one with most entries in the window. Vector issue is 60-65 % busy now.
 constexpr int kGrp = 16, kRing = 128;   // ring: a part group (15), two groups in work, 64 new entries
 
 template <int NS>
@@ -1180,7 +1225,7 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
   constexpr bool kGF3 = B::kGF3;
   constexpr int GG = NS > 28 ? 2 : 4;         // Gaussians per geometric-term reduction (register budget)
   __shared__ __align__(16) float s_mem[4][B::kWave];
-  __shared__ uint32_t s_wi;
+  __shared__ BlockItems s_items;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l16 = lane & 15, g4 = lane >> 4;
   const int Kr = 4 + src.n_sem;
@@ -1194,11 +1239,9 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
   float* const F = W + B::kW;
   float* const A = F + B::kF;
   const Region rg = wave_region(tws, wave, lane);
-  for (;;) {
-    if (tid == 0) s_wi = atomicAdd(&ctl[2], 1u);
-    lds_barrier();
-    const uint32_t wi = __builtin_amdgcn_readfirstlane(s_wi);
-    lds_barrier();
+  items_init(s_items);
+  for (uint32_t round = 0;; ++round) {
+    const uint32_t wi = next_item(s_items, &ctl[2], wave, round);
     if (wi >= n_work) break;
     const uint2 wk = work[wi];
     const int tile = (int)__builtin_amdgcn_readfirstlane(wk.x);
@@ -1406,27 +1449,40 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
       const int n_sem = opaque(src.n_sem), total = n_sem + 10;
       const int ls = total <= 16 ? 4 : total <= 32 ? 5 : 6, L = 1 << ls;
       for (int o = lane & (L - 1); o < total; o += L) {
-        float* base;
+        char* base;
         int stride, col;
-        float scale = 1.0f;
+        const int k = o - n_sem - 3;   // the record's component, if any
         if (o < n_sem) {
-          base = out.gsem + n_sem * foff + o;
-          stride = n_sem;
+          base = (char*)(out.gsem + n_sem * foff + o);
+          stride = 4 * n_sem;
           col = 4 + o;
-        } else if (o < n_sem + 3) {
-          base = out.grgb + 3 * foff + (o - n_sem);
-          stride = 3;
+        } else if (k < 0) {
+          base = (char*)(out.grgb + 3 * foff + (o - n_sem));
+          stride = 12;
           col = o - n_sem;
         } else {
-          const int k = o - n_sem - 3;
-          base = out.g2d + 8 * e0 + k;
-          stride = 8;
+          base = (char*)(out.g2d + kGradRec * e0 + k);
+          stride = 8 * kGradRec;
           col = k < 6 ? KP + k : 3;
-          if (k < 6) scale = kGeoScale[k];
         }
-        for (int e = lane >> ls; e < cnt; e += 64 >> ls) {
-          const float val = A[e * AROW + col];
-          if (val != 0.0f) atomicAdd(base + (int64_t)stride * __float_as_uint(R[8 * e + 7]), val * scale);
+        const float scale = k >= 0 && k < 6 ? kGeoScale[k] : 1.0f;
+        // eight Gaussians' values are read before the first goes out
+        for (int e1 = lane >> ls; e1 < cnt; e1 += 512 >> ls) {
+          float val[8];
+          uint32_t g[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const int e = min(e1 + i * (64 >> ls), kGrp - 1);
+            val[i] = A[e * AROW + col];
+            g[i] = __float_as_uint(R[8 * e + 7]);
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (e1 + i * (64 >> ls) < cnt && val[i] != 0.0f) {
+              char* p = base + (int64_t)stride * g[i];
+              if (k < 0) atomicAdd((float*)p, val[i]);
+              else atomicAdd((double*)p, (double)(val[i] * scale));
+            }
         }
       }
     };
@@ -1526,9 +1582,9 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
             const float dalpha = Tq * gf - acc * rom;
             acc = act ? __builtin_fmaf(gf, wq, acc) : acc;
             T = Tq;
-            const bool unclamped = act & (araw < amax);
-            const float dpow = unclamped ? dalpha * araw : 0.0f;
-            const float dop = unclamped ? dalpha * G : 0.0f;
+            const float dfree = (act & (araw < amax)) ? dalpha : 0.0f;   // no gradient through the clamp
+            const float dpow = dfree * araw;
+            const float dop = dfree * G;
             W[qq * kPs + lane] = wq;
             // d power / d (mean2d, A, B, C) up to the per-component factors of kGeoScale
             const float pdx = dpow * dx, pdy = dpow * dy;
@@ -1733,7 +1789,7 @@ int launch_fwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
 template <int NS, bool EMB>
 int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items, int n_items,
                  int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& fwd,
-                 const gs_images& gin, float* g2d, const gs_grads& gr, void* seg_ws, int64_t cap, hipStream_t s) {
+                 const gs_images& gin, double* g2d, const gs_grads& gr, void* seg_ws, int64_t cap, hipStream_t s) {
   SegWs w;
   seg_layout(n_tiles, cap, seg_len(cfg), (char*)seg_ws, &w);
   // with the forward's saved state the segments start from it: no summary pass
@@ -1791,7 +1847,7 @@ int launch_render_fwd_split(const gs_config& cfg, const gs_gaussians& g, const g
 
 int launch_render_bwd_split(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items,
                             int n_items, int n_tiles, const uint32_t* vals, const uint32_t* ranges,
-                            const gs_images& fwd, const gs_images& gin, float* g2d, const gs_grads& gr, void* seg_ws,
+                            const gs_images& fwd, const gs_images& gin, double* g2d, const gs_grads& gr, void* seg_ws,
                             int64_t cap, hipStream_t s) {
   const int ns = cfg.n_sem;
   if (cap < 0) return GS_ERR_WORKSPACE;
