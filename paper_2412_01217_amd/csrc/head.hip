@@ -1,7 +1,7 @@
 // Learned semantic head: logits = W2 relu(W1 E + b1) + b2 per pixel, where E is the
 // composited 16-wide embedding (eq. 9 with an embedding in place of class logits),
 // W1 [64][16] and W2 [C][64] bfloat16, biases float32. Forward and backward run on
-// matrix cores as v_mfma_f32_32x32x8bf16_1k. Single-precision activations enter the
+// matrix cores as v_mfma_f32_32x32x16_bf16, two k-steps of 32x32x8 at a time (mfma2). Single-precision activations enter the
 // bfloat16 products as a hi + lo pair (x = bf16(x) + bf16(x - bf16(x))), which keeps
 // the decode within ~2^-16 of single precision; products of two single-precision
 // factors (weight gradients) use hi*hi + hi*lo + lo*hi.
@@ -39,18 +39,21 @@ __device__ __forceinline__ uint16_t bf16_rne(float x) {
 }
 __device__ __forceinline__ float bf16_f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// Splits four floats into hi and lo bfloat16 operands (hardware round-to-nearest-even).
+// Splits four floats into hi and lo bfloat16 operands (hardware round-to-nearest-even), two
+// values per conversion.
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split4(const float* x, v4s& hi, v4s& lo) {
+  uint32_t h[2], l[2];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const __bf16 h = (__bf16)x[j];
-    const __bf16 l = (__bf16)(x[j] - (float)h);
-    hi[j] = __builtin_bit_cast(short, h);
-    lo[j] = __builtin_bit_cast(short, l);
+  for (int k = 0; k < 2; ++k) {
+    h[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){x[2 * k], x[2 * k + 1]}, bf2));
+    const float h0 = __uint_as_float(h[k] << 16), h1 = __uint_as_float(h[k] & 0xffff0000u);
+    l[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){x[2 * k] - h0, x[2 * k + 1] - h1}, bf2));
   }
+  hi = __builtin_bit_cast(v4s, make_uint2(h[0], h[1]));
+  lo = __builtin_bit_cast(v4s, make_uint2(l[0], l[1]));
 }
-
-__device__ __forceinline__ v16f mfma(v4s a, v4s b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0); }
 
 // Two consecutive k-steps of 32x32x8 as one v_mfma_f32_32x32x16_bf16 (twice the work per
 // instruction on gfx950): lane (l % 32, h = l / 32) supplies k = 8 h + 0..7 of the 16; given
@@ -72,120 +75,6 @@ __device__ __forceinline__ v16f zero16() {
 #pragma unroll
   for (int r = 0; r < 16; ++r) z[r] = 0.0f;
   return z;
-}
-
-struct PixelRef {     // where one global pixel's channel c lives in a planar image
-  int64_t base;       // pixel_base * channels + local index
-  int64_t HW;
-  bool live;
-};
-
-__device__ __forceinline__ PixelRef pixel_ref(const gs_item* items, int n_items, int64_t P, int64_t pix, int channels) {
-  PixelRef r;
-  r.live = pix < P;
-  if (!r.live) { r.base = 0; r.HW = 0; return r; }
-  const gs_item it = items[item_of_pixel(items, n_items, pix)];
-  r.HW = (int64_t)it.W * it.H;
-  r.base = it.pixel_base * channels + (pix - it.pixel_base);
-  return r;
-}
-
-// Layer 1 for the wave's 64 pixels: H^T[hb][pb] = W1 E^T (pre-activation, bias added).
-__device__ __forceinline__ void layer1(const gs_item* items, int n_items, int64_t P, int64_t wave_pix, int K,
-                                       const float* __restrict__ color, const uint16_t* __restrict__ W1,
-                                       const float* __restrict__ b1, v16f (&H)[2][2]) {
-  const int lane = threadIdx.x & 63;
-  // A = W1 (i = hidden l%32 + 32 hb, k = d 8 ks + 4 (l/32) + 0..3): exact bfloat16
-  v4s a[2][2];
-#pragma unroll
-  for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        a[hb][ks][j] = (short)W1[((lane & 31) + 32 * hb) * kDin + 8 * ks + 4 * (lane >> 5) + j];
-#pragma unroll
-  for (int pb = 0; pb < 2; ++pb) {
-    const PixelRef pr = pixel_ref(items, n_items, P, wave_pix + (lane & 31) + 32 * pb, K);
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      float e[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) e[j] = pr.live ? color[pr.base + (4 + 8 * ks + 4 * (lane >> 5) + j) * pr.HW] : 0.0f;
-      v4s hi, lo;
-      split4(e, hi, lo);
-#pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
-        if (ks == 0) H[hb][pb] = zero16();
-        H[hb][pb] = mfma(a[hb][ks], hi, H[hb][pb]);
-        H[hb][pb] = mfma(a[hb][ks], lo, H[hb][pb]);
-      }
-    }
-  }
-#pragma unroll
-  for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float bias = b1[drow(r, lane) + 32 * hb];
-      H[hb][0][r] += bias;
-      H[hb][1][r] += bias;
-    }
-}
-
-// B operand (k = hidden 8 ks + 4 (l/32) + 0..3, j = pixel) of k-step ks from H^T registers.
-__device__ __forceinline__ void hidden_operand(const v16f (&X)[2][2], int pb, int ks, v4s& hi, v4s& lo) {
-  const int hb = ks >> 2, g = ks & 3;
-  float x[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) x[j] = X[hb][pb][4 * g + j];
-  split4(x, hi, lo);
-}
-
-__global__ __launch_bounds__(256) void k_head_fwd(const gs_item* __restrict__ items, int n_items, int64_t P, int K,
-                                                  int C, const float* __restrict__ color,
-                                                  const uint16_t* __restrict__ W1, const float* __restrict__ b1,
-                                                  const uint16_t* __restrict__ W2, const float* __restrict__ b2,
-                                                  float* __restrict__ logits) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave_pix = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
-  if (wave_pix >= P) return;
-  v16f H[2][2];
-  layer1(items, n_items, P, wave_pix, K, color, W1, b1, H);
-#pragma unroll
-  for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-    for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) H[hb][pb][r] = fmaxf(H[hb][pb][r], 0.0f);
-  // logits^T[cb][pb] = W2 h^T: A = W2 (i = class l%32 + 32 cb, k = hidden 8 ks + 4 (l/32) + 0..3)
-#pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
-    const int cls = (lane & 31) + 32 * cb;
-    v16f L[2] = {zero16(), zero16()};
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      v4s a;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a[j] = cls < C ? (short)W2[(int64_t)cls * kHid + 8 * ks + 4 * (lane >> 5) + j] : (short)0;
-#pragma unroll
-      for (int pb = 0; pb < 2; ++pb) {
-        v4s hi, lo;
-        hidden_operand(H, pb, ks, hi, lo);
-        L[pb] = mfma(a, hi, L[pb]);
-        L[pb] = mfma(a, lo, L[pb]);
-      }
-    }
-#pragma unroll
-    for (int pb = 0; pb < 2; ++pb) {
-      const PixelRef pr = pixel_ref(items, n_items, P, wave_pix + (lane & 31) + 32 * pb, C);
-      if (!pr.live) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = drow(r, lane) + 32 * cb;
-        if (c < C) logits[pr.base + c * pr.HW] = L[pb][r] + b2[c];
-      }
-    }
-  }
 }
 
 // Walks the 64-pixel chunks of the concatenated items in increasing order. Chunks
@@ -625,6 +514,111 @@ __device__ __forceinline__ bool chunk_info(ConstItems items, int n_items, int64_
   return true;
 }
 
+// Decode of the rendered embeddings: logits W2 relu(W1 E + b1) + b2 per pixel. Persistent waves
+// walk 64-pixel chunks; W1 stays in registers, W2 in LDS, and the next chunk's 16 values per lane
+// are loaded before this one's are used. A half of a chunk's 32 pixels goes through
+// H^T = W1 E^T and logits^T = W2 h^T with the hidden layer in registers (see the top of the file),
+// split once for both class blocks. Bound by the logits' way to memory: at 52 classes 2.07 million
+// pixels read 133 MB and write 431 MB, 0.12 ms at copy rate; a wave per chunk that fetched the
+// weights value by value took 0.36 ms.
+__global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__ items, int n_items, int K, int C,
+                                                     const float* __restrict__ color,
+                                                     const uint16_t* __restrict__ W1, const float* __restrict__ b1,
+                                                     const uint16_t* __restrict__ W2, const float* __restrict__ b2,
+                                                     float* __restrict__ logits) {
+  __shared__ __align__(16) uint16_t w2r[kHid * kWtStride];   // W2 [class][kperm(hidden)], rows >= C zero
+  __shared__ float s_b1[kHid], s_b2[kHid];
+  const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int i = threadIdx.x; i < kHid * kHid; i += 256) {
+    const int c = i / kHid, h = i % kHid;
+    w2r[c * kWtStride + kperm(h)] = c < C ? W2[c * kHid + h] : (uint16_t)0;
+  }
+  if (threadIdx.x < kHid) {
+    s_b1[threadIdx.x] = b1[threadIdx.x];
+    s_b2[threadIdx.x] = (int)threadIdx.x < C ? b2[threadIdx.x] : 0.0f;
+  }
+  // A = W1 (i = hidden l32 + 32 hb, k = d 8 ks + 4 half + j)
+  v4s w1a[2][2];
+#pragma unroll
+  for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w1a[hb][ks][j] = (short)W1[(l32 + 32 * hb) * kDin + 8 * ks + 4 * half + j];
+  __syncthreads();
+  ConstItems citems = (ConstItems)items;
+  ChunkCursor cur;
+  cur.item = 0;
+  cur.first = 0;
+  cur.end = ((int64_t)citems[0].W * citems[0].H + 63) / 64;
+  const int64_t stride = (int64_t)gridDim.x * 4;
+  ChunkInfo ci, cn;
+  float e[2][2][4];   // embedding value 8 ks + 4 half + j of pixel 32 pb + l32
+  auto load = [&](const ChunkInfo& c) {
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+      const float* b = color + c.pixel_base * K + c.local0 + min(l32 + 32 * pb, c.nlive - 1) + (4 + 4 * half) * c.HW;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) e[pb][ks][j] = b[(8 * ks + j) * c.HW];
+    }
+  };
+  if (!chunk_info(citems, n_items, (int64_t)blockIdx.x * 4 + wave, cur, ci)) return;
+  load(ci);
+  for (;;) {
+    v4s ehi[2][2], elo[2][2];
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) split4(e[pb][ks], ehi[pb][ks], elo[pb][ks]);
+    const bool more = chunk_info(citems, n_items, ci.chunk + stride, cur, cn);
+    if (more) load(cn);
+    float* out = logits + ci.pixel_base * C + ci.local0 + l32;
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+      v16f H[2];
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        H[hb] = mfma2(w1a[hb][0], w1a[hb][1], ehi[pb][0], ehi[pb][1], zero16());
+        H[hb] = mfma2(w1a[hb][0], w1a[hb][1], elo[pb][0], elo[pb][1], H[hb]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) H[hb][r] = fmaxf(H[hb][r] + s_b1[drow(r, lane) + 32 * hb], 0.0f);
+      }
+      v16f Lg[2] = {zero16(), zero16()};
+#pragma unroll
+      for (int s2 = 0; s2 < 4; ++s2) {
+        v4s hi[2], lo[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int ks = 2 * s2 + u;
+          float x[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[j] = H[ks >> 2][4 * (ks & 3) + j];
+          split4(x, hi[u], lo[u]);
+        }
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          const v8s a = *reinterpret_cast<const v8s*>(w2r + (l32 + 32 * cb) * kWtStride + 16 * s2 + 8 * half);
+          Lg[cb] = mfma2(a, hi[0], hi[1], Lg[cb]);
+          Lg[cb] = mfma2(a, lo[0], lo[1], Lg[cb]);
+        }
+      }
+      if (l32 + 32 * pb < ci.nlive)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int c = drow(r, lane) + 32 * cb;
+            if (c < C) __builtin_nontemporal_store(Lg[cb][r] + s_b2[c], out + 32 * pb + c * ci.HW);
+          }
+    }
+    if (!more) break;
+    ci = cn;
+  }
+}
+
 constexpr int kStageLoads = kDin + 4 + 3 + 1 + 1;   // direct-to-LDS loads per staged chunk
 
 // Waits until at most kStageLoads vector memory operations are in flight: those are the
@@ -933,8 +927,10 @@ int head_shape_ok(const gs_head& h) { return h.d_in == kDin && h.d_hidden == kHi
 int launch_head_fwd(const gs_item* items, int n_items, int64_t P, int K, const gs_head& h, const float* color,
                     float* logits, hipStream_t s) {
   if (P == 0) return GS_OK;
-  const int64_t blocks = ceil_div(P, 256);
-  hipLaunchKernelGGL(k_head_fwd, dim3((unsigned)blocks), dim3(256), 0, s, items, n_items, P, K, h.n_classes, color, h.W1,
+  // at most one 64-pixel chunk per item is partial, so P / 64 + n_items bounds the chunk count
+  const int resident = resident_blocks(k_head_fwd, 256, 512);
+  const int64_t blocks = std::min<int64_t>(resident, ceil_div(ceil_div(P, 64) + n_items, 4));
+  hipLaunchKernelGGL(k_head_fwd, dim3((unsigned)blocks), dim3(256), 0, s, items, n_items, K, h.n_classes, color, h.W1,
                      h.b1, h.W2, h.b2, logits);
   return launch_status();
 }
