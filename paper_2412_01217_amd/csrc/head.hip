@@ -118,12 +118,15 @@ constexpr int kGst = 65;   // LDS row stride of the staged logit gradients
 // at 16 s + 8 h: one 16-byte LDS read.
 __host__ __device__ constexpr int kperm(int k) { return (k & ~12) | ((k & 4) << 1) | ((k & 8) >> 1); }
 
-struct alignas(16) HeadLds {
-  float buf[4 * kHid * kGst];        // per wave [class][pixel]; the block's partial at the end
+template <int ROW>
+struct alignas(16) HeadLdsOf {
+  static constexpr int kRow = ROW;
+  float buf[4 * kHid * ROW];         // per wave [class][pixel]; the block's partial at the end
   uint16_t w2t[kHid * kWtStride];    // W2^T [hidden][kperm(class)], classes >= C zero
   uint16_t w1t[kDin * kWtStride];    // W1^T [d][kperm(hidden)]
   float b1[kHid];
 };
+using HeadLds = HeadLdsOf<kGst>;
 
 // Per-lane accumulators of the weight gradients over a block's chunks.
 struct HeadAcc {
@@ -131,7 +134,8 @@ struct HeadAcc {
   float B2[2];            // class l32 + 32 cb, this lane's pixels
 };
 
-__device__ __forceinline__ void head_setup(HeadLds& L, int C, const uint16_t* __restrict__ W1,
+template <class LDS>
+__device__ __forceinline__ void head_setup(LDS& L, int C, const uint16_t* __restrict__ W1,
                                            const float* __restrict__ b1, const uint16_t* __restrict__ W2,
                                            HeadAcc& acc, v4s (&w1a)[2][2], float (&b1l)[2]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
@@ -144,8 +148,8 @@ __device__ __forceinline__ void head_setup(HeadLds& L, int C, const uint16_t* __
     L.w1t[d * kWtStride + kperm(h)] = W1[h * kDin + d];
   }
   if (threadIdx.x < kHid) L.b1[threadIdx.x] = b1[threadIdx.x];
-  float* sg = L.buf + wave * kHid * kGst;
-  for (int i = C * kGst + lane; i < kHid * kGst; i += 64) sg[i] = 0.0f;   // rows of absent classes
+  float* sg = L.buf + wave * kHid * LDS::kRow;
+  for (int i = C * LDS::kRow + lane; i < kHid * LDS::kRow; i += 64) sg[i] = 0.0f;   // rows of absent classes
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -166,22 +170,17 @@ __device__ __forceinline__ void head_setup(HeadLds& L, int C, const uint16_t* __
 }
 
 // Steps (1)-(5) for one 64-pixel chunk whose logit gradients are staged in sg [class][pixel].
-// Eb: pixel 0 of plane 0 of the chunk's embedding, plane d at Eb + d es (es = HW in global
-// memory; the row stride when staged in LDS, whose 64 entries per row are all readable);
-// dEb: the chunk's gradient planes (plane d at dEb + d HW). on_in (LDS_E, the fused loss):
-// the ReLU masks its decode formed, [half][hb] bit r for hidden unit drow(r) + 32 hb, in
-// place of step (1)'s recomputation.
-template <bool ADD, bool LDS_E>
-__device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const float* sg, const float* Eb, int64_t es,
-                                                    float* dEb, int64_t HW, int nlive, const v4s (&w1a)[2][2],
-                                                    const float (&b1l)[2], HeadAcc& acc,
-                                                    const uint32_t (*on_in)[2] = nullptr) {
+// Eb: pixel 0 of plane 0 of the chunk's embedding, plane d at Eb + d HW; dEb: the chunk's
+// gradient planes, which dE is added to.
+__device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const float* sg, const float* Eb, float* dEb,
+                                                    int64_t HW, int nlive, const v4s (&w1a)[2][2],
+                                                    const float (&b1l)[2], HeadAcc& acc) {
   const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
 #pragma unroll 1
   for (int pb = 0; pb < 2; ++pb) {
     const int q = l32 + 32 * pb;
     const bool qlive = q < nlive;
-    const float* Eq = Eb + 4 * half * es + min(q, nlive - 1);   // plane 8 ks + 4 half + j at Eq + (8 ks + j) es
+    const float* Eq = Eb + 4 * half * HW + min(q, nlive - 1);   // plane 8 ks + 4 half + j at Eq + (8 ks + j) HW
     const float* Gq = sg + 4 * half * kGst + q;                 // class 8 ks + 4 half + j at Gq + (8 ks + j) kGst
     // (1) E with d in registers, pixels across lanes; the sign of the hidden pre-activations
     v4s ehi[2], elo[2];
@@ -190,16 +189,12 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
       float e[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float v = Eq[(8 * ks + j) * es];
+        const float v = Eq[(8 * ks + j) * HW];
         e[j] = qlive ? v : 0.0f;
       }
       split4(e, ehi[ks], elo[ks]);
     }
     uint32_t on[2];   // bit r: hidden unit drow(r) + 32 hb is active at this pixel
-    if constexpr (LDS_E) {
-      on[0] = pb ? on_in[1][0] : on_in[0][0];
-      on[1] = pb ? on_in[1][1] : on_in[0][1];
-    } else {
 #pragma unroll
       for (int hb = 0; hb < 2; ++hb) {
         v16f h;
@@ -212,7 +207,6 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
         for (int r = 0; r < 16; ++r) bits |= (h[r] > 0.0f ? 1u : 0u) << r;
         on[hb] = bits;
       }
-    }
 
     // (2) dH^T = W2^T dlogits^T: A = W2^T (i = hidden l32 + 32 hb, k = class 8 ks + 4 half + j)
     v16f dHT[2] = {zero16(), zero16()};
@@ -259,13 +253,12 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
         dE = mfma2(a, hi[0], hi[1], dE);
         dE = mfma2(a, lo[0], lo[1], dE);
       }
-      // rows 0..15 = d: added to what the caller's gradient holds there, or stored
+      // rows 0..15 = d: added to what the caller's gradient holds there
       if (qlive)
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
           float* dst = dEb + (int64_t)drow(r, lane) * HW + q;
-          if constexpr (ADD) *dst += dE[r];
-          else *dst = dE[r];
+          *dst += dE[r];
         }
     }
 
@@ -345,7 +338,7 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
 #pragma unroll
       for (int r = 0; r < 16; ++r) dH[hb][r] = ((onH[hb] >> r) & 1u) ? dH[hb][r] : 0.0f;
     // (5b) dW1[h][d] += sum_p dH[p][h] [E, 1][p][d]: A = dH (i = hidden l32 + 32 hb, k = p), B = [E, 1] (j = d l32)
-    const float* Ed = Eb + (int64_t)min(l32, kDin - 1) * es;
+    const float* Ed = Eb + (int64_t)min(l32, kDin - 1) * HW;
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2) {
       v4s bhi[2], blo[2];
@@ -355,7 +348,7 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
         float e[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float v = Ed[LDS_E ? p0 + j : min(p0 + j, nlive - 1)];
+          const float v = Ed[min(p0 + j, nlive - 1)];
           e[j] = p0 + j >= nlive ? 0.0f : (l32 < kDin ? v : (l32 == kDin ? 1.0f : 0.0f));
         }
         split4(e, bhi[u], blo[u]);
@@ -379,7 +372,8 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
 }
 
 // Sums the block's four waves' accumulators in LDS and writes the block's partial.
-__device__ __forceinline__ void head_write_partial(HeadLds& L, const HeadAcc& acc, float* __restrict__ partial) {
+template <class LDS>
+__device__ __forceinline__ void head_write_partial(LDS& L, const HeadAcc& acc, float* __restrict__ partial) {
   const int lane = threadIdx.x & 63, l32 = lane & 31;
   float* s_acc = L.buf;
   __syncthreads();
@@ -449,8 +443,8 @@ __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__
       }
     }
     wave_fence();
-    head_chunk_backward<true, false>(L, sg, color + it.pixel_base * K + 4 * HW + local0, HW,
-                                     gcolor + it.pixel_base * K + 4 * HW + local0, HW, nlive, w1a, b1l, acc);
+    head_chunk_backward(L, sg, color + it.pixel_base * K + 4 * HW + local0, gcolor + it.pixel_base * K + 4 * HW + local0,
+                        HW, nlive, w1a, b1l, acc);
     // every lane is past this chunk's reads of the staged rows before the next chunk writes them
     wave_fence();
   }
@@ -461,8 +455,7 @@ __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__
 // cross-entropy on the head's logits): per 64-pixel chunk of one item, the L1 colour and
 // depth terms (lane = pixel, as in the plain loss), the decode logits = W2 relu(W1 E + b1)
 // + b2 on the matrix cores, the cross-entropy against the label and its logit gradient
-// w2 (softmax - onehot) / HW, staged in LDS, then the head's backward (steps (1)-(5) above)
-// storing dL/dE in the colour-gradient planes 4..19 and accumulating the weight gradients.
+// w2 (softmax - onehot) / HW, and the head's backward (steps (2)-(5) above) storing dL/dE in the colour-gradient planes 4..19 and accumulating the weight gradients.
 // No logits touch global memory. Loss partial sums go to the same per-item slots as the
 // plain loss's.
 //
@@ -471,7 +464,9 @@ __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__
 // on one chunk, direct global-to-LDS loads fill the other of its two staging buffers with
 // its next chunk. The buffers are two separate LDS arrays and the loop handles two chunks
 // per iteration, one from each, so that the compiler's wait for a buffer's loads never
-// waits for the other's.
+// waits for the other's. Vector issue is 57 % busy, its waits 23 %: four full-HD pyramids with 52
+// classes 2.80 ms with the logit gradients staged for both halves and read back (and split) as three
+// operands, and the ReLU masks carried as bits; 1.95 ms with all that in registers.
 constexpr int kEst = 68;   // row stride (floats) of a staged embedding plane
 
 struct ChunkStage {        // one wave's staged chunk: 64 pixels of every input plane
@@ -653,170 +648,287 @@ __device__ __forceinline__ void stage_chunk(ChunkStage& S, const ChunkInfo& ci, 
   __builtin_amdgcn_global_load_lds(tlabel + ci.pixel_base + p, &S.lab[0], 4, 0, 0);
 }
 
+// A wave's loss sums over its chunks of one item, per lane.
+struct LossSums {
+  float rgb, depth, ce, valid;
+  int item, slot;
+};
+// One atomic per wave and quantity.
+__device__ __forceinline__ void flush_loss(LossSums& a, int n_slots, float* loss_slots, float* count_slots) {
+  const float lr = wave_sum(a.rgb), ld = wave_sum(a.depth), c = wave_sum(a.ce), v = wave_sum(a.valid);
+  if ((threadIdx.x & 63) == 0) {
+    float* loss = loss_slots + a.slot;
+    atomicAdd(&loss[(3 * a.item + 0) * n_slots], lr);
+    if (v != 0.0f) {
+      atomicAdd(&loss[(3 * a.item + 1) * n_slots], ld);
+      atomicAdd(&count_slots[a.item * n_slots + a.slot], v);
+    }
+    atomicAdd(&loss[(3 * a.item + 2) * n_slots], c);
+  }
+  a.rgb = a.depth = a.ce = a.valid = 0.0f;
+}
+
 // Everything k_head_loss does for one staged chunk.
-__device__ __forceinline__ void head_loss_chunk(const HeadLds& L, const uint16_t* w2r, const ChunkStage& S,
+constexpr int kFst = 36;   // LDS row stride of a half's logit gradients (32 pixels)
+using FusedLds = HeadLdsOf<kFst>;
+__device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_t* w2r, const ChunkStage& S,
                                                 const ChunkInfo& ci, float* sg, int K, int C, float w0, float w2,
-                                                bool rgb_grad, int n_slots, const float (&b2r)[2][16],
+                                                bool rgb_grad, int n_slots, const float* b2s,
                                                 const v4s (&w1a)[2][2], const float (&b1l)[2], HeadAcc& acc,
-                                                float* __restrict__ loss_slots, float* __restrict__ count_slots,
-                                                float* __restrict__ gcolor) {
-  const int lane = threadIdx.x & 63, l32 = lane & 31;
+                                                LossSums& sums, float* __restrict__ loss_slots,
+                                                float* __restrict__ count_slots, float* __restrict__ gcolor) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
   const int64_t HW = ci.HW;
   const int nlive = ci.nlive;
   const float invp = 1.0f / (float)HW;
+  if (sums.item != ci.item) {   // (uniform)
+    if (sums.item >= 0) flush_loss(sums, n_slots, loss_slots, count_slots);
+    sums.item = ci.item;
+    sums.slot = (int)(ci.chunk % n_slots);
+  }
   wait_own_stage();
   // L1 colour and depth, lane = pixel
   const bool live = lane < nlive;
   const int64_t cbase = ci.pixel_base * K + ci.local0 + min(lane, nlive - 1);
-  float col[4], tr[3];
-#pragma unroll
-  for (int ch = 0; ch < 4; ++ch) col[ch] = S.col[ch][lane];
-#pragma unroll
-  for (int ch = 0; ch < 3; ++ch) tr[ch] = S.tr[ch][lane];
-  const float td = S.td[lane];
   const int y_own = S.lab[lane];
-  float lr = 0.0f, ld = 0.0f, nv = 0.0f, ls = 0.0f;
   {
-    const float inv3 = 1.0f / (3.0f * (float)HW);
-    float gc[3];
+    const float td = S.td[lane], inv3 = 1.0f / (3.0f * (float)HW);
+    float gc[3], lr = 0.0f;
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
-      const float d = col[ch] - tr[ch];
+      const float d = S.col[ch][lane] - S.tr[ch][lane];
       lr += fabsf(d) * inv3;
       gc[ch] = w0 * (float)((d > 0.0f) - (d < 0.0f)) * inv3;
     }
-    float gd = 0.0f;
-    if (td > 0.0f) {
-      const float d = col[3] - td;
-      ld = fabsf(d);
-      nv = 1.0f;
-      gd = (float)((d > 0.0f) - (d < 0.0f));
-    }
+    const float dd = S.col[3][lane] - td;
+    const bool valid = td > 0.0f;
+    const float gd = valid ? (float)((dd > 0.0f) - (dd < 0.0f)) : 0.0f;
     if (live) {
       if (rgb_grad)
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) __builtin_nontemporal_store(gc[ch], &gcolor[cbase + ch * HW]);
       __builtin_nontemporal_store(gd, &gcolor[cbase + 3 * HW]);
-    } else {
-      lr = ld = nv = 0.0f;
+      sums.rgb += lr;
+      sums.depth += valid ? fabsf(dd) : 0.0f;
+      sums.valid += valid ? 1.0f : 0.0f;
     }
   }
-  // decode and cross-entropy per 32-pixel half: logits^T[cb][.] in D layout, lane l holding
-  // pixel 32 pb + l32, classes drow(r) + 32 cb; each pixel's classes span lanes l32 and l32 + 32.
-  // The hidden layer's ReLU masks are kept for the backward (the same D layout); the halves
-  // are unrolled so that the masks stay in registers.
-  uint32_t onb[2][2];
-#pragma unroll
+  // Per half of 32 pixels, decode, cross-entropy and their backward in one go. In the D layout
+  // lane l holds pixel 32 pb + l32 of hidden units (or classes) drow(r) + 32 hb, which is also the
+  // operand layout of the next product over them, so the logit gradients go from the softmax to
+  // the products over classes in registers, split once; only the product over pixels (5a) takes
+  // them from LDS, where it finds a class's pixels side by side.
+#pragma unroll 1
   for (int pb = 0; pb < 2; ++pb) {
     const int q = l32 + 32 * pb;
     const bool qlive = q < nlive;
     const int y = __shfl(y_own, q, 64);
-    v16f H[2];
-    {
-      v4s ehi[2], elo[2];
+    // E with d in registers, pixels across lanes
+    v4s ehi[2], elo[2];
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        float e[4];
+    for (int ks = 0; ks < 2; ++ks) {
+      float e[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float v = S.E[8 * ks + 4 * (lane >> 5) + j][q];
-          e[j] = qlive ? v : 0.0f;
-        }
-        split4(e, ehi[ks], elo[ks]);
+      for (int j = 0; j < 4; ++j) {
+        const float v = S.E[8 * ks + 4 * half + j][q];
+        e[j] = qlive ? v : 0.0f;
       }
-#pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
-        H[hb] = mfma2(w1a[hb][0], w1a[hb][1], ehi[0], ehi[1], zero16());
-        H[hb] = mfma2(w1a[hb][0], w1a[hb][1], elo[0], elo[1], H[hb]);
-      }
-#pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
-        uint32_t bits = 0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float pre = H[hb][r] + L.b1[drow(r, lane) + 32 * hb];
-          bits |= (pre > 0.0f ? 1u : 0u) << r;
-          H[hb][r] = fmaxf(pre, 0.0f);
-        }
-        onb[pb][hb] = bits;
-      }
+      split4(e, ehi[ks], elo[ks]);
     }
-    v16f Lg[2];
+    v16f H[2];
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-      Lg[cb] = zero16();
-      const uint16_t* wrow = w2r + (l32 + 32 * cb) * kWtStride + 8 * (lane >> 5);
+    for (int hb = 0; hb < 2; ++hb) {
+      H[hb] = mfma2(w1a[hb][0], w1a[hb][1], ehi[0], ehi[1], zero16());
+      H[hb] = mfma2(w1a[hb][0], w1a[hb][1], elo[0], elo[1], H[hb]);
 #pragma unroll
-      for (int s2 = 0; s2 < 4; ++s2) {
-        // A = W2 (i = class l32 + 32 cb, k = hidden 8 ks + 4 (l / 32) + j, ks = 2 s2, 2 s2 + 1);
-        // rows >= C are zero
-        const v8s a = *reinterpret_cast<const v8s*>(wrow + 16 * s2);
-        v4s hi[2], lo[2];
+      for (int r = 0; r < 16; ++r) H[hb][r] = fmaxf(H[hb][r] + L.b1[drow(r, lane) + 32 * hb], 0.0f);
+    }
+    // logits: A = W2 (i = class l32 + 32 cb, k = hidden 8 ks + 4 half + j); rows >= C are zero
+    v16f Lg[2] = {zero16(), zero16()};
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int ks = 2 * s2 + u;
-          float x[4];
+    for (int s2 = 0; s2 < 4; ++s2) {
+      v4s hi[2], lo[2];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) x[j] = H[ks >> 2][4 * (ks & 3) + j];
-          split4(x, hi[u], lo[u]);
-        }
+      for (int u = 0; u < 2; ++u) {
+        const int ks = 2 * s2 + u;
+        float x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = H[ks >> 2][4 * (ks & 3) + j];
+        split4(x, hi[u], lo[u]);
+      }
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        const v8s a = *reinterpret_cast<const v8s*>(w2r + (l32 + 32 * cb) * kWtStride + 16 * s2 + 8 * half);
         Lg[cb] = mfma2(a, hi[0], hi[1], Lg[cb]);
         Lg[cb] = mfma2(a, lo[0], lo[1], Lg[cb]);
       }
     }
-    // softmax over the pixel's classes: this lane's 32, then the partner lane's
+    // softmax over the pixel's classes: this lane's 32, then the partner lane's. b2s is minus
+    // infinity for an absent class, whose logit then leaves nothing behind.
     float m = -INFINITY;
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int c = drow(r, lane) + 32 * cb;
-        const float v = c < C ? Lg[cb][r] + b2r[cb][r] : -INFINITY;
-        Lg[cb][r] = v;
-        m = fmaxf(m, v);
+        Lg[cb][r] += b2s[drow(r, lane) + 32 * cb];
+        m = fmaxf(m, Lg[cb][r]);
       }
     m = fmaxf(m, __shfl_xor(m, 32, 64));
+    const int yl = y - 4 * half;   // class drow(r) + 32 cb is 8 (r / 4) + r % 4 + 32 cb of this lane's
     float z = 0.0f, xy = 0.0f;
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int c = drow(r, lane) + 32 * cb;
-        xy = c == y ? Lg[cb][r] : xy;
-        const float e = c < C ? __expf(Lg[cb][r] - m) : 0.0f;
+        xy = yl == 8 * (r >> 2) + (r & 3) + 32 * cb ? Lg[cb][r] : xy;
+        const float e = __expf(Lg[cb][r] - m);
         Lg[cb][r] = e;
         z += e;
       }
     z += __shfl_xor(z, 32, 64);
     xy += __shfl_xor(xy, 32, 64);
     const bool labelled = qlive && y >= 0 && y < C;   // outside [0, C): unlabelled, no semantic term
-    if (labelled && lane < 32) ls += (m + __logf(z) - xy) * invp;
+    if (labelled && lane < 32) sums.ce += (m + __logf(z) - xy) * invp;
     const float sc = labelled ? w2 * invp / z : 0.0f;
     const float oh = labelled ? w2 * invp : 0.0f;
-    // dlogits to LDS [class][pixel] (rows of absent classes stay zero)
+    v4s dhi[8], dlo[8];   // dlogits as an operand over classes, k-step ks
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = drow(r, lane) + 32 * cb;
-        if (c < C) sg[c * kGst + q] = Lg[cb][r] * sc - (c == y ? oh : 0.0f);
+      for (int g = 0; g < 4; ++g) {
+        float x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = 4 * g + j;
+          x[j] = Lg[cb][r] * sc - (yl == 8 * (r >> 2) + (r & 3) + 32 * cb ? oh : 0.0f);
+          sg[(drow(r, lane) + 32 * cb) * kFst + l32] = x[j];
+        }
+        split4(x, dhi[4 * cb + g], dlo[4 * cb + g]);
       }
-  }
-  wave_fence();
-  head_chunk_backward<false, true>(L, sg, &S.E[0][0], kEst, gcolor + ci.pixel_base * K + 4 * HW + ci.local0, HW,
-                                   nlive, w1a, b1l, acc, onb);
-  wave_fence();
-  // loss partial sums: one atomic per wave and quantity (a chunk lies in one item)
-  const float a = wave_sum(lr), bsum = wave_sum(ld), c = wave_sum(ls), v = wave_sum(nv);
-  if (lane == 0) {
-    const int slot = (int)(ci.chunk % n_slots);
-    float* loss = loss_slots + slot;
-    atomicAdd(&loss[(3 * ci.item + 0) * n_slots], a);
-    if (v != 0.0f) {
-      atomicAdd(&loss[(3 * ci.item + 1) * n_slots], bsum);
-      atomicAdd(&count_slots[ci.item * n_slots + slot], v);
+    // (2) dH^T = W2^T dlogits^T: A = W2^T (i = hidden l32 + 32 hb, k = class 8 ks + 4 half + j),
+    // masked by the ReLU
+    v16f dHT[2] = {zero16(), zero16()};
+#pragma unroll
+    for (int s2 = 0; s2 < 4; ++s2)
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        const v8s a = *reinterpret_cast<const v8s*>(L.w2t + (l32 + 32 * hb) * kWtStride + 16 * s2 + 8 * half);
+        dHT[hb] = mfma2(a, dhi[2 * s2], dhi[2 * s2 + 1], dHT[hb]);
+        dHT[hb] = mfma2(a, dlo[2 * s2], dlo[2 * s2 + 1], dHT[hb]);
+      }
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dHT[hb][r] = H[hb][r] > 0.0f ? dHT[hb][r] : 0.0f;
+    // (3) dE^T = W1^T dH^T: A = W1^T (i = d l32, k = hidden 8 ks + 4 half + j)
+    {
+      v16f dE = zero16();
+#pragma unroll
+      for (int s2 = 0; s2 < 4; ++s2) {
+        v8s a = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (l32 < kDin) a = *reinterpret_cast<const v8s*>(L.w1t + l32 * kWtStride + 16 * s2 + 8 * half);
+        v4s hi[2], lo[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int ks = 2 * s2 + u;
+          float x[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[j] = dHT[ks >> 2][4 * (ks & 3) + j];
+          split4(x, hi[u], lo[u]);
+        }
+        dE = mfma2(a, hi[0], hi[1], dE);
+        dE = mfma2(a, lo[0], lo[1], dE);
+      }
+      if (qlive) {   // rows 0..15 = d
+        float* dst = gcolor + ci.pixel_base * K + 4 * HW + ci.local0 + q;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) dst[(int64_t)drow(r, lane) * HW] = dE[r];
+      }
     }
-    atomicAdd(&loss[(3 * ci.item + 2) * n_slots], c);
+    // (4) H with pixels in registers: A = E (i = pixel), B = W1^T (k = d, j = hidden l32 + 32 hb);
+    // dH likewise: A = dlogits (i = pixel, k = class), B = W2 (j = hidden)
+    v16f dH[2] = {zero16(), zero16()};
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      H[hb] = mfma2(ehi[0], ehi[1], w1a[hb][0], w1a[hb][1], zero16());
+      H[hb] = mfma2(elo[0], elo[1], w1a[hb][0], w1a[hb][1], H[hb]);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) H[hb][r] = fmaxf(H[hb][r] + b1l[hb], 0.0f);
+    }
+#pragma unroll
+    for (int s2 = 0; s2 < 4; ++s2)
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        const v8s b = *reinterpret_cast<const v8s*>(L.w2t + (l32 + 32 * hb) * kWtStride + 16 * s2 + 8 * half);
+        dH[hb] = mfma2(dhi[2 * s2], dhi[2 * s2 + 1], b, dH[hb]);
+        dH[hb] = mfma2(dlo[2 * s2], dlo[2 * s2 + 1], b, dH[hb]);
+      }
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dH[hb][r] = H[hb][r] > 0.0f ? dH[hb][r] : 0.0f;
+    wave_fence();
+    // (5) over the half's pixels p = 8 kk + 4 half + j (registers 4 kk + j):
+    //  dW2[c][h] += dlogits[c][p] relu(H)[p][h], A = dlogits (i = class l32 + 32 cb, k = p);
+    //  dW1[h][d] += dH[p][h] [E, 1][p][d], A = dH (i = hidden l32 + 32 hb, k = p), B = [E, 1] (j = d l32)
+    const float* Ed = &S.E[min(l32, kDin - 1)][32 * pb];
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      v4s hhi[2][2], hlo[2][2];
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          float y4[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y4[j] = H[hb][4 * (2 * k2 + u) + j];
+          split4(y4, hhi[hb][u], hlo[hb][u]);
+        }
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        v4s ahi[2], alo[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float4 v = *reinterpret_cast<const float4*>(sg + (l32 + 32 * cb) * kFst + 8 * (2 * k2 + u) + 4 * half);
+          const float x[4] = {v.x, v.y, v.z, v.w};
+          acc.B2[cb] += (x[0] + x[1]) + (x[2] + x[3]);
+          split4(x, ahi[u], alo[u]);
+        }
+#pragma unroll
+        for (int hb = 0; hb < 2; ++hb) {
+          acc.W2[cb][hb] = mfma2(ahi[0], ahi[1], hhi[hb][0], hhi[hb][1], acc.W2[cb][hb]);
+          acc.W2[cb][hb] = mfma2(ahi[0], ahi[1], hlo[hb][0], hlo[hb][1], acc.W2[cb][hb]);
+          acc.W2[cb][hb] = mfma2(alo[0], alo[1], hhi[hb][0], hhi[hb][1], acc.W2[cb][hb]);
+        }
+      }
+      v4s bhi[2], blo[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int p0 = 8 * (2 * k2 + u) + 4 * half;
+        float e[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float v = Ed[p0 + j];
+          e[j] = 32 * pb + p0 + j >= nlive ? 0.0f : (l32 < kDin ? v : (l32 == kDin ? 1.0f : 0.0f));
+        }
+        split4(e, bhi[u], blo[u]);
+      }
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        v4s ahi[2], alo[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          float y4[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y4[j] = dH[hb][4 * (2 * k2 + u) + j];
+          split4(y4, ahi[u], alo[u]);
+        }
+        acc.W1[hb] = mfma2(ahi[0], ahi[1], bhi[0], bhi[1], acc.W1[hb]);
+        acc.W1[hb] = mfma2(ahi[0], ahi[1], blo[0], blo[1], acc.W1[hb]);
+        acc.W1[hb] = mfma2(alo[0], alo[1], bhi[0], bhi[1], acc.W1[hb]);
+      }
+    }
+    wave_fence();   // the half's rows are read before the next half writes them
   }
 }
 
@@ -829,8 +941,9 @@ __global__ __launch_bounds__(256, 1) void k_head_loss(const gs_item* __restrict_
                                                       float w0, float w2, bool rgb_grad, int n_slots,
                                                       float* __restrict__ loss_slots, float* __restrict__ count_slots,
                                                       float* __restrict__ gcolor, float* __restrict__ partial) {
-  __shared__ HeadLds L;
+  __shared__ FusedLds L;
   __shared__ __align__(16) uint16_t w2r[kHid * kWtStride];   // W2 [class][kperm(hidden)], rows >= C zero
+  __shared__ float b2s[kHid];                                // b2, minus infinity for absent classes
   __shared__ ChunkStage SA[4];
   __shared__ ChunkStage SB[4];
   const int lane = threadIdx.x & 63;
@@ -840,20 +953,13 @@ __global__ __launch_bounds__(256, 1) void k_head_loss(const gs_item* __restrict_
     const int c = i / kHid, h = i % kHid;
     w2r[c * kWtStride + kperm(h)] = c < C ? W2[c * kHid + h] : (uint16_t)0;
   }
+  if (threadIdx.x < kHid) b2s[threadIdx.x] = (int)threadIdx.x < C ? b2[threadIdx.x] : -INFINITY;
   HeadAcc acc;
   v4s w1a[2][2];
   float b1l[2];
   head_setup(L, C, W1, b1, W2, acc, w1a, b1l);   // ends in a block barrier: w2r is complete
-  float* sg = L.buf + wave * kHid * kGst;
-  // b2 of this lane's classes drow(r) + 32 cb
-  float b2r[2][16];
-#pragma unroll
-  for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int c = drow(r, lane) + 32 * cb;
-      b2r[cb][r] = c < C ? b2[c] : 0.0f;
-    }
+  float* sg = L.buf + wave * kHid * kFst;
+  LossSums sums{0.0f, 0.0f, 0.0f, 0.0f, -1, 0};
   ConstItems citems = (ConstItems)items;
   ChunkCursor cur;
   cur.item = 0;
@@ -874,16 +980,17 @@ __global__ __launch_bounds__(256, 1) void k_head_loss(const gs_item* __restrict_
     const bool hb = chunk_info(citems, n_items, ca.chunk + stride, cur, cb);
     if (!hb) cb = ca;
     stage_chunk(SB[wave], cb, K, color, trgb, tdepth, tlabel);
-    head_loss_chunk(L, w2r, SA[wave], ca, sg, K, C, w0, w2, rgb_grad, n_slots, b2r, w1a, b1l, acc, loss_slots,
-                    count_slots, gcolor);
+    head_loss_chunk(L, w2r, SA[wave], ca, sg, K, C, w0, w2, rgb_grad, n_slots, b2s, w1a, b1l, acc, sums,
+                    loss_slots, count_slots, gcolor);
     if (!hb) break;
     const bool ha = chunk_info(citems, n_items, cb.chunk + stride, cur, ca);
     if (!ha) ca = cb;
     stage_chunk(SA[wave], ca, K, color, trgb, tdepth, tlabel);
-    head_loss_chunk(L, w2r, SB[wave], cb, sg, K, C, w0, w2, rgb_grad, n_slots, b2r, w1a, b1l, acc, loss_slots,
-                    count_slots, gcolor);
+    head_loss_chunk(L, w2r, SB[wave], cb, sg, K, C, w0, w2, rgb_grad, n_slots, b2s, w1a, b1l, acc, sums,
+                    loss_slots, count_slots, gcolor);
     if (!ha) break;
   }
+  flush_loss(sums, n_slots, loss_slots, count_slots);
   // the last iteration's loads into the unused buffer are complete before the block's LDS
   // is reused below
   __builtin_amdgcn_s_waitcnt(0);
