@@ -118,15 +118,15 @@ constexpr int kGst = 65;   // LDS row stride of the staged logit gradients
 // at 16 s + 8 h: one 16-byte LDS read.
 __host__ __device__ constexpr int kperm(int k) { return (k & ~12) | ((k & 4) << 1) | ((k & 8) >> 1); }
 
-template <int ROW>
+template <int ROW, int WAVES>
 struct alignas(16) HeadLdsOf {
   static constexpr int kRow = ROW;
-  float buf[4 * kHid * ROW];         // per wave [class][pixel]; the block's partial at the end
+  float buf[WAVES * kHid * ROW];         // per wave [class][pixel]; the block's partial at the end
   uint16_t w2t[kHid * kWtStride];    // W2^T [hidden][kperm(class)], classes >= C zero
   uint16_t w1t[kDin * kWtStride];    // W1^T [d][kperm(hidden)]
   float b1[kHid];
 };
-using HeadLds = HeadLdsOf<kGst>;
+using HeadLds = HeadLdsOf<kGst, 4>;
 
 // Per-lane accumulators of the weight gradients over a block's chunks.
 struct HeadAcc {
@@ -139,11 +139,11 @@ __device__ __forceinline__ void head_setup(LDS& L, int C, const uint16_t* __rest
                                            const float* __restrict__ b1, const uint16_t* __restrict__ W2,
                                            HeadAcc& acc, v4s (&w1a)[2][2], float (&b1l)[2]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, l32 = lane & 31;
-  for (int i = threadIdx.x; i < kHid * kHid; i += 256) {
+  for (int i = threadIdx.x; i < kHid * kHid; i += (int)blockDim.x) {
     const int c = i / kHid, h = i % kHid;
     L.w2t[h * kWtStride + kperm(c)] = c < C ? W2[c * kHid + h] : (uint16_t)0;
   }
-  for (int i = threadIdx.x; i < kHid * kDin; i += 256) {
+  for (int i = threadIdx.x; i < kHid * kDin; i += (int)blockDim.x) {
     const int h = i / kDin, d = i % kDin;
     L.w1t[d * kWtStride + kperm(h)] = W1[h * kDin + d];
   }
@@ -371,13 +371,13 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
   }
 }
 
-// Sums the block's four waves' accumulators in LDS and writes the block's partial.
+// Sums the block's waves' accumulators in LDS and writes the block's partial.
 template <class LDS>
 __device__ __forceinline__ void head_write_partial(LDS& L, const HeadAcc& acc, float* __restrict__ partial) {
   const int lane = threadIdx.x & 63, l32 = lane & 31;
   float* s_acc = L.buf;
   __syncthreads();
-  for (int i = threadIdx.x; i < kPart; i += 256) s_acc[i] = 0.0f;
+  for (int i = threadIdx.x; i < kPart; i += (int)blockDim.x) s_acc[i] = 0.0f;
   __syncthreads();
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
@@ -396,7 +396,7 @@ __device__ __forceinline__ void head_write_partial(LDS& L, const HeadAcc& acc, f
     for (int r = 0; r < 16; ++r) atomicAdd(&s_acc[kPartW2 + (drow(r, lane) + 32 * hb) * 32 + l32], acc.W1[hb][r]);
   __syncthreads();
   float* out = partial + (int64_t)blockIdx.x * kPart;
-  for (int i = threadIdx.x; i < kPart; i += 256) out[i] = s_acc[i];
+  for (int i = threadIdx.x; i < kPart; i += (int)blockDim.x) out[i] = s_acc[i];
 }
 
 __device__ __forceinline__ void wave_fence() {
@@ -459,22 +459,20 @@ __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__
 // No logits touch global memory. Loss partial sums go to the same per-item slots as the
 // plain loss's.
 //
-// At one wave per SIMD nothing hides a load's latency, so every input a chunk reads (the
-// 16 embedding planes, colour and depth, the targets) comes from LDS: while a wave works
-// on one chunk, direct global-to-LDS loads fill the other of its two staging buffers with
-// its next chunk. The buffers are two separate LDS arrays and the loop handles two chunks
-// per iteration, one from each, so that the compiler's wait for a buffer's loads never
-// waits for the other's. Vector issue is 57 % busy, its waits 23 %: four full-HD pyramids with 52
-// classes 2.80 ms with the logit gradients staged for both halves and read back (and split) as three
-// operands, and the ReLU masks carried as bits; 1.95 ms with all that in registers.
-constexpr int kEst = 68;   // row stride (floats) of a staged embedding plane
+// A block is eight waves, two per SIMD, on one CU: the weights are in LDS once for all, and what
+// is left of the 160 KB is a wave's half of logit gradients (9 KB) and two buffers for the 16
+// embedding planes of a chunk (4 KB each): while a wave works on one chunk, direct global-to-LDS
+// loads fill the other buffer with its next chunk. The buffers are two separate LDS arrays and the
+// loop handles two chunks per iteration, one from each, so that the compiler's wait for a buffer's
+// loads never waits for the other's. Labels come one chunk ahead in a register, colour, depth and
+// their targets during the chunk. (One wave per SIMD with every input staged, logit gradients
+// staged and read back as three operands, ReLU masks as bits: 2.80 ms on four full-HD pyramids with
+// 52 classes; everything over classes in registers: 1.95; two waves per SIMD: 1.74.)
+constexpr int kEst = 65;   // row stride (floats) of a staged embedding plane: lanes on rows meet no bank twice
+constexpr int kFusedWaves = 8;
 
-struct ChunkStage {        // one wave's staged chunk: 64 pixels of every input plane
+struct ChunkStage {        // one wave's staged chunk: 64 pixels of every embedding plane
   float E[kDin][kEst];
-  float col[4][64];
-  float tr[3][64];
-  float td[64];
-  int32_t lab[64];
 };
 
 struct ChunkInfo {
@@ -614,22 +612,21 @@ __global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__
   }
 }
 
-constexpr int kStageLoads = kDin + 4 + 3 + 1 + 1;   // direct-to-LDS loads per staged chunk
+constexpr int kStageLoads = kDin;   // direct-to-LDS loads per staged chunk
 
 // Waits until at most kStageLoads vector memory operations are in flight: those are the
 // other buffer's loads, issued last, so everything before them -- this buffer's loads and
 // the previous chunk's stores -- is complete. Vector memory operations complete in issue
-// order. (s_waitcnt encoding: vmcnt 25 in bits 3:0 and 15:14, expcnt and lgkmcnt not
+// order. (s_waitcnt encoding: vmcnt 16 in bits 3:0 and 15:14, expcnt and lgkmcnt not
 // waited for.)
 __device__ __forceinline__ void wait_own_stage() {
-  static_assert(kStageLoads == 25, "the wait below encodes vmcnt(25)");
-  __builtin_amdgcn_s_waitcnt((1 << 14) | (0xF << 8) | (0x7 << 4) | 9);
+  static_assert(kStageLoads == 16, "the wait below encodes vmcnt(16)");
+  __builtin_amdgcn_s_waitcnt((1 << 14) | (0xF << 8) | (0x7 << 4) | 0);
 }
 
 // Issues the direct-to-LDS loads of chunk ci into S (lane l fills entry l of every row;
 // lanes past the item's last pixel load that pixel again).
-__device__ __forceinline__ void stage_chunk(ChunkStage& S, const ChunkInfo& ci, int K, const float* color,
-                                            const float* trgb, const float* tdepth, const int32_t* tlabel) {
+__device__ __forceinline__ void stage_chunk(ChunkStage& S, const ChunkInfo& ci, int K, const float* color) {
   const int lane = threadIdx.x & 63;
   const int64_t p = ci.local0 + min(lane, ci.nlive - 1);
   const float* cb = color + ci.pixel_base * K + p;
@@ -639,13 +636,9 @@ __device__ __forceinline__ void stage_chunk(ChunkStage& S, const ChunkInfo& ci, 
 #pragma unroll
   for (int d = 0; d < kDin; ++d)
     __builtin_amdgcn_global_load_lds(cb + (int64_t)(4 + d) * ci.HW, &S.E[d][0], 4, 0, 0);
-#pragma unroll
-  for (int ch = 0; ch < 4; ++ch) __builtin_amdgcn_global_load_lds(cb + (int64_t)ch * ci.HW, &S.col[ch][0], 4, 0, 0);
-  const float* tb = trgb + ci.pixel_base * 3 + p;
-#pragma unroll
-  for (int ch = 0; ch < 3; ++ch) __builtin_amdgcn_global_load_lds(tb + (int64_t)ch * ci.HW, &S.tr[ch][0], 4, 0, 0);
-  __builtin_amdgcn_global_load_lds(tdepth + ci.pixel_base + p, &S.td[0], 4, 0, 0);
-  __builtin_amdgcn_global_load_lds(tlabel + ci.pixel_base + p, &S.lab[0], 4, 0, 0);
+}
+__device__ __forceinline__ int load_label(const ChunkInfo& ci, const int32_t* tlabel) {
+  return tlabel[ci.pixel_base + ci.local0 + min((int)(threadIdx.x & 63), ci.nlive - 1)];
 }
 
 // A wave's loss sums over its chunks of one item, per lane.
@@ -670,14 +663,16 @@ __device__ __forceinline__ void flush_loss(LossSums& a, int n_slots, float* loss
 
 // Everything k_head_loss does for one staged chunk.
 constexpr int kFst = 36;   // LDS row stride of a half's logit gradients (32 pixels)
-using FusedLds = HeadLdsOf<kFst>;
+using FusedLds = HeadLdsOf<kFst, kFusedWaves>;
 __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_t* w2r, const ChunkStage& S,
                                                 const ChunkInfo& ci, float* sg, int K, int C, float w0, float w2,
                                                 bool rgb_grad, int n_slots, const float* b2s,
                                                 const v4s (&w1a)[2][2], const float (&b1l)[2], HeadAcc& acc,
-                                                LossSums& sums, float* __restrict__ loss_slots,
-                                                float* __restrict__ count_slots, float* __restrict__ gcolor) {
-  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+                                                LossSums& sums, int y_own, const float* __restrict__ color,
+                                                const float* __restrict__ trgb, const float* __restrict__ tdepth,
+                                                float* __restrict__ loss_slots, float* __restrict__ count_slots,
+                                                float* __restrict__ gcolor) {
+  const int lane = threadIdx.x & 63;
   const int64_t HW = ci.HW;
   const int nlive = ci.nlive;
   const float invp = 1.0f / (float)HW;
@@ -687,32 +682,6 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
     sums.slot = (int)(ci.chunk % n_slots);
   }
   wait_own_stage();
-  // L1 colour and depth, lane = pixel
-  const bool live = lane < nlive;
-  const int64_t cbase = ci.pixel_base * K + ci.local0 + min(lane, nlive - 1);
-  const int y_own = S.lab[lane];
-  {
-    const float td = S.td[lane], inv3 = 1.0f / (3.0f * (float)HW);
-    float gc[3], lr = 0.0f;
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-      const float d = S.col[ch][lane] - S.tr[ch][lane];
-      lr += fabsf(d) * inv3;
-      gc[ch] = w0 * (float)((d > 0.0f) - (d < 0.0f)) * inv3;
-    }
-    const float dd = S.col[3][lane] - td;
-    const bool valid = td > 0.0f;
-    const float gd = valid ? (float)((dd > 0.0f) - (dd < 0.0f)) : 0.0f;
-    if (live) {
-      if (rgb_grad)
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) __builtin_nontemporal_store(gc[ch], &gcolor[cbase + ch * HW]);
-      __builtin_nontemporal_store(gd, &gcolor[cbase + 3 * HW]);
-      sums.rgb += lr;
-      sums.depth += valid ? fabsf(dd) : 0.0f;
-      sums.valid += valid ? 1.0f : 0.0f;
-    }
-  }
   // Per half of 32 pixels, decode, cross-entropy and their backward in one go. In the D layout
   // lane l holds pixel 32 pb + l32 of hidden units (or classes) drow(r) + 32 hb, which is also the
   // operand layout of the next product over them, so the logit gradients go from the softmax to
@@ -720,6 +689,11 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
   // them from LDS, where it finds a class's pixels side by side.
 #pragma unroll 1
   for (int pb = 0; pb < 2; ++pb) {
+    // (a lane number of unknown origin: the many LDS addresses formed from it are not hoisted out of
+    // the loops, where they would hold the registers that the accumulators need)
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int l32 = lane & 31, half = lane >> 5;
     const int q = l32 + 32 * pb;
     const bool qlive = q < nlive;
     const int y = __shfl(y_own, q, 64);
@@ -743,10 +717,12 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
 #pragma unroll
       for (int r = 0; r < 16; ++r) H[hb][r] = fmaxf(H[hb][r] + L.b1[drow(r, lane) + 32 * hb], 0.0f);
     }
+    __builtin_amdgcn_sched_barrier(0);
     // logits: A = W2 (i = class l32 + 32 cb, k = hidden 8 ks + 4 half + j); rows >= C are zero
     v16f Lg[2] = {zero16(), zero16()};
 #pragma unroll
     for (int s2 = 0; s2 < 4; ++s2) {
+      __builtin_amdgcn_sched_barrier(0);
       v4s hi[2], lo[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -763,6 +739,7 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
         Lg[cb] = mfma2(a, lo[0], lo[1], Lg[cb]);
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
     // softmax over the pixel's classes: this lane's 32, then the partner lane's. b2s is minus
     // infinity for an absent class, whose logit then leaves nothing behind.
     float m = -INFINITY;
@@ -791,6 +768,7 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
     if (labelled && lane < 32) sums.ce += (m + __logf(z) - xy) * invp;
     const float sc = labelled ? w2 * invp / z : 0.0f;
     const float oh = labelled ? w2 * invp : 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
     v4s dhi[8], dlo[8];   // dlogits as an operand over classes, k-step ks
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb)
@@ -805,21 +783,24 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
         }
         split4(x, dhi[4 * cb + g], dlo[4 * cb + g]);
       }
+    __builtin_amdgcn_sched_barrier(0);
     // (2) dH^T = W2^T dlogits^T: A = W2^T (i = hidden l32 + 32 hb, k = class 8 ks + 4 half + j),
     // masked by the ReLU
-    v16f dHT[2] = {zero16(), zero16()};
+    v16f dHT[2];
 #pragma unroll
-    for (int s2 = 0; s2 < 4; ++s2)
+    for (int hb = 0; hb < 2; ++hb) {
+      __builtin_amdgcn_sched_barrier(0);
+      dHT[hb] = zero16();
 #pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
+      for (int s2 = 0; s2 < 4; ++s2) {
         const v8s a = *reinterpret_cast<const v8s*>(L.w2t + (l32 + 32 * hb) * kWtStride + 16 * s2 + 8 * half);
         dHT[hb] = mfma2(a, dhi[2 * s2], dhi[2 * s2 + 1], dHT[hb]);
         dHT[hb] = mfma2(a, dlo[2 * s2], dlo[2 * s2 + 1], dHT[hb]);
       }
 #pragma unroll
-    for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
       for (int r = 0; r < 16; ++r) dHT[hb][r] = H[hb][r] > 0.0f ? dHT[hb][r] : 0.0f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
     // (3) dE^T = W1^T dH^T: A = W1^T (i = d l32, k = hidden 8 ks + 4 half + j)
     {
       v16f dE = zero16();
@@ -845,28 +826,32 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
         for (int r = 0; r < 8; ++r) dst[(int64_t)drow(r, lane) * HW] = dE[r];
       }
     }
-    // (4) H with pixels in registers: A = E (i = pixel), B = W1^T (k = d, j = hidden l32 + 32 hb);
-    // dH likewise: A = dlogits (i = pixel, k = class), B = W2 (j = hidden)
-    v16f dH[2] = {zero16(), zero16()};
+    __builtin_amdgcn_sched_barrier(0);
+    // (4) dH with pixels in registers: A = dlogits (i = pixel, k = class), B = W2 (j = hidden
+    // l32 + 32 hb); H likewise: A = E (i = pixel), B = W1^T (k = d)
+    v16f dH[2];
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      dH[hb] = zero16();
+#pragma unroll
+      for (int s2 = 0; s2 < 4; ++s2) {
+        const v8s b = *reinterpret_cast<const v8s*>(L.w2t + (l32 + 32 * hb) * kWtStride + 16 * s2 + 8 * half);
+        dH[hb] = mfma2(dhi[2 * s2], dhi[2 * s2 + 1], b, dH[hb]);
+        dH[hb] = mfma2(dlo[2 * s2], dlo[2 * s2 + 1], b, dH[hb]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int hb = 0; hb < 2; ++hb) {
       H[hb] = mfma2(ehi[0], ehi[1], w1a[hb][0], w1a[hb][1], zero16());
       H[hb] = mfma2(elo[0], elo[1], w1a[hb][0], w1a[hb][1], H[hb]);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) H[hb][r] = fmaxf(H[hb][r] + b1l[hb], 0.0f);
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < 4; ++s2)
-#pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
-        const v8s b = *reinterpret_cast<const v8s*>(L.w2t + (l32 + 32 * hb) * kWtStride + 16 * s2 + 8 * half);
-        dH[hb] = mfma2(dhi[2 * s2], dhi[2 * s2 + 1], b, dH[hb]);
-        dH[hb] = mfma2(dlo[2 * s2], dlo[2 * s2 + 1], b, dH[hb]);
+      for (int r = 0; r < 16; ++r) {
+        H[hb][r] = fmaxf(H[hb][r] + b1l[hb], 0.0f);
+        dH[hb][r] = H[hb][r] > 0.0f ? dH[hb][r] : 0.0f;
       }
-#pragma unroll
-    for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dH[hb][r] = H[hb][r] > 0.0f ? dH[hb][r] : 0.0f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
     wave_fence();
     // (5) over the half's pixels p = 8 kk + 4 half + j (registers 4 kk + j):
     //  dW2[c][h] += dlogits[c][p] relu(H)[p][h], A = dlogits (i = class l32 + 32 cb, k = p);
@@ -874,6 +859,7 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
     const float* Ed = &S.E[min(l32, kDin - 1)][32 * pb];
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2) {
+      __builtin_amdgcn_sched_barrier(0);
       v4s hhi[2][2], hlo[2][2];
 #pragma unroll
       for (int hb = 0; hb < 2; ++hb)
@@ -930,9 +916,41 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
     }
     wave_fence();   // the half's rows are read before the next half writes them
   }
+  // L1 colour and depth, lane = pixel
+  const bool live = lane < nlive;
+  const int64_t cbase = ci.pixel_base * K + ci.local0 + min(lane, nlive - 1);
+  float col[4], tr[3];
+#pragma unroll
+  for (int ch = 0; ch < 4; ++ch) col[ch] = color[cbase + ch * HW];
+  const int64_t tpix = ci.local0 + min(lane, nlive - 1);
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) tr[ch] = trgb[ci.pixel_base * 3 + tpix + ch * HW];
+  const float td = tdepth[ci.pixel_base + tpix];
+  {
+    const float inv3 = 1.0f / (3.0f * (float)HW);
+    float gc[3], lr = 0.0f;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+      const float d = col[ch] - tr[ch];
+      lr += fabsf(d) * inv3;
+      gc[ch] = w0 * (float)((d > 0.0f) - (d < 0.0f)) * inv3;
+    }
+    const float dd = col[3] - td;
+    const bool valid = td > 0.0f;
+    const float gd = valid ? (float)((dd > 0.0f) - (dd < 0.0f)) : 0.0f;
+    if (live) {
+      if (rgb_grad)
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) __builtin_nontemporal_store(gc[ch], &gcolor[cbase + ch * HW]);
+      __builtin_nontemporal_store(gd, &gcolor[cbase + 3 * HW]);
+      sums.rgb += lr;
+      sums.depth += valid ? fabsf(dd) : 0.0f;
+      sums.valid += valid ? 1.0f : 0.0f;
+    }
+  }
 }
 
-__global__ __launch_bounds__(256, 1) void k_head_loss(const gs_item* __restrict__ items, int n_items, int K, int C,
+__global__ __launch_bounds__(64 * kFusedWaves, 2) void k_head_loss(const gs_item* __restrict__ items, int n_items, int K, int C,
                                                       const float* __restrict__ color, const float* __restrict__ trgb,
                                                       const float* __restrict__ tdepth,
                                                       const int32_t* __restrict__ tlabel,
@@ -944,12 +962,12 @@ __global__ __launch_bounds__(256, 1) void k_head_loss(const gs_item* __restrict_
   __shared__ FusedLds L;
   __shared__ __align__(16) uint16_t w2r[kHid * kWtStride];   // W2 [class][kperm(hidden)], rows >= C zero
   __shared__ float b2s[kHid];                                // b2, minus infinity for absent classes
-  __shared__ ChunkStage SA[4];
-  __shared__ ChunkStage SB[4];
+  __shared__ ChunkStage SA[kFusedWaves];
+  __shared__ ChunkStage SB[kFusedWaves];
   const int lane = threadIdx.x & 63;
   // wave-uniform: the chunk walk and the item table reads stay in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int i = threadIdx.x; i < kHid * kHid; i += 256) {
+  for (int i = threadIdx.x; i < kHid * kHid; i += 64 * kFusedWaves) {
     const int c = i / kHid, h = i % kHid;
     w2r[c * kWtStride + kperm(h)] = c < C ? W2[c * kHid + h] : (uint16_t)0;
   }
@@ -965,29 +983,32 @@ __global__ __launch_bounds__(256, 1) void k_head_loss(const gs_item* __restrict_
   cur.item = 0;
   cur.first = 0;
   cur.end = ((int64_t)citems[0].W * citems[0].H + 63) / 64;
-  const int64_t stride = (int64_t)gridDim.x * 4;
+  const int64_t stride = (int64_t)gridDim.x * kFusedWaves;
   // Every iteration issues the same loads whether or not a next chunk exists (past the end
   // the current chunk is loaded again and not used), so the number of loads in flight is
   // the same on every path and each buffer's wait covers exactly its own loads.
   ChunkInfo ca, cb;
-  bool have = chunk_info(citems, n_items, (int64_t)blockIdx.x * 4 + wave, cur, ca);
+  bool have = chunk_info(citems, n_items, (int64_t)blockIdx.x * kFusedWaves + wave, cur, ca);
   if (!have) {
     head_write_partial(L, acc, partial);
     return;
   }
-  stage_chunk(SA[wave], ca, K, color, trgb, tdepth, tlabel);
+  int ya = load_label(ca, tlabel), yb;
+  stage_chunk(SA[wave], ca, K, color);
   for (;;) {
     const bool hb = chunk_info(citems, n_items, ca.chunk + stride, cur, cb);
     if (!hb) cb = ca;
-    stage_chunk(SB[wave], cb, K, color, trgb, tdepth, tlabel);
-    head_loss_chunk(L, w2r, SA[wave], ca, sg, K, C, w0, w2, rgb_grad, n_slots, b2s, w1a, b1l, acc, sums,
-                    loss_slots, count_slots, gcolor);
+    yb = load_label(cb, tlabel);
+    stage_chunk(SB[wave], cb, K, color);
+    head_loss_chunk(L, w2r, SA[wave], ca, sg, K, C, w0, w2, rgb_grad, n_slots, b2s, w1a, b1l, acc, sums, ya, color,
+                    trgb, tdepth, loss_slots, count_slots, gcolor);
     if (!hb) break;
     const bool ha = chunk_info(citems, n_items, cb.chunk + stride, cur, ca);
     if (!ha) ca = cb;
-    stage_chunk(SA[wave], ca, K, color, trgb, tdepth, tlabel);
-    head_loss_chunk(L, w2r, SB[wave], cb, sg, K, C, w0, w2, rgb_grad, n_slots, b2s, w1a, b1l, acc, sums,
-                    loss_slots, count_slots, gcolor);
+    ya = load_label(ca, tlabel);
+    stage_chunk(SA[wave], ca, K, color);
+    head_loss_chunk(L, w2r, SB[wave], cb, sg, K, C, w0, w2, rgb_grad, n_slots, b2s, w1a, b1l, acc, sums, yb, color,
+                    trgb, tdepth, loss_slots, count_slots, gcolor);
     if (!ha) break;
   }
   flush_loss(sums, n_slots, loss_slots, count_slots);
@@ -1063,9 +1084,9 @@ int launch_head_loss(const gs_item* items, int n_items, int64_t P, int K, const 
                      float* count_slots, float* gcolor, float* partial, float* gW1, float* gb1, float* gW2, float* gb2,
                      hipStream_t s) {
   if (P == 0) return GS_OK;
-  const int resident = resident_blocks(k_head_loss, 256, kHeadBlocksMax);
-  const int blocks = (int)std::min<int64_t>(std::min(kHeadBlocksMax, resident), ceil_div(ceil_div(P, 64) + n_items, 4));
-  hipLaunchKernelGGL(k_head_loss, dim3(blocks), dim3(256), 0, s, items, n_items, K, h.n_classes, color, t.rgb, t.depth,
+  const int resident = resident_blocks(k_head_loss, 64 * kFusedWaves, kHeadBlocksMax);
+  const int blocks = (int)std::min<int64_t>(std::min(kHeadBlocksMax, resident), ceil_div(ceil_div(P, 64) + n_items, kFusedWaves));
+  hipLaunchKernelGGL(k_head_loss, dim3(blocks), dim3(64 * kFusedWaves), 0, s, items, n_items, K, h.n_classes, color, t.rgb, t.depth,
                      t.label, h.W1, h.b1, h.W2, h.b2, w0, w2, rgb_grad, n_slots, loss_slots, count_slots, gcolor,
                      partial);
   hipLaunchKernelGGL(k_head_reduce, dim3((unsigned)ceil_div(kPart, 64)), dim3(256), 0, s, partial, blocks, h.n_classes,
