@@ -426,33 +426,65 @@ __device__ __forceinline__ Region wave_region(int tws, int r, int lane) {
   return g;
 }
 
-// Where a Gaussian's channels come from. `vec`: semantic rows (or embeddings) are read as
-// 16-byte (8-byte) vectors, which their alignment allows (sem_vec below); else one by one.
+// Where a Gaussian's channels come from, and how its semantic row is read (a template parameter:
+// a branch between the loads would make the compiler wait for them where its sides meet).
 struct FeatSrc {
   const float *rgb, *sem, *depth;
   const uint16_t* emb;
-  int n_sem, vec;
+  int n_sem;
 };
-// Rows of n_sem floats start on 16-byte boundaries if the array does and n_sem is a multiple
-// of 4; an embedding row is 32 bytes.
-inline int sem_vec(const gs_gaussians& g, int n_sem) {
-  return g.emb ? (uintptr_t)g.emb % 16 == 0 : (n_sem % 4 == 0 && (uintptr_t)g.sem % 16 == 0);
+enum FeatMode {
+  kRowVec,     // class logits, 16 bytes at a time: n_sem a multiple of 4, the array 16-byte aligned
+  kEmbVec,     // embedding, 8 bytes at a time: the array 16-byte aligned (a row is 32 bytes)
+  kValues      // logits or embedding, value by value
+};
+inline FeatMode feat_mode(const gs_gaussians& g, int n_sem) {
+  if (g.emb) return (uintptr_t)g.emb % 16 == 0 ? kEmbVec : kValues;
+  return n_sem > 0 && n_sem % 4 == 0 && (uintptr_t)g.sem % 16 == 0 ? kRowVec : kValues;
+}
+// The quads of channels k .. k + 3 (k % 4 = 0) of the rows of Gaussians g[p], into f[4 p ..]. Every
+// lane loads from a valid address; what lies past the last channel is dropped when it is used.
+template <int MODE, int NP>
+__device__ __forceinline__ void load_quads(const FeatSrc& s, const uint32_t (&g)[NP], int64_t foff, int k, float* f) {
+  if constexpr (MODE == kRowVec) {
+    const float* a = s.sem + (int64_t)s.n_sem * foff + (k < s.n_sem ? k : 0);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const float4 v = *reinterpret_cast<const float4*>(a + (uint64_t)(uint32_t)s.n_sem * g[p]);
+      f[4 * p] = v.x;
+      f[4 * p + 1] = v.y;
+      f[4 * p + 2] = v.z;
+      f[4 * p + 3] = v.w;
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float v = 0.0f;
+        if (k + i < s.n_sem) {
+          const int64_t at = (int64_t)s.n_sem * ((int64_t)g[p] + foff) + k + i;
+          v = s.emb ? __uint_as_float((uint32_t)s.emb[at] << 16) : s.sem[at];
+        }
+        f[4 * p + i] = v;
+      }
+  }
 }
 
 // A batch's features on their way from memory to F^T in LDS. Neighbouring lanes read the
 // neighbouring quads (four channels) of a row, so that a load touches few cache lines: QL
 // lanes a Gaussian for plain semantics, four for an embedding (8 bytes each). Colour and depth
 // come beside them: lane q < 32 Gaussian q's colour, lane 32 + q its depth.
-template <int NS, bool EMB>
+template <int NS, int MODE>
 struct Feats {
+  static constexpr bool EMB = MODE == kEmbVec;
   static constexpr int KP = SShape<NS>::KP;
   static constexpr int QL = EMB ? 4 : KP / 4, NP = QL / 2;   // lanes a Gaussian, passes over 32 Gaussians
   float f[EMB ? 1 : 4 * NP];
   uint2 r[EMB ? NP : 1];
   float c0, c1, c2;
 
-  // q-th queued Gaussian: its index at Q[8 q + 7] (0 where there is none). Every lane loads
-  // from a valid address; what it should not have is dropped by commit.
+  // q-th queued Gaussian: its index at Q[8 q + 7] (0 where there is none); see load_quads
   __device__ __forceinline__ void load(const FeatSrc& s, const float* Q, int64_t foff, int64_t e0, int lane) {
     uint32_t g[NP];
 #pragma unroll
@@ -460,45 +492,16 @@ struct Feats {
     const uint32_t gc = __float_as_uint(Q[8 * (lane & 31) + 7]);
     if constexpr (EMB) {
       const uint16_t* a = s.emb + 4 * (lane % QL);
-      if (s.vec) {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) r[p] = *reinterpret_cast<const uint2*>(a + 16 * (int64_t)g[p]);
-      } else {
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-          const uint16_t* b = a + 16 * (int64_t)g[p];
-          r[p] = make_uint2((uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16));
-        }
-      }
-    } else if (s.n_sem > 0) {
-      const int k = 4 * (lane % QL) < s.n_sem ? 4 * (lane % QL) : 0;
-      const float* a = s.sem + (int64_t)s.n_sem * foff + k;
-      if (s.vec) {
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-          const float4 v = *reinterpret_cast<const float4*>(a + (int64_t)s.n_sem * g[p]);
-          f[4 * p] = v.x;
-          f[4 * p + 1] = v.y;
-          f[4 * p + 2] = v.z;
-          f[4 * p + 3] = v.w;
-        }
-      } else {
-#pragma unroll
-        for (int p = 0; p < NP; ++p)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int o = k + i < s.n_sem ? i : 0;
-            f[4 * p + i] = a[(int64_t)s.n_sem * g[p] + o];
-          }
-      }
+      for (int p = 0; p < NP; ++p) r[p] = *reinterpret_cast<const uint2*>(a + 16 * (uint64_t)g[p]);
+    } else {
+      load_quads<MODE>(s, g, foff, 4 * (lane % QL), f);
     }
     const float* a = lane < 32 ? s.rgb + 3 * ((int64_t)gc + foff) : s.depth + (e0 + gc);
+    const int o = lane < 32 ? 1 : 0;   // (depth again for the lanes that have no colour to load)
     c0 = a[0];
-    c1 = c2 = 0.0f;
-    if (lane < 32) {
-      c1 = a[1];
-      c2 = a[2];
-    }
+    c1 = a[o];
+    c2 = a[2 * o];
   }
   // F^T[channel][Gaussian], packed hi|lo (an embedding value is its own hi part), of cnt
   // Gaussians; zero for the rest of the batch and past the last channel
@@ -508,23 +511,25 @@ struct Feats {
     for (int p = 0; p < NP; ++p) {
       const int q = p * (64 / QL) + lane / QL;
       uint32_t* d = FT + (4 + k) * kWs + q;
+      // (a mask: a branch around each value's conversion would wait for the loads one by one. A quad
+      // of a kRowVec row is whole or absent, one of kValues is zero past the last channel.)
+      const uint32_t m = q < cnt && (EMB || k < n_sem) ? ~0u : 0u;
       if constexpr (EMB) {
-        const uint32_t x = q < cnt ? r[p].x : 0u, y = q < cnt ? r[p].y : 0u;
-        d[0] = x << 16;
-        d[kWs] = x & 0xffff0000u;
-        d[2 * kWs] = y << 16;
-        d[3 * kWs] = y & 0xffff0000u;
+        d[0] = (r[p].x << 16) & m;
+        d[kWs] = (r[p].x & 0xffff0000u) & m;
+        d[2 * kWs] = (r[p].y << 16) & m;
+        d[3 * kWs] = (r[p].y & 0xffff0000u) & m;
       } else if (k < NS) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) d[i * kWs] = q < cnt && k + i < n_sem ? pack_hl(f[4 * p + i]) : 0u;
+        for (int i = 0; i < 4; ++i) d[i * kWs] = pack_hl(f[4 * p + i]) & m;
       }
     }
     uint32_t* d = FT + (lane < 32 ? 0 : 3 * kWs) + (lane & 31);
-    const bool live = (lane & 31) < cnt;
-    d[0] = live ? pack_hl(c0) : 0u;
+    const uint32_t m = (lane & 31) < cnt ? ~0u : 0u;
+    d[0] = pack_hl(c0) & m;
     if (lane < 32) {
-      d[kWs] = live ? pack_hl(c1) : 0u;
-      d[2 * kWs] = live ? pack_hl(c2) : 0u;
+      d[kWs] = pack_hl(c1) & m;
+      d[2 * kWs] = pack_hl(c2) & m;
     }
   }
 };
@@ -607,13 +612,14 @@ __device__ __forceinline__ int opaque_v(int x) { asm volatile("" : "+v"(x)); ret
 // against 0.21 ms: scratch traffic queues between the gathers).
 constexpr int kQueue = 128;     // a batch's remainder (31), 64 entries and a last batch's filling (32)
 
-template <int NS, bool SEG, bool EMB>
+template <int NS, bool SEG, int MODE>
 __global__ __launch_bounds__(256, NS <= 28 ? 3 : 2) void k_render_fwd_split(
     gs_config cfg, FeatSrc src, const float* __restrict__ rec, int64_t n, const gs_item* __restrict__ items, int n_items,
     const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, float* __restrict__ color,
     float* __restrict__ Tout, uint32_t* __restrict__ ncout, const uint2* __restrict__ work, uint32_t* __restrict__ ctl,
     FState fs) {
   using S = SShape<NS>;
+  constexpr bool EMB = MODE == kEmbVec;
   constexpr int CB = S::CB, KP = S::KP;
   __shared__ __align__(16) float s_queue[4][8 * kQueue];    // per wave: the record's six floats, list position, Gaussian
   __shared__ __align__(16) uint32_t s_ft[4][KP * kWs];      // per wave: F^T, packed hi|lo, [channel][Gaussian]
@@ -674,7 +680,7 @@ __global__ __launch_bounds__(256, NS <= 28 ? 3 : 2) void k_render_fwd_split(
     // composites the cnt (1..32) queued Gaussians from position o of the queue on
     auto batch = [&](int o, int cnt) {
       const float* R0 = Q + 8 * o;
-      Feats<NS, EMB> ft;
+      Feats<NS, MODE> ft;
       ft.load(src, R0, foff, e0, lane);
       // front-to-back recurrence, branch-free; only Tw carries from one Gaussian to the next:
       // T while the pixel is active, 0 once it has stopped (so that it takes nothing more); `at`
@@ -718,7 +724,6 @@ __global__ __launch_bounds__(256, NS <= 28 ? 3 : 2) void k_render_fwd_split(
 #pragma unroll
         for (int q = 16; q < kB; ++q) w[q] = 0.0f;
       }
-      if (__ballot(at > 0) == 0ull) return;
       if (at > 0) last = __float_as_uint(R0[8 * at - 2]);
       wave_sync();   // the previous batch's reads of F^T come first
       ft.commit(FT, src.n_sem, cnt, lane);
@@ -757,14 +762,14 @@ __global__ __launch_bounds__(256, NS <= 28 ? 3 : 2) void k_render_fwd_split(
       const bool active = alive();
       if (__ballot(alive()) != 0ull && a0 < b0) {
         // this lane's entry of the 64 at hand (ra, rb: its record) and the next 64 entries' ids
-        auto load_id = [&](uint32_t b) -> uint32_t { return b + lane < b0 ? vals[b + lane] : 0u; };
-        auto load_half = [&](uint32_t b, uint32_t g, int part) -> float4 {
-          return b + lane < b0 ? reinterpret_cast<const float4*>(rec + kRecFloats * (e0 + g))[part]
-                               : make_float4(0.f, 0.f, 0.f, 0.f);
+        // (every lane loads, past the last entry that entry again: no wait at a branch's end)
+        auto load_id = [&](uint32_t b) -> uint32_t { return vals[min(b + lane, b0 - 1u)]; };
+        auto load_half = [&](uint32_t g, int part) -> float4 {
+          return reinterpret_cast<const float4*>(rec + kRecFloats * (e0 + g))[part];
         };
         uint32_t gid = load_id(a0);
-        float4 ra = load_half(a0, gid, 0), rb = load_half(a0, gid, 1);
-        uint32_t gnext = a0 + 64 < b0 ? load_id(a0 + 64) : 0u;
+        uint32_t gnext = load_id(a0 + 64);
+        float4 ra = load_half(gid, 0), rb = load_half(gid, 1);
         int qn = 0;   // queued Gaussians
         for (uint32_t b = a0;; b += 64) {
           const LRec r = local_rec(ra, rb, ox, oy);
@@ -778,12 +783,10 @@ __global__ __launch_bounds__(256, NS <= 28 ? 3 : 2) void k_render_fwd_split(
           }
           qn += __builtin_popcountll(m);
           const bool more = b + 64 < b0;   // else the remainder is composited too
-          if (more) {
-            gid = gnext;
-            ra = load_half(b + 64, gid, 0);
-            rb = load_half(b + 64, gid, 1);
-            gnext = b + 128 < b0 ? load_id(b + 128) : 0u;
-          }
+          gid = gnext;
+          ra = load_half(gid, 0);
+          rb = load_half(gid, 1);
+          gnext = load_id(b + 128);
           // a last batch's missing entries: a negative opacity, so no alpha reaches the threshold
           if (!more) reinterpret_cast<float4*>(Q + 8 * qn)[lane] = make_float4(0.f, (lane & 1) ? -1.f : 0.f, 0.f, 0.f);
           wave_sync();
@@ -1213,7 +1216,7 @@ struct BShape {
   static constexpr int kWave = kQ + kW + kF + kA > kStage ? kQ + kW + kF + kA : kStage;
 };
 
-template <int NS, bool EMB>
+template <int NS, int MODE>
 __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
     gs_config cfg, FeatSrc src, const float* __restrict__ rec, int64_t n, const gs_item* __restrict__ items, int n_items,
     const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, const float* __restrict__ Tfin,
@@ -1221,6 +1224,7 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
     uint32_t* __restrict__ ctl, const uint32_t* __restrict__ tile_lmax, const float* __restrict__ segP,
     const float* __restrict__ segGC, FState fs) {
   using B = BShape<NS>;
+  constexpr bool EMB = MODE == kEmbVec;
   constexpr int KP = SShape<NS>::KP, CB = SShape<NS>::CB, FROW = B::FROW, AROW = B::AROW;
   constexpr bool kGF3 = B::kGF3;
   constexpr int GG = NS > 28 ? 2 : 4;         // Gaussians per geometric-term reduction (register budget)
@@ -1363,32 +1367,8 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
       const uint32_t gc = __float_as_uint(R[8 * (lane >> 2) + 7]);
       const float* a0p = (lane & 3) < 3 ? src.rgb + 3 * ((int64_t)gc + foff) + (lane & 3) : src.depth + (e0 + gc);
       f0 = *a0p;
-      if constexpr (EMB) {
-        const uint16_t* a = src.emb + 16 * (int64_t)gc + 4 * (lane & 3);
-        if (src.vec) fe = *reinterpret_cast<const uint2*>(a);
-        else fe = make_uint2((uint32_t)a[0] | ((uint32_t)a[1] << 16), (uint32_t)a[2] | ((uint32_t)a[3] << 16));
-      } else if (src.n_sem > 0) {
-        const int k = 4 * (lane % QL) < src.n_sem ? 4 * (lane % QL) : 0;
-        const float* a = src.sem + (int64_t)src.n_sem * foff + k;
-        if (src.vec) {
-#pragma unroll
-          for (int p = 0; p < NP; ++p) {
-            const float4 x = *reinterpret_cast<const float4*>(a + (int64_t)src.n_sem * gq[p]);
-            f[4 * p] = x.x;
-            f[4 * p + 1] = x.y;
-            f[4 * p + 2] = x.z;
-            f[4 * p + 3] = x.w;
-          }
-        } else {
-#pragma unroll
-          for (int p = 0; p < NP; ++p)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int o = k + i < src.n_sem ? i : 0;
-              f[4 * p + i] = a[(int64_t)src.n_sem * gq[p] + o];
-            }
-        }
-      }
+      if constexpr (EMB) fe = *reinterpret_cast<const uint2*>(src.emb + 16 * (uint64_t)gc + 4 * (lane & 3));
+      else load_quads<MODE>(src, gq, foff, 4 * (lane % QL), f);
     };
     // the gathered features to their rows: three bfloat16 parts of each value, or the value. (A
     // part group's missing Gaussians have a row too, of whatever Gaussian 0 has; no sum uses it.)
@@ -1428,11 +1408,12 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
         *reinterpret_cast<uint2*>(row + 32) = z;
       } else {
         const int k = 4 * (lane % QL);
+        const uint32_t m = k < src.n_sem ? ~0u : 0u;   // (see Feats::commit)
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
           float x[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) x[i] = k + i < src.n_sem ? f[4 * p + i] : 0.0f;
+          for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(__float_as_uint(f[4 * p + i]) & m);
           if (k < NS) put4(p * (64 / QL) + lane / QL, 4 + k, x);
         }
       }
@@ -1488,14 +1469,14 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
     };
 
     // this lane's entry of the 64 at hand (ra, rb: its record), list position hi - 1 - lane
-    auto load_id = [&](int hi) -> uint32_t { return hi - 1 - lane >= a0 ? vals[c.start + hi - 1 - lane] : 0u; };
-    auto load_half = [&](int hi, uint32_t g, int part) -> float4 {
-      return hi - 1 - lane >= a0 ? reinterpret_cast<const float4*>(rec + kRecFloats * (e0 + g))[part]
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+    // (every lane loads, past the first entry that entry again: no wait at a branch's end)
+    auto load_id = [&](int hi) -> uint32_t { return vals[c.start + max(hi - 1 - lane, a0)]; };
+    auto load_half = [&](uint32_t g, int part) -> float4 {
+      return reinterpret_cast<const float4*>(rec + kRecFloats * (e0 + g))[part];
     };
     uint32_t gid = load_id(b0);
-    float4 ra = load_half(b0, gid, 0), rb = load_half(b0, gid, 1);
     uint32_t gnext = load_id(b0 - 64);
+    float4 ra = load_half(gid, 0), rb = load_half(gid, 1);
     int tail = 0, done = 0, issued = 0;   // entries in the ring so far; groups worked on, gathered
     for (int hi = b0;; hi -= 64) {
       {
@@ -1511,12 +1492,11 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
         tail += __builtin_popcountll(m);
       }
       const bool fin = hi - 64 <= a0;
-      if (!fin) {
-        gid = gnext;
-        ra = load_half(hi - 64, gid, 0);
-        rb = load_half(hi - 64, gid, 1);
-        gnext = load_id(hi - 128);
-      } else if (lane < 2 * (-tail & (kGrp - 1))) {
+      gid = gnext;
+      ra = load_half(gid, 0);
+      rb = load_half(gid, 1);
+      gnext = load_id(hi - 128);
+      if (fin && lane < 2 * (-tail & (kGrp - 1))) {
         // a part group's missing entries: a negative opacity, so no alpha reaches the threshold
         reinterpret_cast<float4*>(Q + 8 * ((tail + (lane >> 1)) & (kRing - 1)))[lane & 1] =
             make_float4(0.f, (lane & 1) ? -1.f : 0.f, 0.f, 0.f);
@@ -1754,13 +1734,13 @@ FLayout state_of(const gs_images& im, int n_tiles, int K, int seg) {
   return w;
 }
 
-template <int NS, bool EMB>
+template <int NS, int MODE>
 int launch_fwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items, int n_items,
                  int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& out, hipStream_t s) {
   const FLayout w = state_of(out, n_tiles, 4 + cfg.n_sem, seg_len(cfg));
-  const FeatSrc src{g.rgb, g.sem, p.depth, g.emb, cfg.n_sem, sem_vec(g, cfg.n_sem)};
+  const FeatSrc src{g.rgb, g.sem, p.depth, g.emb, cfg.n_sem};
   if (!w.fs.tcnt) {
-    hipLaunchKernelGGL((k_render_fwd_split<NS, false, EMB>), dim3(n_tiles), dim3(256), 0, s, cfg, src, p.rec, g.n, items,
+    hipLaunchKernelGGL((k_render_fwd_split<NS, false, MODE>), dim3(n_tiles), dim3(256), 0, s, cfg, src, p.rec, g.n, items,
                        n_items, vals, ranges, out.color, out.T, out.n_contrib, nullptr, nullptr, w.fs);
     return launch_status();
   }
@@ -1773,12 +1753,12 @@ int launch_fwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   hipLaunchKernelGGL(k_seg_list, dim3(tb), dim3(256), 0, s, w.cnt, w.base, w.total, n_tiles, cfg.tile_order,
                      w.max_segs, w.work, w.ctl, w.fs.tcnt, w.fs.tbase);
   const int grid_t = resident_blocks(k_fwd_trans, 256, 0);
-  const int grid_f = resident_blocks(k_render_fwd_split<NS, true, EMB>, 256, 0);
+  const int grid_f = resident_blocks(k_render_fwd_split<NS, true, MODE>, 256, 0);
   if (!grid_t || !grid_f) return GS_ERR_HIP;
   if (cfg.fwd_chunk > 0)
     hipLaunchKernelGGL(k_fwd_trans, dim3(grid_t), dim3(256), 0, s, cfg, p.rec, g.n, items, n_items, vals, ranges,
                        w.work, w.ctl, w.fs.P);
-  hipLaunchKernelGGL((k_render_fwd_split<NS, true, EMB>), dim3(grid_f), dim3(256), 0, s, cfg, src, p.rec, g.n, items, n_items,
+  hipLaunchKernelGGL((k_render_fwd_split<NS, true, MODE>), dim3(grid_f), dim3(256), 0, s, cfg, src, p.rec, g.n, items, n_items,
                      vals, ranges, out.color, out.T, out.n_contrib, w.work, w.ctl, w.fs);
   if (cfg.fwd_chunk > 0)
     hipLaunchKernelGGL(k_fwd_combine<NS>, dim3(n_tiles), dim3(256), 0, s, items, n_items, ranges, 4 + cfg.n_sem,
@@ -1786,7 +1766,7 @@ int launch_fwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   return launch_status();
 }
 
-template <int NS, bool EMB>
+template <int NS, int MODE>
 int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items, int n_items,
                  int n_tiles, const uint32_t* vals, const uint32_t* ranges, const gs_images& fwd,
                  const gs_images& gin, double* g2d, const gs_grads& gr, void* seg_ws, int64_t cap, hipStream_t s) {
@@ -1801,7 +1781,7 @@ int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   if (st) return st;
   hipLaunchKernelGGL(k_seg_list, dim3((unsigned)ceil_div(n_tiles, 256)), dim3(256), 0, s, w.cnt, w.base, w.total,
                      n_tiles, cfg.tile_order, w.max_segs, w.work, w.ctl, nullptr, nullptr);
-  const int grid_main = resident_blocks(k_render_bwd_main<NS, EMB>, 256, 0);
+  const int grid_main = resident_blocks(k_render_bwd_main<NS, MODE>, 256, 0);
   if (!grid_main) return GS_ERR_HIP;
   if (!fs.tcnt) {
     const int grid_sum = resident_blocks(k_seg_summary<NS>, 256, 0);
@@ -1810,8 +1790,8 @@ int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
                        p.depth, g.n, items, n_items, vals, ranges, fwd.n_contrib, gin.color, w.work, w.ctl, w.lmax, w.P,
                        w.GC);
   }
-  const FeatSrc src{g.rgb, g.sem, p.depth, g.emb, cfg.n_sem, sem_vec(g, cfg.n_sem)};
-  hipLaunchKernelGGL((k_render_bwd_main<NS, EMB>), dim3(grid_main), dim3(256), 0, s, cfg, src, p.rec, g.n, items, n_items,
+  const FeatSrc src{g.rgb, g.sem, p.depth, g.emb, cfg.n_sem};
+  hipLaunchKernelGGL((k_render_bwd_main<NS, MODE>), dim3(grid_main), dim3(256), 0, s, cfg, src, p.rec, g.n, items, n_items,
                      vals, ranges, fwd.T, fwd.n_contrib, gin.color, GradDst{gr.rgb, gr.sem, g2d}, w.work, w.ctl, w.lmax,
                      w.P, w.GC, fs);
   return launch_status();
@@ -1838,10 +1818,11 @@ int64_t render_seg_capacity(int n_tiles, int seg, size_t bytes) {
 int launch_render_fwd_split(const gs_config& cfg, const gs_gaussians& g, const gs_projected& p, const gs_item* items,
                             int n_items, int n_tiles, const uint32_t* vals, const uint32_t* ranges,
                             const gs_images& out, hipStream_t s) {
-  const int ns = cfg.n_sem;
-  if (g.emb) return launch_fwd_s<28, true>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
-  if (ns <= 28) return launch_fwd_s<28, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
-  if (ns <= 60) return launch_fwd_s<60, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s);
+  const auto launch = [&](auto f) { return f(cfg, g, p, items, n_items, n_tiles, vals, ranges, out, s); };
+  const FeatMode m = feat_mode(g, cfg.n_sem);
+  if (cfg.n_sem <= 28)
+    return launch(m == kEmbVec ? launch_fwd_s<28, kEmbVec> : m == kRowVec ? launch_fwd_s<28, kRowVec> : launch_fwd_s<28, kValues>);
+  if (cfg.n_sem <= 60) return launch(m == kRowVec ? launch_fwd_s<60, kRowVec> : launch_fwd_s<60, kValues>);
   return GS_ERR_UNSUPPORTED;
 }
 
@@ -1849,14 +1830,14 @@ int launch_render_bwd_split(const gs_config& cfg, const gs_gaussians& g, const g
                             int n_items, int n_tiles, const uint32_t* vals, const uint32_t* ranges,
                             const gs_images& fwd, const gs_images& gin, double* g2d, const gs_grads& gr, void* seg_ws,
                             int64_t cap, hipStream_t s) {
-  const int ns = cfg.n_sem;
   if (cap < 0) return GS_ERR_WORKSPACE;
-  if (g.emb)
-    return launch_bwd_s<28, true>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
-  if (ns <= 28)
-    return launch_bwd_s<28, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
-  if (ns <= 60)
-    return launch_bwd_s<60, false>(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
+  const auto launch = [&](auto f) {
+    return f(cfg, g, p, items, n_items, n_tiles, vals, ranges, fwd, gin, g2d, gr, seg_ws, cap, s);
+  };
+  const FeatMode m = feat_mode(g, cfg.n_sem);
+  if (cfg.n_sem <= 28)
+    return launch(m == kEmbVec ? launch_bwd_s<28, kEmbVec> : m == kRowVec ? launch_bwd_s<28, kRowVec> : launch_bwd_s<28, kValues>);
+  if (cfg.n_sem <= 60) return launch(m == kRowVec ? launch_bwd_s<60, kRowVec> : launch_bwd_s<60, kValues>);
   return GS_ERR_UNSUPPORTED;
 }
 
