@@ -134,6 +134,13 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders a wave's LDS accesses between its lanes (a wave runs in step: no barrier is needed).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // One tile of one item, as a render block sees it (tile width 1 << tws, height 256 >> tws).
 struct Ctx {
   int item, view, tx, ty, tiles_x, tiles_y, tws;

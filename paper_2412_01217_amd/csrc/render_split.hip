@@ -196,12 +196,6 @@ __device__ __forceinline__ v4f mma6(const v8bf (&a)[3], const v8bf (&b)[3], v4f 
 }
 __device__ __forceinline__ v4f zero4() { return (v4f){0.0f, 0.0f, 0.0f, 0.0f}; }
 
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Batch staging, double-buffered through registers: thread t stages Gaussian q = t / 8
 // of the batch, channels [(t % 8) CPT, +CPT) of its features and, for t % 8 < 2, half of
 // its 8-float record. The batch's Gaussian ids are loaded a batch earlier than its data
