@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace gs {
 namespace {
@@ -575,17 +576,51 @@ __global__ void k_full_keys(const uint32_t* __restrict__ tkeys, const uint32_t* 
 // then every tile's list sorted by its (depth bits, Gaussian index) keys in LDS.
 //
 // Block b of the two pair kernels takes the same entries. The first counts the block's
-// duplicates per tile with LDS atomics and writes the counts tile-major; their exclusive scan
-// gives every (tile, block) its first slot, tile t's list starting at the slot of (t, 0). The
-// second kernel hands each duplicate the next slot of its (tile, block) from an LDS counter,
-// in whatever order the LDS atomics serve the lanes, and stores its key there. The per-tile
-// sort then puts every list in (depth, index) order: the key is unique within a tile (a
-// Gaussian meets a tile of its item once), so the order in which slots were taken does not
-// show in the result, which is the (tile, depth, index) order of the radix path exactly.
+// duplicates per tile with LDS atomics, then adds its counts to the tiles' totals: what the
+// atomic returns is the block's first slot within each tile's list (the blocks come in any
+// order). The second kernel turns the totals into the lists' starts (every block for itself,
+// in LDS) and hands each duplicate the next slot of its (tile, block) from an LDS counter, in
+// whatever order the LDS atomics serve the lanes, and stores its key there. The per-tile sort
+// then puts every list in (depth, index) order: the key is unique within a tile (a Gaussian
+// meets a tile of its item once), so the order in which slots were taken does not show in the
+// result, which is the (tile, depth, index) order of the radix path exactly.
+// A block's row of slots is written and read along the tiles, and 16 neighbouring totals are
+// one atomic request, so a block costs little and every compute unit gets one. (Counts written
+// tile by tile for a scan over (tile, block) cost a memory request each, which held the pair
+// kernels to some 120 blocks. 1M entries, 8160 tiles, 3.5M duplicates: counting 57 -> 23 us,
+// scattering 73 -> 61 (half of it is the stores of single keys), the scan's 16 us gone for a 5 us
+// clearing; 600k entries, 4270 tiles, 0.87M duplicates: 58 -> 36 us in all. A search for each
+// pair's entry, in place of the bit masks below, made the first 39 and 69.)
 // ---------------------------------------------------------------------------
 constexpr int kBkThreads = 1024;
 constexpr int kBkWaves = kBkThreads / 64;
 constexpr int kBkMaxTiles = 12288;   // tile counters a block keeps in LDS (48 KB)
+
+// Number of m's bits below the lane.
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// OR over the wave of 64-bit words given in halves.
+__device__ __forceinline__ uint32_t wave_or32(uint32_t v) {
+  auto mov = [](uint32_t x, auto ctrl) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl(), 0xF, 0xF, true);
+  };
+  v |= mov(v, std::integral_constant<int, 0xB1>());    // within rows of 16 lanes
+  v |= mov(v, std::integral_constant<int, 0x4E>());
+  v |= mov(v, std::integral_constant<int, 0x141>());
+  v |= mov(v, std::integral_constant<int, 0x140>());
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 0) | (uint32_t)__builtin_amdgcn_readlane((int)v, 16) |
+         (uint32_t)__builtin_amdgcn_readlane((int)v, 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+}
+__device__ __forceinline__ uint64_t wave_or(uint32_t lo, uint32_t hi) {
+  return ((uint64_t)wave_or32(hi) << 32) | wave_or32(lo);
+}
+
+__global__ __launch_bounds__(256) void k_zero_u32(uint32_t* __restrict__ p, int n) {
+  const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (i < n) p[i] = 0u;
+}
 
 template <bool COUNT>
 __global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, const int32_t* __restrict__ radius,
@@ -593,23 +628,60 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, cons
                                                              const float* __restrict__ rec,
                                                              const gs_item* __restrict__ items, int64_t E, int64_t n,
                                                              int n_tiles, int nblk, uint32_t* __restrict__ hist,
-                                                             int64_t cap, uint64_t* __restrict__ tmp,
-                                                             const uint64_t* __restrict__ dtotal,
+                                                             uint32_t* __restrict__ total,
+                                                             uint32_t* __restrict__ offs, int64_t cap,
+                                                             uint64_t* __restrict__ tmp,
+                                                             uint64_t* __restrict__ dtotal,
                                                              int64_t* __restrict__ n_dup_out,
                                                              int32_t* __restrict__ status) {
   __shared__ uint32_t s_cnt[kBkMaxTiles];      // per tile: the block's count, or its next slot
-  __shared__ uint32_t s_pre[kBkWaves][64];     // inclusive prefix of the wave's tile counts
+  __shared__ uint32_t s_first[kBkWaves][64];   // the entry's first pair among the wave's
   __shared__ int4 s_rect[kBkWaves][64];        // x0, width, tiles_x, id of tile (0, y0) of the item
   __shared__ uint64_t s_key[kBkWaves][64];     // the entry's key within its tiles (scatter)
   const int b = blockIdx.x;
-  for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) s_cnt[t] = COUNT ? 0u : hist[(int64_t)t * nblk + b];
-  if (!COUNT && b == 0 && threadIdx.x == 0) {
-    const uint64_t D = *dtotal;
-    if (n_dup_out) *n_dup_out = (int64_t)D;
-    if (status) *status = D > (uint64_t)cap ? GS_ERR_CAPACITY : GS_OK;
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t* const row = hist + (int64_t)b * n_tiles;
+  for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) s_cnt[t] = COUNT ? 0u : total[t];
+  __syncthreads();
+  if (!COUNT) {
+    // exclusive scan of the totals; thread i has the tiles [i per, (i + 1) per), an odd number so
+    // that neighbouring threads meet different LDS banks
+    const int per = (int)((uint32_t)(n_tiles + kBkThreads - 1) / kBkThreads) | 1;
+    const int t0 = min(n_tiles, (int)threadIdx.x * per), t1 = min(n_tiles, t0 + per);
+    uint64_t sum = 0;
+    for (int t = t0; t < t1; ++t) sum += s_cnt[t];
+    uint64_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t v = __shfl_up(inc, off, 64);
+      if (lane >= off) inc += v;
+    }
+    if (lane == 63) s_key[0][wid] = inc;
+    __syncthreads();
+    uint64_t at = inc - sum, D = 0;
+    for (int k = 0; k < kBkWaves; ++k) {
+      const uint64_t v = s_key[0][k];
+      at += k < wid ? v : 0;
+      D += v;
+    }
+    for (int t = t0; t < t1; ++t) {
+      const uint32_t c = s_cnt[t];
+      s_cnt[t] = (uint32_t)at;
+      at += c;
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) {
+      const uint32_t first = s_cnt[t];
+      if (b == 0) offs[t] = first;
+      s_cnt[t] = first + row[t];
+    }
+    if (b == 0 && threadIdx.x == 0) {
+      *dtotal = D;
+      if (n_dup_out) *n_dup_out = (int64_t)D;
+      if (status) *status = D > (uint64_t)cap ? GS_ERR_CAPACITY : GS_OK;
+    }
+    __syncthreads();
+  }
   const int64_t n_groups = (E + 63) >> 6, stride = (int64_t)nblk * kBkWaves;
   // groups of 64 consecutive entries, the block's waves on consecutive groups in each round.
   // Loads run ahead of use: a group's records (and depths) are loaded one group ahead, from
@@ -653,96 +725,156 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, cons
       const uint32_t t = __shfl_up(inc, off, 64);
       if (lane >= off) inc += t;
     }
-    // (the previous group's reads of the wave's slots are done: a wave's LDS operations
-    // complete in order)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    s_pre[wid][lane] = inc;
-    s_rect[wid][lane] = rc;
-    if (!COUNT) s_key[wid][lane] = key;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint32_t total = __shfl(inc, 63, 64);
-    for (uint32_t k = lane; k < total; k += 64) {
-      int lo = 0, hi = 63;   // first entry whose inclusive prefix exceeds k
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (s_pre[wid][mid] > k) hi = mid; else lo = mid + 1;
+    // the entries that have tiles, packed, go to LDS (the previous group's reads of the wave's
+    // slots are done: a wave's LDS operations complete in order)
+    const uint32_t first = inc - c;
+    const uint64_t some = __ballot(c > 0);
+    wave_sync();
+    if (c > 0) {
+      const int at = lanes_below(some);
+      s_first[wid][at] = first;
+      s_rect[wid][at] = rc;
+      if (!COUNT) s_key[wid][at] = key;
+    }
+    wave_sync();
+    // 64 pairs at a time. Bit i of m: an entry's pairs begin at k0 + 1 + i; so the lane's pair is
+    // of the entry that comes (m's bits below the lane) after the one at k0, with no search.
+    const uint32_t pairs = __shfl(inc, 63, 64);
+    for (uint32_t k0 = 0; k0 < pairs; k0 += 64) {
+      const uint32_t d = first - k0 - 1;
+      const uint64_t m = wave_or(c > 0 && d < 32 ? 1u << d : 0u, c > 0 && d - 32 < 32 ? 1u << (d - 32) : 0u);
+      const int at = __popcll(__ballot(c > 0 && first <= k0)) - 1 + lanes_below(m);
+      const uint32_t k = k0 + lane;
+      if (k < pairs) {
+        const uint32_t i = k - s_first[wid][at];
+        const int4 rr = s_rect[wid][at];
+        // (exact: i and the width are below 2^14)
+        const int row = (int)(((float)i + 0.5f) * __builtin_amdgcn_rcpf((float)rr.y));
+        const int tile = rr.w + row * rr.z + rr.x + ((int)i - row * rr.y);
+        const uint32_t pos = atomicAdd(&s_cnt[tile], 1u);
+        if (!COUNT && (int64_t)pos < cap) tmp[pos] = s_key[wid][at];
       }
-      const uint32_t m = k - (lo > 0 ? s_pre[wid][lo - 1] : 0u);
-      const int4 rr = s_rect[wid][lo];
-      const int row = (int)(m / (uint32_t)rr.y), col = (int)m - row * rr.y;
-      const int tile = rr.w + row * rr.z + rr.x + col;
-      const uint32_t pos = atomicAdd(&s_cnt[tile], 1u);
-      if (!COUNT && (int64_t)pos < cap) tmp[pos] = s_key[wid][lo];
     }
   }
   if (COUNT) {
     __syncthreads();
-    for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) hist[(int64_t)t * nblk + b] = s_cnt[t];
+    // four atomics in flight a thread; the blocks start at different tiles
+    const int rounds = (n_tiles + 4 * kBkThreads - 1) / (4 * kBkThreads);
+    for (int i = 0; i < rounds; ++i) {
+      const int t0 = (i + b) % rounds * 4 * kBkThreads + (int)threadIdx.x;
+      uint32_t at[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = t0 + u * kBkThreads;
+        if (t < n_tiles) at[u] = atomicAdd(&total[t], s_cnt[t]);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (t0 + u * kBkThreads < n_tiles) row[t0 + u * kBkThreads] = at[u];
+    }
   }
 }
 
-// Tile t's list: [offs[t * nblk], offs[(t + 1) * nblk]) (the duplicate total past the last
-// tile), clamped to the capacity; a negative length (wrapped 32-bit slots past the capacity)
+// Tile t's list: [offs[t], offs[t + 1]) (the duplicate total past the last tile), clamped to the capacity; a negative length (wrapped 32-bit slots past the capacity)
 // reads as empty.
-__device__ __forceinline__ void tile_span(const uint32_t* offs, int nblk, int n_tiles, const uint64_t* dtotal,
+__device__ __forceinline__ void tile_span(const uint32_t* offs, int n_tiles, const uint64_t* dtotal,
                                           int64_t cap, int t, int64_t& start, int64_t& len) {
-  const int64_t a = offs[(int64_t)t * nblk];
-  const int64_t b = t + 1 < n_tiles ? (int64_t)offs[(int64_t)(t + 1) * nblk] : (int64_t)*dtotal;
+  const int64_t a = offs[t];
+  const int64_t b = t + 1 < n_tiles ? (int64_t)offs[t + 1] : (int64_t)*dtotal;
   start = min(a, cap);
   len = min(b, cap) - start;
 }
 
 // Per-tile sort. The list is cut into sub-lists of 256 keys; a wave owns whole sub-lists
 // (sub-list c: wave c mod W), which it sorts in registers with Batcher's bitonic network,
-// four keys per lane (lane l ends with sorted positions 4 l .. 4 l + 3; steps between lanes
-// exchange keys by shuffles). A list of one sub-list is then written out directly. Otherwise
-// the sorted sub-lists go to LDS, and the rank of the key at sorted position j in the whole
-// list is j plus, for every other sub-list, the number of its keys below the key (a binary
-// search). Lists of up to CH keys; T threads (W = T / 64).
+// four keys per lane (lane l ends with sorted positions 4 l .. 4 l + 3). Lists of more are
+// merged two by two by the same network: a merge compares position i with its mirror, then
+// positions half a list, a quarter, ... apart. Steps between sub-lists exchange all four keys of
+// a lane through LDS, the last eight stay within the wave, whose lanes exchange by DPP and
+// permlane swaps: no step depends on the keys, LDS is read in lane order, and the result lies in
+// place. (A binary search of every key in every other sub-list, with the 256-sorts' exchanges by
+// shuffles, kept the LDS pipe busy and its steps waited for each other: 3.5M keys in 8160 lists
+// 127 us, now 57; 0.87M in 4270 lists 59, now 40; a list of 2115 alone 31, now 17. Merges by
+// searches in the sibling only: 68, 49 and 22.)
+// Lists of up to CH keys; T threads (W = T / 64).
 constexpr int kSub = 256;
 
-__device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int m) {
-  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
-  const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
-  return ((uint64_t)hi << 32) | lo;
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+// The value of lane ^ X, X = 1, 2, 4 or 8, without the LDS pipe.
+template <int X>
+__device__ __forceinline__ uint32_t lane_xor32(uint32_t v) {
+  if constexpr (X == 1) return dpp_mov<0xB1>(v);
+  else if constexpr (X == 2) return dpp_mov<0x4E>(v);
+  else if constexpr (X == 4) return dpp_mov<0x1B>(dpp_mov<0x141>(v));   // lane ^ 7 ^ 3
+  else return dpp_mov<0x128>(v);
+}
+template <int X>
+__device__ __forceinline__ uint64_t lane_xor64(uint64_t v) {
+  return ((uint64_t)lane_xor32<X>((uint32_t)(v >> 32)) << 32) | lane_xor32<X>((uint32_t)v);
+}
+// Lanes l and l ^ X (X = 16 or 32) of x and y: afterwards the lane with bit X clear holds both
+// lanes' x, the other one both lanes' y, x from the lane with the bit clear and y from the other.
+// A second call undoes it.
+template <int X>
+__device__ __forceinline__ void lane_swap64(uint64_t& x, uint64_t& y) {
+  uint32_t a[2] = {(uint32_t)x, (uint32_t)(x >> 32)}, b[2] = {(uint32_t)y, (uint32_t)(y >> 32)};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if constexpr (X == 16) {
+      const auto t = __builtin_amdgcn_permlane16_swap(a[i], b[i], false, false);
+      a[i] = t[0];
+      b[i] = t[1];
+    } else {
+      const auto t = __builtin_amdgcn_permlane32_swap(a[i], b[i], false, false);
+      a[i] = t[0];
+      b[i] = t[1];
+    }
+  }
+  x = ((uint64_t)a[1] << 32) | a[0];
+  y = ((uint64_t)b[1] << 32) | b[0];
+}
+
+// (x, y) = (smaller, larger), or the other way round.
+__device__ __forceinline__ void order2(uint64_t& a, uint64_t& b, bool up) {
+  const uint64_t x = a, y = b;
+  const bool sw = (y < x) == up;   // (keys differ, or their order does not matter)
+  a = sw ? y : x;
+  b = sw ? x : y;
+}
+
+// Stage (k, j) of the network below.
+template <int K, int J>
+__device__ __forceinline__ void sort_stage(uint64_t (&v)[4], int lane) {
+  if constexpr (J >= 64) {
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+      lane_swap64<J / 4>(v[r], v[r + 1]);
+      order2(v[r], v[r + 1], ((4 * lane) & K) == 0);
+      lane_swap64<J / 4>(v[r], v[r + 1]);
+    }
+  } else if constexpr (J >= 4) {
+    const bool want_min = (((4 * lane) & J) == 0) == (((4 * lane) & K) == 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint64_t o = lane_xor64<J / 4>(v[r]);   // position i ^ j: lane ^ (j / 4), same r
+      v[r] = (v[r] < o) == want_min ? v[r] : o;
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)   // each in-lane pair once, at its lower position
+      if ((r ^ J) > r) order2(v[r], v[r ^ J], ((4 * lane + r) & K) == 0);
+  }
+  if constexpr (J > 1) sort_stage<K, J / 2>(v, lane);
+  else if constexpr (K < 256) sort_stage<2 * K, K>(v, lane);
 }
 
 // Ascending bitonic sort of the wave's 256 keys, lane l holding positions 4 l + r in v[r].
 // Stage (k, j) pairs position i with i ^ j; the pair's lower position takes the smaller key
 // when i & k is 0 (an ascending run), the larger one otherwise.
-__device__ __forceinline__ void wave_sort256(uint64_t (&v)[4]) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int k = 2; k <= 256; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j >= 1; j >>= 1) {
-      if (j >= 4) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 4 * lane + r;
-          const uint64_t o = shfl_xor64(v[r], j >> 2);   // position i ^ j: lane ^ (j / 4), same r
-          const bool lt = v[r] < o;
-          const bool want_min = ((i & j) == 0) == ((i & k) == 0);
-          v[r] = (lt == want_min) ? v[r] : o;
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int p = r ^ j;
-          if (p < r) continue;   // each in-lane pair once, at its lower position
-          const bool up = ((4 * lane + r) & k) == 0;
-          const uint64_t x = v[r], y = v[p];
-          const bool sw = up ? (y < x) : (x < y);
-          v[r] = sw ? y : x;
-          v[p] = sw ? x : y;
-        }
-      }
-    }
-  }
-}
+__device__ __forceinline__ void wave_sort256(uint64_t (&v)[4]) { sort_stage<2, 1>(v, threadIdx.x & 63); }
 
 template <int T, int CH>
 __device__ __forceinline__ void sort_tile(uint64_t* s, const uint64_t* __restrict__ g, int L, int t, int64_t start,
@@ -751,96 +883,64 @@ __device__ __forceinline__ void sort_tile(uint64_t* s, const uint64_t* __restric
                                           uint64_t* __restrict__ keys) {
   constexpr int W = T / 64, NS = CH / (kSub * W), R = kSub / 64;
   static_assert(R == 4, "four keys per lane");
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nsub = (L + kSub - 1) / kSub;
   uint64_t k[NS][R];
 #pragma unroll
   for (int q = 0; q < NS; ++q) {
-    const int c0 = (wid + q * W) * kSub, cl = min(kSub, L - c0);   // cl <= 0: no sub-list
+    const int c0 = (wid + q * W) * kSub;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int j = lane * R + r;
-      k[q][r] = j < cl ? g[c0 + j] : ~0ull;   // past the list: +inf, sorted to the end
+      const int j = c0 + 64 * r + lane;   // (in any order)
+      k[q][r] = j < L ? g[j] : ~0ull;     // past the list: +inf, sorted to the end
     }
-    if (cl > 0) wave_sort256(k[q]);   // uniform over the wave
+    if (c0 < L) wave_sort256(k[q]);       // uniform over the wave
   }
-  const int64_t item = keys ? item_of_tile(items, n_items, t) : 0;
-  if (nsub == 1) {
-    if (wid == 0) {
+  for (int half = 1; half < nsub; half <<= 1) {   // merge lists of `half` sub-lists
+    // one exchange with sub-list c ^ m, mirrored for m = 2 half - 1. A list with no sibling stays.
+    auto exchange = [&](int m, bool mirror) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int j = lane * R + r;
-        if (j >= L) continue;
-        const uint32_t gi = (uint32_t)k[0][r];
-        vals[start + j] = gi;
-        if (keys) {
-          const uint32_t db = gi < (uint64_t)n ? __float_as_uint(depth[item * n + gi]) : 0u;
-          keys[start + j] = ((uint64_t)(uint32_t)t << 32) | (uint64_t)db;
+      for (int q = 0; q < NS; ++q) {
+        const int c = wid + q * W;
+        if ((c & ~(2 * half - 1)) + half < nsub) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) s[(R * c + r) * 64 + lane] = k[q][r];
         }
       }
-    }
-    return;
-  }
+      __syncthreads();
 #pragma unroll
-  for (int q = 0; q < NS; ++q) {
-    const int c0 = (wid + q * W) * kSub, cl = min(kSub, L - c0);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int j = lane * R + r;
-      if (j < cl) s[c0 + j] = k[q][r];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NS; ++q) {
-    const int own = wid + q * W, c0 = own * kSub, cl = min(kSub, L - c0);
-    if (cl <= 0) continue;   // uniform over the wave
-    // lane l holds positions 4 l .. 4 l + 3 of the sorted sub-list: neighbouring lanes search
-    // for neighbouring keys, so their LDS reads mostly meet at the same addresses
-    uint32_t rank[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) rank[r] = (uint32_t)(lane * R + r);
-    // the other sub-lists four at a time, the 4 x R searches in lockstep (branch-free lower
-    // bound by binary lifting: pos grows by each power of two while the key at pos + step - 1
-    // is below the searched key), so that their LDS reads overlap
-    for (int cg = 0; cg < nsub; cg += 4) {
-      int nn[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = cg + u;
-        nn[u] = (c < nsub && c != own) ? min(kSub, L - c * kSub) : 0;
-      }
-      int pos[4][R];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int r = 0; r < R; ++r) pos[u][r] = 0;
-#pragma unroll
-      for (int step = kSub; step >= 1; step >>= 1) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
+      for (int q = 0; q < NS; ++q) {
+        const int c = wid + q * W, p = c ^ m;
+        if ((c & ~(2 * half - 1)) + half < nsub) {
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            const int p = pos[u][r] + step;
-            if (p <= nn[u] && s[(cg + u) * kSub + p - 1] < k[q][r]) pos[u][r] = p;
+            const uint64_t o = mirror ? s[(R * p + R - 1 - r) * 64 + 63 - lane] : s[(R * p + r) * 64 + lane];
+            k[q][r] = (k[q][r] < o) == (c < p) ? k[q][r] : o;
           }
+        }
       }
+      __syncthreads();
+    };
+    exchange(2 * half - 1, true);
+    for (int h = half >> 1; h >= 1; h >>= 1) exchange(h, false);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+    for (int q = 0; q < NS; ++q)
+      if (((wid + q * W) & ~(2 * half - 1)) + half < nsub) sort_stage<256, 128>(k[q], lane);
+  }
+  const int64_t item = keys ? item_of_tile(items, n_items, t) : 0;
 #pragma unroll
-        for (int r = 0; r < R; ++r) rank[r] += (uint32_t)pos[u][r];
-    }
+  for (int q = 0; q < NS; ++q)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      if (lane * R + r >= cl) continue;
+      const int j = (wid + q * W) * kSub + lane * R + r;
+      if (j >= L) continue;
       const uint32_t gi = (uint32_t)k[q][r];
-      vals[start + rank[r]] = gi;
+      vals[start + j] = gi;
       if (keys) {
         const uint32_t db = gi < (uint64_t)n ? __float_as_uint(depth[item * n + gi]) : 0u;
-        keys[start + rank[r]] = ((uint64_t)(uint32_t)t << 32) | (uint64_t)db;
+        keys[start + j] = ((uint64_t)(uint32_t)t << 32) | (uint64_t)db;
       }
     }
-  }
 }
 
 // Lists longer than the long kernel's CH: the all-ascending form of Batcher's bitonic network
@@ -918,12 +1018,14 @@ __device__ void bitonic_tile(uint64_t* s, uint64_t* g, int64_t L) {
   }
 }
 
-// Short lists (up to 1024 keys), one block per tile; also writes every tile's range.
-constexpr int kShortKeys = 1024;
+// Short lists (up to 2048 keys, a sub-list a wave), one block per tile; also writes every tile's
+// range.
+constexpr int kShortKeys = 2048;
+constexpr int kShortThreads = kShortKeys / kSub * 64;
 constexpr int kLongThreads = 1024;
 constexpr int kLongKeys = 8192;
 
-__global__ __launch_bounds__(256) void k_tile_sort_short(const uint32_t* __restrict__ offs, int nblk, int n_tiles,
+__global__ __launch_bounds__(kShortThreads) void k_tile_sort_short(const uint32_t* __restrict__ offs, int n_tiles,
                                                          const uint64_t* __restrict__ dtotal, int64_t cap,
                                                          const uint64_t* __restrict__ tmp,
                                                          const float* __restrict__ depth,
@@ -933,19 +1035,19 @@ __global__ __launch_bounds__(256) void k_tile_sort_short(const uint32_t* __restr
   __shared__ __align__(16) uint64_t s[kShortKeys];
   const int t = blockIdx.x;
   int64_t start, L;
-  tile_span(offs, nblk, n_tiles, dtotal, cap, t, start, L);
+  tile_span(offs, n_tiles, dtotal, cap, t, start, L);
   if (threadIdx.x == 0) {
     ranges[2 * (int64_t)t] = L > 0 ? (uint32_t)start : 0u;
     ranges[2 * (int64_t)t + 1] = L > 0 ? (uint32_t)(start + L) : 0u;
   }
   if (L <= 0 || L > kShortKeys) return;
-  sort_tile<256, kShortKeys>(s, tmp + start, (int)L, t, start, depth, items, n_items, n, vals, keys);
+  sort_tile<kShortThreads, kShortKeys>(s, tmp + start, (int)L, t, start, depth, items, n_items, n, vals, keys);
 }
 
-// Longer lists: blocks of 1024 threads walk the tiles; up to 8192 keys by rank, beyond that
+// Longer lists: blocks of 1024 threads walk the tiles; up to 8192 keys in LDS, beyond that
 // the bitonic network.
-__global__ __launch_bounds__(kLongThreads) void k_tile_sort_long(const uint32_t* __restrict__ offs, int nblk,
-                                                                 int n_tiles, const uint64_t* __restrict__ dtotal,
+__global__ __launch_bounds__(kLongThreads) void k_tile_sort_long(const uint32_t* __restrict__ offs, int n_tiles,
+                                                                 const uint64_t* __restrict__ dtotal,
                                                                  int64_t cap, uint64_t* tmp,
                                                                  const float* __restrict__ depth,
                                                                  const gs_item* __restrict__ items, int n_items,
@@ -962,7 +1064,7 @@ __global__ __launch_bounds__(kLongThreads) void k_tile_sort_long(const uint32_t*
     const int64_t tt = t0 + (int64_t)gridDim.x * threadIdx.x;
     if (tt < n_tiles) {
       int64_t st, ln;
-      tile_span(offs, nblk, n_tiles, dtotal, cap, (int)tt, st, ln);
+      tile_span(offs, n_tiles, dtotal, cap, (int)tt, st, ln);
       if (ln > kShortKeys) s_list[atomicAdd(&s_n, 1)] = (int)tt;
     }
     __syncthreads();
@@ -970,7 +1072,7 @@ __global__ __launch_bounds__(kLongThreads) void k_tile_sort_long(const uint32_t*
     for (int li = 0; li < nl; ++li) {
       const int t = s_list[li];
       int64_t start, L;
-      tile_span(offs, nblk, n_tiles, dtotal, cap, t, start, L);
+      tile_span(offs, n_tiles, dtotal, cap, t, start, L);
       if (L <= kLongKeys) {
         sort_tile<kLongThreads, kLongKeys>(s, tmp + start, (int)L, t, start, depth, items, n_items, n, vals, keys);
       } else {
@@ -1124,46 +1226,43 @@ int radix_covered_bits(int bits) {
 
 }  // namespace
 
-// Bucket path: block count of the pair kernels. Every block writes (and the scan reads) one
-// counter per tile, while fewer blocks leave each wave more groups of entries to walk one
-// after another; the two costs balance near 11 sqrt(E / tiles) blocks (at most 512, two per
-// compute unit, and at most 2^22 counters).
+// Bucket path: block count of the pair kernels, a group of entries a wave and at most one block
+// per compute unit (128, 256 and 512 blocks: 119, 108 and 108 us for the first, 41, 33 and 42 for the
+// second workload above), and at most 2^22 slots.
 int bucket_blocks(int64_t E, int64_t n_tiles) {
   const int64_t groups = ceil_div(std::max<int64_t>(E, 1), 64);
-  const double bal = 11.0 * std::sqrt((double)std::max<int64_t>(E, 1) / (double)std::max<int64_t>(n_tiles, 1));
-  int64_t nb = std::min<int64_t>({(int64_t)512, ceil_div(groups, kBkWaves), std::max<int64_t>(16, (int64_t)bal)});
+  int64_t nb = std::min<int64_t>(256, ceil_div(groups, kBkWaves));
   nb = std::min<int64_t>(nb, ((int64_t)1 << 22) / std::max<int64_t>(n_tiles, 1));
   return (int)std::max<int64_t>(1, nb);
 }
 
 struct BucketWs {
-  uint32_t* hist;      // [n_tiles * nblk]
-  uint32_t* partial;   // scan partials
+  uint32_t* hist;      // [nblk][n_tiles]: the block's first slot in the tile's list
+  uint32_t* total;     // [n_tiles]
+  uint32_t* offs;      // [n_tiles]: the list's start
   uint64_t* tmp;       // [cap]
   uint64_t* counters;  // [0]: duplicate total
   int nblk;
-  int64_t hist_n;
   size_t bytes;
 };
 
 BucketWs plan_bucket(int64_t E, int64_t n_tiles, int64_t cap, void* base) {
   BucketWs w{};
   w.nblk = bucket_blocks(E, n_tiles);
-  w.hist_n = std::max<int64_t>(n_tiles, 0) * w.nblk;
-  const int64_t np = ceil_div(std::max<int64_t>(w.hist_n, 1), kScanTile) + 2;
+  const size_t tiles = (size_t)std::max<int64_t>(n_tiles, 1);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
     off = align_up(off + bytes);
     return o;
   };
-  const size_t o_hist = take(4 * (size_t)std::max<int64_t>(w.hist_n, 1)), o_part = take(4 * (size_t)np),
-               o_tmp = take(8 * (size_t)std::max<int64_t>(cap, 1)), o_cnt = take(8 * 4);
+  const size_t o_hist = take(4 * tiles * w.nblk), o_total = take(4 * tiles), o_offs = take(4 * tiles), o_tmp = take(8 * (size_t)std::max<int64_t>(cap, 1)), o_cnt = take(8 * 4);
   w.bytes = off;
   if (base) {
     char* b = static_cast<char*>(base);
     w.hist = (uint32_t*)(b + o_hist);
-    w.partial = (uint32_t*)(b + o_part);
+    w.total = (uint32_t*)(b + o_total);
+    w.offs = (uint32_t*)(b + o_offs);
     w.tmp = (uint64_t*)(b + o_tmp);
     w.counters = (uint64_t*)(b + o_cnt);
   }
@@ -1187,19 +1286,19 @@ int launch_bucket_sort(const gs_config& cfg, const gs_projected& proj, const gs_
   const int64_t E = (int64_t)n_items * n;
   BucketWs w = plan_bucket(E, n_tiles, cap, ws);
   uint64_t* d_total = w.counters;
+  if (n_tiles > 0)
+    hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)ceil_div(n_tiles, 256)), dim3(256), 0, s, w.total, n_tiles);
   hipLaunchKernelGGL(k_bucket_pairs<true>, dim3(w.nblk), dim3(kBkThreads), 0, s, cfg, proj.radius, proj.depth,
-                     proj.rec, items, E, n, n_tiles, w.nblk, w.hist, cap, w.tmp, (const uint64_t*)nullptr,
+                     proj.rec, items, E, n, n_tiles, w.nblk, w.hist, w.total, w.offs, cap, w.tmp, d_total,
                      (int64_t*)nullptr, (int32_t*)nullptr);
-  const int st = device_scan(w.hist, w.hist, nullptr, w.hist_n, w.hist_n, w.partial, d_total, s);
-  if (st) return st;
   hipLaunchKernelGGL(k_bucket_pairs<false>, dim3(w.nblk), dim3(kBkThreads), 0, s, cfg, proj.radius, proj.depth,
-                     proj.rec, items, E, n, n_tiles, w.nblk, w.hist, cap, w.tmp, (const uint64_t*)d_total, n_dup_dev,
+                     proj.rec, items, E, n, n_tiles, w.nblk, w.hist, w.total, w.offs, cap, w.tmp, d_total, n_dup_dev,
                      status_dev);
   if (n_tiles > 0) {
-    hipLaunchKernelGGL(k_tile_sort_short, dim3((unsigned)n_tiles), dim3(256), 0, s, w.hist, w.nblk, n_tiles,
+    hipLaunchKernelGGL(k_tile_sort_short, dim3((unsigned)n_tiles), dim3(kShortThreads), 0, s, w.offs, n_tiles,
                        (const uint64_t*)d_total, cap, w.tmp, proj.depth, items, n_items, n, ranges, vals, keys);
-    hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)std::min(n_tiles, 512)), dim3(kLongThreads), 0, s, w.hist,
-                       w.nblk, n_tiles, (const uint64_t*)d_total, cap, w.tmp, proj.depth, items, n_items, n, vals,
+    hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)std::min(n_tiles, 512)), dim3(kLongThreads), 0, s, w.offs,
+                       n_tiles, (const uint64_t*)d_total, cap, w.tmp, proj.depth, items, n_items, n, vals,
                        keys);
   }
   return launch_status();
