@@ -943,43 +943,57 @@ __global__ __launch_bounds__(256) void k_fwd_combine(const gs_item* __restrict__
 // d power/d mean2d = -(dE/d dx, dE/d dy) / log2(e) and d power/d(A, B, C) =
 // -(dx^2 / 2, dx dy, dy^2 / 2); the reverse pass sums dE/d dx, dE/d dy, dx^2, dx dy, dy^2
 // (times dL/d power) and applies these factors once per Gaussian.
-// Sums the geometric terms of GG Gaussians (6 GG values per lane) over the wave's four
-// lane rows and over the lane pairs (l16, l16 ^ 8) of a row, halving the values held at each
-// step instead of reducing each value separately: a permlane32 swap pairs rows (0, 2) and
-// (1, 3), a permlane16 swap rows (0, 1) and (2, 3), a row rotation by 8 the halves of a row.
-// Moves within the half rows finish the sums: every lane (row R, l16) returns Y[j] = the wave's
-// sum of V[f + j], with f = 6 R + 3 (l16 / 8) for GG = 4 and f = 3 R for GG = 2.
-template <int GG>
-__device__ __forceinline__ void geo_reduce(const float (&V)[6 * GG], float (&Y)[3]) {
-  constexpr int H1 = 3 * GG, H2 = 3 * GG / 2;
-  float W[H1], X[H2];
+// The geometric sums of a group from D[Gaussian][pixel of the wave] = dL/d power: lane (g4, l16)
+// takes Gaussian l16's pixels 32 ks + 8 g4 + e, two runs of eight along x, so that dy is one value a
+// run and three sums over it (of D, D dx, D dx^2) give all six terms; the four lane rows' parts
+// are then added with values halved at each step (permlane32 pairs rows (0, 2) and (1, 3), permlane16
+// rows (0, 1) and (2, 3)). The opacity's sum is that of D over the opacity
+// (an opacity of 0, which alpha_min = 0 lets through, has no gradient: its logit's is o (1 - o) times it). (Six terms for each pixel's
+// lane and their sums over 64 lanes were a quarter of the reverse pass's instructions.)
+// (x, y): position of the lane's first pixel; ys: rows from its first run to its second.
+__device__ __forceinline__ void geo_sums(const float* D, const float* R, float x, float y, float ys, int l16, int g4,
+                                         float& Y0, float& Y1) {
+  const LRec q = load_rec(R, l16);
+  float dx[8];
 #pragma unroll
-  for (int j = 0; j < H1; ++j) {
-    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(V[j]), __float_as_uint(V[j + H1]), false, false);
-    W[j] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-  }
+  for (int e = 0; e < 8; ++e) dx[e] = (x + (float)e) - q.m.x;
+  float s00 = 0.0f, s10 = 0.0f, s20 = 0.0f, s01 = 0.0f, s11 = 0.0f, s02 = 0.0f;
 #pragma unroll
-  for (int j = 0; j < H2; ++j) {
-    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(W[j]), __float_as_uint(W[j + H2]), false, false);
-    X[j] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-  }
-  if constexpr (GG == 4) {
-    const bool upper = (threadIdx.x & 8) != 0;
+  for (int ks = 0; ks < 2; ++ks) {
+    const float* d8 = D + l16 * kPs + 32 * ks + 8 * g4;
+    const float4 d0 = *reinterpret_cast<const float4*>(d8), d1 = *reinterpret_cast<const float4*>(d8 + 4);
+    const float d[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+    float a = 0.0f, b = 0.0f, c = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const float keep = upper ? X[j + 3] : X[j], send = upper ? X[j] : X[j + 3];
-      Y[j] = keep + dpp_ror8(send);
+    for (int e = 0; e < 8; ++e) {
+      const float t = d[e] * dx[e];
+      a += d[e];
+      b += t;
+      c = __builtin_fmaf(t, dx[e], c);
     }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 3; ++j) Y[j] = X[j] + dpp_ror8(X[j]);
+    const float dy = (y + (ks ? ys : 0.0f)) - q.m.y;
+    s00 += a;
+    s10 += b;
+    s20 += c;
+    const float t = a * dy;
+    s01 += t;
+    s11 = __builtin_fmaf(b, dy, s11);
+    s02 = __builtin_fmaf(t, dy, s02);
   }
+  // sums of D times dE/d dx = 2a dx + b dy, dE/d dy = b dx + 2c dy, dx^2, dx dy, dy^2, 1 / opacity
+  const float V[6] = {__builtin_fmaf(2.0f * q.m.z, s10, q.m.w * s01), __builtin_fmaf(q.m.w, s10, 2.0f * (q.c.x * s01)),
+                      s20, s11, s02, q.c.y > 1e-30f ? s00 * __builtin_amdgcn_rcpf(q.c.y) : 0.0f};
+  float W[3];
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    Y[j] += dpp_half_mirror(Y[j]);
-    Y[j] += dpp_xor1(Y[j]);
-    Y[j] += dpp_xor2(Y[j]);
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(V[j]), __float_as_uint(V[j + 3]), false, false);
+    W[j] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
   }
+  // lane row g4: Y0 is term 0, 1, 3, 4; Y1 term 2, 2, 5, 5
+  const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(W[0]), __float_as_uint(W[1]), false, false);
+  Y0 = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+  const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(W[2]), __float_as_uint(W[2]), false, false);
+  Y1 = __uint_as_float(u[0]) + __uint_as_float(u[1]);
 }
 
 __constant__ float kGeoScale[6] = {-1.0f / kLog2e, -1.0f / kLog2e, -0.5f, -1.0f, -0.5f, 1.0f};
@@ -1190,13 +1204,14 @@ struct GradDst {
 // (measured), so a group's sums go out with the lanes of a Gaussian side by side: a record's seven
 // components or an embedding's row (64 bytes) are one request each.
 // It replaces a block that staged 32 entries at a time for its four waves and met at two barriers a
-// batch: 16 full-HD pyramids, embedding 70.3 -> 27.1 ms; eight 636x476 pyramids, 20 classes
-// 6.44 -> 2.78 ms; a 1200x680 pyramid, 52 classes 1.04 -> 0.48 ms; a 320x240 pyramid 0.28 -> 0.14 ms
+// batch: 16 full-HD pyramids, embedding 70.3 -> 24.3 ms; eight 636x476 pyramids, 20 classes
+// 6.44 -> 2.65 ms; a 1200x680 pyramid, 52 classes 1.04 -> 0.45 ms; a 320x240 pyramid 0.28 -> 0.13 ms
 // (29.7, 3.14, 0.52 and 0.14 ms with a barrier per work item, sums read one by one as they go out
-// and records in single precision; 26.2, 2.73, 0.47, 0.13 with the latter alone).
+// and records in single precision; 27.0, 2.90, 0.48 and 0.14 with the geometric sums by pixel).
 // Windows of 64 entries shared by the four waves, their sums meeting in LDS (half the atomic
 // requests), took 45.9 ms and 0.88 ms on the first and third: 28 % of the cycles were waves waiting
-// for the one with most entries in the window. Vector issue is 60-65 % busy now.
+// for the one with most entries in the window. On the first, vector instructions now issue in 57 %
+// of the cycles, at the two waves per SIMD that the registers allow.
 constexpr int kGrp = 16, kRing = 128;   // ring: a part group (15), two groups in work, 64 new entries
 
 template <int NS>
@@ -1206,8 +1221,12 @@ struct BShape {
   static constexpr int FROW = kGF3 ? 3 * 16 + 4 : KP + 4;      // dwords of a feature row: 3 parts of 32 bf16, or floats
   static constexpr int AROW = KP + 8;                          // floats of a sum row: channels, then 6 geometric sums
   static constexpr int kQ = 8 * kRing, kW = kGrp * kPs, kF = kGrp * FROW, kA = kGrp * AROW;
+  // dL/d power of a group [Gaussian][pixel]: with 64 channels in the features' place, which the
+  // products have read by then
+  static constexpr int kD = KP > 32 ? 0 : kGrp * kPs;
+  static_assert(kD > 0 || kF >= kGrp * kPs, "the features' rows hold dL/d power");
   static constexpr int kStage = 32 * kPs;                      // upstream gradient staging at an item's start
-  static constexpr int kWave = kQ + kW + kF + kA > kStage ? kQ + kW + kF + kA : kStage;
+  static constexpr int kSum = kQ + kW + kF + kA + kD, kWave = kSum > kStage ? kSum : kStage;
 };
 
 template <int NS, int MODE>
@@ -1221,7 +1240,6 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
   constexpr bool EMB = MODE == kEmbVec;
   constexpr int KP = SShape<NS>::KP, CB = SShape<NS>::CB, FROW = B::FROW, AROW = B::AROW;
   constexpr bool kGF3 = B::kGF3;
-  constexpr int GG = NS > 28 ? 2 : 4;         // Gaussians per geometric-term reduction (register budget)
   __shared__ __align__(16) float s_mem[4][B::kWave];
   __shared__ BlockItems s_items;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -1236,7 +1254,11 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
   float* const W = Q + B::kQ;
   float* const F = W + B::kW;
   float* const A = F + B::kF;
+  float* const D = B::kD ? A + B::kA : F;
   const Region rg = wave_region(tws, wave, lane);
+  // the lane's two runs of eight pixels in geo_sums
+  const bool wide = tws == 6;   // a region of 16x4 pixels
+  const float gx = rg.x0 + (wide ? (float)(8 * (g4 & 1)) : 0.0f), gy = rg.y0 + (float)(wide ? g4 >> 1 : g4);
   items_init(s_items);
   for (uint32_t round = 0;; ++round) {
     const uint32_t wi = next_item(s_items, &ctl[2], wave, round);
@@ -1537,48 +1559,34 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
         block_transpose(Y4);
         // reverse recurrence over the group (T recovered with the hardware reciprocal)
 #pragma unroll
-        for (int gb = 0; gb < kGrp / GG; ++gb) {
-          float V[6 * GG];   // V[6 r + k]: component k of the geometric terms of Gaussian GG gb + r
-#pragma unroll
-          for (int r = 0; r < GG; ++r) {
-            const int qq = GG * gb + r;
-            const LRec rq = load_rec(R, qq);
-            const uint32_t pos = __float_as_uint(R[8 * qq + 6]);
-            float dx, dy, t;
-            const float G = __builtin_amdgcn_exp2f(local_power2(rg.lx, rg.ly, rq, dx, dy, t));
-            const float araw = rq.c.y * G;
-            const bool act = (pos < last) & (araw >= amin);
-            const float a = fminf(amax, araw);
-            const float rom = __builtin_amdgcn_rcpf(1.0f - a);
-            const float Tq = act ? T * rom : T;   // transmittance in front of this Gaussian
-            const float wq = act ? a * Tq : 0.0f;
-            const float gf = __uint_as_float(Y4[qq >> 2][qq & 3]);
-            const float dalpha = Tq * gf - acc * rom;
-            acc = act ? __builtin_fmaf(gf, wq, acc) : acc;
-            T = Tq;
-            const float dfree = (act & (araw < amax)) ? dalpha : 0.0f;   // no gradient through the clamp
-            const float dpow = dfree * araw;
-            const float dop = dfree * G;
-            W[qq * kPs + lane] = wq;
-            // d power / d (mean2d, A, B, C) up to the per-component factors of kGeoScale
-            const float pdx = dpow * dx, pdy = dpow * dy;
-            V[6 * r + 0] = dpow * __builtin_fmaf(rq.m.z, dx, t);   // 2a dx + b dy
-            V[6 * r + 1] = dpow * __builtin_fmaf(rq.m.w, dx, 2.0f * (rq.c.x * dy));
-            V[6 * r + 2] = pdx * dx;
-            V[6 * r + 3] = pdx * dy;
-            V[6 * r + 4] = pdy * dy;
-            V[6 * r + 5] = dop;                                  // d/d opacity
-          }
-          float Y[3];
-          geo_reduce<GG>(V, Y);
-          // the Gaussian and first component of this lane's three sums
-          const int qd = GG * gb + (GG == 4 ? g4 : g4 >> 1);
-          const int k0 = GG == 4 ? 3 * (l16 >> 3) : 3 * (g4 & 1);
-          if ((l16 & (GG == 4 ? 7 : 15)) == 0)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) A[qd * AROW + KP + k0 + j] = Y[j];
+        for (int qq = 0; qq < kGrp; ++qq) {
+          const LRec rq = load_rec(R, qq);
+          const uint32_t pos = __float_as_uint(R[8 * qq + 6]);
+          float dx, dy, t;
+          const float G = __builtin_amdgcn_exp2f(local_power2(rg.lx, rg.ly, rq, dx, dy, t));
+          const float araw = rq.c.y * G;
+          const bool act = (pos < last) & (araw >= amin);
+          const float a = fminf(amax, araw);
+          const float rom = __builtin_amdgcn_rcpf(1.0f - a);
+          const float Tq = act ? T * rom : T;   // transmittance in front of this Gaussian
+          const float wq = act ? a * Tq : 0.0f;
+          const float gf = __uint_as_float(Y4[qq >> 2][qq & 3]);
+          const float dalpha = Tq * gf - acc * rom;
+          acc = act ? __builtin_fmaf(gf, wq, acc) : acc;
+          T = Tq;
+          const float dfree = (act & (araw < amax)) ? dalpha : 0.0f;   // no gradient through the clamp
+          W[qq * kPs + lane] = wq;
+          D[qq * kPs + lane] = dfree * araw;   // d L / d power
         }
         wave_sync();
+        {
+          // d power / d (mean2d, A, B, C) up to the per-component factors of kGeoScale
+          float Y0, Y1;
+          geo_sums(D, R, gx, gy, wide ? 2.0f : 4.0f, l16, g4, Y0, Y1);
+          float* a = A + l16 * AROW + KP;
+          a[g4 + (g4 >> 1)] = Y0;
+          if ((g4 & 1) == 0) a[2 + 3 * (g4 >> 1)] = Y1;
+        }
         // dF: A = W^T (i = Gaussian l16 of the group, k = pixel 32 ks + 8 g4 + e)
         v8bf wh[2], wl2[2];
 #pragma unroll
