@@ -622,66 +622,20 @@ __global__ __launch_bounds__(256) void k_zero_u32(uint32_t* __restrict__ p, int 
   if (i < n) p[i] = 0u;
 }
 
+struct BkLds {
+  uint32_t cnt[kBkMaxTiles];       // per tile: the block's count, or its next slot
+  uint32_t first[kBkWaves][64];    // the entry's first pair among the wave's
+  int4 rect[kBkWaves][64];         // x0, width, tiles_x, id of tile (0, y0) of the item
+};
+
+// The block's share of the (tile, entry) pairs: counted in s.cnt, or each key stored in its tile's
+// next slot (s_key: a wave's keys).
 template <bool COUNT>
-__global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, const int32_t* __restrict__ radius,
-                                                             const float* __restrict__ depth,
-                                                             const float* __restrict__ rec,
-                                                             const gs_item* __restrict__ items, int64_t E, int64_t n,
-                                                             int n_tiles, int nblk, uint32_t* __restrict__ hist,
-                                                             uint32_t* __restrict__ total,
-                                                             uint32_t* __restrict__ offs, int64_t cap,
-                                                             uint64_t* __restrict__ tmp,
-                                                             uint64_t* __restrict__ dtotal,
-                                                             int64_t* __restrict__ n_dup_out,
-                                                             int32_t* __restrict__ status) {
-  __shared__ uint32_t s_cnt[kBkMaxTiles];      // per tile: the block's count, or its next slot
-  __shared__ uint32_t s_first[kBkWaves][64];   // the entry's first pair among the wave's
-  __shared__ int4 s_rect[kBkWaves][64];        // x0, width, tiles_x, id of tile (0, y0) of the item
-  __shared__ uint64_t s_key[kBkWaves][64];     // the entry's key within its tiles (scatter)
-  const int b = blockIdx.x;
+__device__ __forceinline__ void walk_pairs(const gs_config& cfg, const int32_t* __restrict__ radius,
+                                           const float* __restrict__ depth, const float* __restrict__ rec,
+                                           const gs_item* __restrict__ items, int64_t E, int64_t n, int b, int nblk,
+                                           BkLds& s, uint64_t (*s_key)[64], int64_t cap, uint64_t* __restrict__ tmp) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint32_t* const row = hist + (int64_t)b * n_tiles;
-  for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) s_cnt[t] = COUNT ? 0u : total[t];
-  __syncthreads();
-  if (!COUNT) {
-    // exclusive scan of the totals; thread i has the tiles [i per, (i + 1) per), an odd number so
-    // that neighbouring threads meet different LDS banks
-    const int per = (int)((uint32_t)(n_tiles + kBkThreads - 1) / kBkThreads) | 1;
-    const int t0 = min(n_tiles, (int)threadIdx.x * per), t1 = min(n_tiles, t0 + per);
-    uint64_t sum = 0;
-    for (int t = t0; t < t1; ++t) sum += s_cnt[t];
-    uint64_t inc = sum;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint64_t v = __shfl_up(inc, off, 64);
-      if (lane >= off) inc += v;
-    }
-    if (lane == 63) s_key[0][wid] = inc;
-    __syncthreads();
-    uint64_t at = inc - sum, D = 0;
-    for (int k = 0; k < kBkWaves; ++k) {
-      const uint64_t v = s_key[0][k];
-      at += k < wid ? v : 0;
-      D += v;
-    }
-    for (int t = t0; t < t1; ++t) {
-      const uint32_t c = s_cnt[t];
-      s_cnt[t] = (uint32_t)at;
-      at += c;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) {
-      const uint32_t first = s_cnt[t];
-      if (b == 0) offs[t] = first;
-      s_cnt[t] = first + row[t];
-    }
-    if (b == 0 && threadIdx.x == 0) {
-      *dtotal = D;
-      if (n_dup_out) *n_dup_out = (int64_t)D;
-      if (status) *status = D > (uint64_t)cap ? GS_ERR_CAPACITY : GS_OK;
-    }
-    __syncthreads();
-  }
   const int64_t n_groups = (E + 63) >> 6, stride = (int64_t)nblk * kBkWaves;
   // groups of 64 consecutive entries, the block's waves on consecutive groups in each round.
   // Loads run ahead of use: a group's records (and depths) are loaded one group ahead, from
@@ -732,8 +686,8 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, cons
     wave_sync();
     if (c > 0) {
       const int at = lanes_below(some);
-      s_first[wid][at] = first;
-      s_rect[wid][at] = rc;
+      s.first[wid][at] = first;
+      s.rect[wid][at] = rc;
       if (!COUNT) s_key[wid][at] = key;
     }
     wave_sync();
@@ -746,16 +700,86 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, cons
       const int at = __popcll(__ballot(c > 0 && first <= k0)) - 1 + lanes_below(m);
       const uint32_t k = k0 + lane;
       if (k < pairs) {
-        const uint32_t i = k - s_first[wid][at];
-        const int4 rr = s_rect[wid][at];
+        const uint32_t i = k - s.first[wid][at];
+        const int4 rr = s.rect[wid][at];
         // (exact: i and the width are below 2^14)
         const int row = (int)(((float)i + 0.5f) * __builtin_amdgcn_rcpf((float)rr.y));
         const int tile = rr.w + row * rr.z + rr.x + ((int)i - row * rr.y);
-        const uint32_t pos = atomicAdd(&s_cnt[tile], 1u);
+        const uint32_t pos = atomicAdd(&s.cnt[tile], 1u);
         if (!COUNT && (int64_t)pos < cap) tmp[pos] = s_key[wid][at];
       }
     }
   }
+}
+
+// Every tile's total in s.cnt, turned into the lists' starts; returns the grand total.
+__device__ __forceinline__ uint64_t scan_tiles(BkLds& s, int n_tiles, uint64_t* s_part) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  // thread i has the tiles [i per, (i + 1) per), an odd number so that neighbouring threads meet
+  // different LDS banks
+  const int per = (int)((uint32_t)(n_tiles + kBkThreads - 1) / kBkThreads) | 1;
+  const int t0 = min(n_tiles, (int)threadIdx.x * per), t1 = min(n_tiles, t0 + per);
+  uint64_t sum = 0;
+  for (int t = t0; t < t1; ++t) sum += s.cnt[t];
+  uint64_t inc = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint64_t v = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += v;
+  }
+  if (lane == 63) s_part[wid] = inc;
+  __syncthreads();
+  uint64_t at = inc - sum, D = 0;
+  for (int k = 0; k < kBkWaves; ++k) {
+    const uint64_t v = s_part[k];
+    at += k < wid ? v : 0;
+    D += v;
+  }
+  for (int t = t0; t < t1; ++t) {
+    const uint32_t c = s.cnt[t];
+    s.cnt[t] = (uint32_t)at;
+    at += c;
+  }
+  __syncthreads();
+  return D;
+}
+
+__device__ __forceinline__ void report_total(uint64_t D, int64_t cap, uint64_t* dtotal, int64_t* n_dup_out,
+                                             int32_t* status) {
+  *dtotal = D;
+  if (n_dup_out) *n_dup_out = (int64_t)D;
+  if (status) *status = D > (uint64_t)cap ? GS_ERR_CAPACITY : GS_OK;
+}
+
+template <bool COUNT>
+__global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, const int32_t* __restrict__ radius,
+                                                             const float* __restrict__ depth,
+                                                             const float* __restrict__ rec,
+                                                             const gs_item* __restrict__ items, int64_t E, int64_t n,
+                                                             int n_tiles, int nblk, uint32_t* __restrict__ hist,
+                                                             uint32_t* __restrict__ total,
+                                                             uint32_t* __restrict__ offs, int64_t cap,
+                                                             uint64_t* __restrict__ tmp,
+                                                             uint64_t* __restrict__ dtotal,
+                                                             int64_t* __restrict__ n_dup_out,
+                                                             int32_t* __restrict__ status) {
+  __shared__ BkLds s;
+  __shared__ uint64_t s_key[kBkWaves][64];     // the entry's key within its tiles (scatter)
+  const int b = blockIdx.x;
+  uint32_t* const row = hist + (int64_t)b * n_tiles;
+  for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) s.cnt[t] = COUNT ? 0u : total[t];
+  __syncthreads();
+  if (!COUNT) {
+    const uint64_t D = scan_tiles(s, n_tiles, s_key[0]);
+    for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) {
+      const uint32_t first = s.cnt[t];
+      if (b == 0) offs[t] = first;
+      s.cnt[t] = first + row[t];
+    }
+    if (b == 0 && threadIdx.x == 0) report_total(D, cap, dtotal, n_dup_out, status);
+    __syncthreads();
+  }
+  walk_pairs<COUNT>(cfg, radius, depth, rec, items, E, n, b, nblk, s, s_key, cap, tmp);
   if (COUNT) {
     __syncthreads();
     // four atomics in flight a thread; the blocks start at different tiles
@@ -766,13 +790,40 @@ __global__ __launch_bounds__(kBkThreads) void k_bucket_pairs(gs_config cfg, cons
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int t = t0 + u * kBkThreads;
-        if (t < n_tiles) at[u] = atomicAdd(&total[t], s_cnt[t]);
+        if (t < n_tiles) at[u] = atomicAdd(&total[t], s.cnt[t]);
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         if (t0 + u * kBkThreads < n_tiles) row[t0 + u * kBkThreads] = at[u];
     }
   }
+}
+
+// Entries that a single block takes in one round: it counts, scans and scatters in one launch, not
+// three (500 entries, 12 tiles: the sort 22.6 -> 21.1 us in a graph, a launch's host time apart each).
+// Past them the pair kernels have more blocks to share large footprints: 4000 entries with 100k
+// duplicates take 57 us there and 125 in one block.
+constexpr int64_t kBkOneEntries = kBkThreads;
+
+__global__ __launch_bounds__(kBkThreads) void k_bucket_one(gs_config cfg, const int32_t* __restrict__ radius,
+                                                           const float* __restrict__ depth,
+                                                           const float* __restrict__ rec,
+                                                           const gs_item* __restrict__ items, int64_t E, int64_t n,
+                                                           int n_tiles, uint32_t* __restrict__ offs, int64_t cap,
+                                                           uint64_t* __restrict__ tmp, uint64_t* __restrict__ dtotal,
+                                                           int64_t* __restrict__ n_dup_out,
+                                                           int32_t* __restrict__ status) {
+  __shared__ BkLds s;
+  __shared__ uint64_t s_key[kBkWaves][64];
+  for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) s.cnt[t] = 0u;
+  __syncthreads();
+  walk_pairs<true>(cfg, radius, depth, rec, items, E, n, 0, 1, s, s_key, cap, tmp);
+  __syncthreads();
+  const uint64_t D = scan_tiles(s, n_tiles, s_key[0]);
+  for (int t = threadIdx.x; t < n_tiles; t += kBkThreads) offs[t] = s.cnt[t];
+  if (threadIdx.x == 0) report_total(D, cap, dtotal, n_dup_out, status);
+  __syncthreads();
+  walk_pairs<false>(cfg, radius, depth, rec, items, E, n, 0, 1, s, s_key, cap, tmp);
 }
 
 // Tile t's list: [offs[t], offs[t + 1]) (the duplicate total past the last tile), clamped to the capacity; a negative length (wrapped 32-bit slots past the capacity)
@@ -1286,20 +1337,26 @@ int launch_bucket_sort(const gs_config& cfg, const gs_projected& proj, const gs_
   const int64_t E = (int64_t)n_items * n;
   BucketWs w = plan_bucket(E, n_tiles, cap, ws);
   uint64_t* d_total = w.counters;
-  if (n_tiles > 0)
-    hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)ceil_div(n_tiles, 256)), dim3(256), 0, s, w.total, n_tiles);
-  hipLaunchKernelGGL(k_bucket_pairs<true>, dim3(w.nblk), dim3(kBkThreads), 0, s, cfg, proj.radius, proj.depth,
-                     proj.rec, items, E, n, n_tiles, w.nblk, w.hist, w.total, w.offs, cap, w.tmp, d_total,
-                     (int64_t*)nullptr, (int32_t*)nullptr);
-  hipLaunchKernelGGL(k_bucket_pairs<false>, dim3(w.nblk), dim3(kBkThreads), 0, s, cfg, proj.radius, proj.depth,
-                     proj.rec, items, E, n, n_tiles, w.nblk, w.hist, w.total, w.offs, cap, w.tmp, d_total, n_dup_dev,
-                     status_dev);
+  if (E <= kBkOneEntries) {
+    hipLaunchKernelGGL(k_bucket_one, dim3(1), dim3(kBkThreads), 0, s, cfg, proj.radius, proj.depth, proj.rec, items, E, n,
+                       n_tiles, w.offs, cap, w.tmp, d_total, n_dup_dev, status_dev);
+  } else {
+    if (n_tiles > 0)
+      hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)ceil_div(n_tiles, 256)), dim3(256), 0, s, w.total, n_tiles);
+    hipLaunchKernelGGL(k_bucket_pairs<true>, dim3(w.nblk), dim3(kBkThreads), 0, s, cfg, proj.radius, proj.depth,
+                       proj.rec, items, E, n, n_tiles, w.nblk, w.hist, w.total, w.offs, cap, w.tmp, d_total,
+                       (int64_t*)nullptr, (int32_t*)nullptr);
+    hipLaunchKernelGGL(k_bucket_pairs<false>, dim3(w.nblk), dim3(kBkThreads), 0, s, cfg, proj.radius, proj.depth,
+                       proj.rec, items, E, n, n_tiles, w.nblk, w.hist, w.total, w.offs, cap, w.tmp, d_total, n_dup_dev,
+                       status_dev);
+  }
   if (n_tiles > 0) {
     hipLaunchKernelGGL(k_tile_sort_short, dim3((unsigned)n_tiles), dim3(kShortThreads), 0, s, w.offs, n_tiles,
                        (const uint64_t*)d_total, cap, w.tmp, proj.depth, items, n_items, n, ranges, vals, keys);
-    hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)std::min(n_tiles, 512)), dim3(kLongThreads), 0, s, w.offs,
-                       n_tiles, (const uint64_t*)d_total, cap, w.tmp, proj.depth, items, n_items, n, vals,
-                       keys);
+    // (a Gaussian meets a tile once: no list has more than n entries)
+    if (n > kShortKeys)
+      hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)std::min(n_tiles, 512)), dim3(kLongThreads), 0, s, w.offs,
+                         n_tiles, (const uint64_t*)d_total, cap, w.tmp, proj.depth, items, n_items, n, vals, keys);
   }
   return launch_status();
 }

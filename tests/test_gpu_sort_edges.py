@@ -29,7 +29,8 @@ def test_list_lengths(n, sort_mode):
 
 # 12288 tiles are the most that the bucket path takes
 @pytest.mark.parametrize("tiles", [(1, 1), (5, 13), (32, 32), (33, 31), (64, 64), (17, 241), (128, 96)])
-def test_tile_counts(tiles):
+@pytest.mark.parametrize("n", [700, 1100])   # one block's entries, and more
+def test_tile_counts(tiles, n):
     W, H = 16 * tiles[0], 16 * tiles[1]
 
     def radius(r, m):
@@ -38,7 +39,7 @@ def test_tile_counts(tiles):
         x[[7, 200, 201, m - 1]] = W + H   # every tile
         return x
     views = [scenes.identity_view(W, H, levels=1)]
-    D = _check_sort(views, 700, *projection(700, W, H, radius, tiles[0]), sort_mode=2)
+    D = _check_sort(views, n, *projection(n, W, H, radius, tiles[0]), sort_mode=2)
     assert D > 4 * tiles[0] * tiles[1]
 
 
