@@ -283,9 +283,16 @@ constexpr SsTaps ss_taps() {
 }
 constexpr SsTaps kSsG = ss_taps();
 
-// Per item, the first SSIM tile: prefix[i] = sum over items < i of ceil(W/32) ceil(H/32).
-__global__ void k_ssim_prefix(const gs_item* __restrict__ items, int n_items, int64_t* __restrict__ prefix) {
+// Per item, the first SSIM tile: prefix[i] = sum over items < i of ceil(W/32) ceil(H/32) (the
+// first block); the other blocks clear n floats at p (one launch for two, 5 us).
+__global__ __launch_bounds__(256) void k_ssim_prefix(const gs_item* __restrict__ items, int n_items,
+                                                     int64_t* __restrict__ prefix, float* __restrict__ p, int64_t n) {
   __shared__ int64_t s[256];
+  if (blockIdx.x > 0) {
+    const int64_t i = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x;
+    if (i < n) p[i] = 0.0f;
+    return;
+  }
   int64_t carry = 0;
   for (int base = 0; base < n_items; base += 256) {
     const int i = base + (int)threadIdx.x;
@@ -725,7 +732,12 @@ int launch_loss(const gs_item* items, int n_items, int64_t P, int K, int n_class
   const float* tsem = t.sem_color;
   if (!tsem) lambda_s = 0.0f;
   const bool ssim = lambda != 0.0f, ssim_s = lambda_s != 0.0f;
-  launch_fill_f32(ws, (int64_t)n_items * 6 * kSlots, 0.0f, s);
+  const int64_t n_slots = (int64_t)n_items * 6 * kSlots;
+  if (ssim || ssim_s)
+    hipLaunchKernelGGL(k_ssim_prefix, dim3((unsigned)(1 + ceil_div(n_slots, 256))), dim3(256), 0, s, items, n_items, prefix,
+                       ws, n_slots);
+  else
+    launch_fill_f32(ws, n_slots, 0.0f, s);
 #define GS_LOSS_ARGS items, n_items, P, K, n_classes, color, logits, t.rgb, t.depth, t.label, tsem, w[0], w[2], \
                      !ssim, !ssim_s, loss_slots, count_slots, gcolor, glogits
   if (head) {
@@ -743,7 +755,6 @@ int launch_loss(const gs_item* items, int n_items, int64_t P, int K, int n_class
   if (ssim || ssim_s) {
     // one launch over the colour channels (0..2), the semantic colour ones (3..5) or both
     const int c0 = ssim ? 0 : 3, nch = (ssim && ssim_s) ? 6 : 3;
-    hipLaunchKernelGGL(k_ssim_prefix, dim3(1), dim3(256), 0, s, items, n_items, prefix);
     // a grid-stride loop covers every (tile, channel); the grid only needs to fill the chip
     const int resident = resident_blocks(k_ssim, 256, 512);
     const int64_t est = nch * (ceil_div(P, kSsT * kSsT) + n_items);
