@@ -998,29 +998,33 @@ __device__ __forceinline__ void geo_sums(const float* D, const float* R, float x
 
 __constant__ float kGeoScale[6] = {-1.0f / kLog2e, -1.0f / kLog2e, -0.5f, -1.0f, -0.5f, 1.0f};
 
-// One block per tile: the tile's list length in use (largest n_contrib) and its segment
+// One wave per tile: the tile's list length in use (largest n_contrib) and its segment
 // count, stored in work order (coarse pyramid levels first unless tile_order = 1).
 // With a forward state, a tile that the forward did not split stays one item.
+// (A block per tile spent its time being launched: 174k tiles 540 us, now 93; 4270 tiles 16, now 5.)
 __global__ __launch_bounds__(256) void k_seg_count(const gs_item* __restrict__ items, int n_items,
                                                    const uint32_t* __restrict__ ranges,
                                                    const uint32_t* __restrict__ ncin, int n_tiles, int order, int tws,
                                                    uint32_t seg, const uint32_t* __restrict__ ftcnt,
                                                    uint32_t* __restrict__ tile_lmax, uint32_t* __restrict__ cnt_ord) {
-  __shared__ uint32_t s_m;
-  const int tile = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int tile = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (tile >= n_tiles) return;
   const int item = item_of_tile(items, n_items, tile);
   const gs_item it = items[item];
   const int lt = tile - it.tile_base;
-  const int u = ((lt % it.tiles_x) << tws) + (threadIdx.x & ((1 << tws) - 1));
-  const int v = (lt / it.tiles_x) * (kTilePx >> tws) + (threadIdx.x >> tws);
-  const uint32_t len = ranges[2 * (int64_t)tile + 1] - ranges[2 * (int64_t)tile];
-  const uint32_t last = (u < it.W && v < it.H) ? min(ncin[it.pixel_base + (int64_t)v * it.W + u], len) : 0u;
-  if (threadIdx.x == 0) s_m = 0;
-  __syncthreads();
-  atomicMax(&s_m, last);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t m = s_m;
+  const int u0 = (lt % it.tiles_x) << tws, v0 = (lt / it.tiles_x) * (kTilePx >> tws);
+  uint32_t m = 0;
+#pragma unroll
+  for (int j = 0; j < kTilePx / 64; ++j) {
+    const int t = 64 * j + lane, u = u0 + (t & ((1 << tws) - 1)), v = v0 + (t >> tws);
+    const uint32_t c = ncin[it.pixel_base + (int64_t)min(v, it.H - 1) * it.W + min(u, it.W - 1)];
+    m = u < it.W && v < it.H ? max(m, c) : m;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+  if (lane == 0) {
+    m = min(m, ranges[2 * (int64_t)tile + 1] - ranges[2 * (int64_t)tile]);
     tile_lmax[tile] = m;
     const bool one = m <= seg || (ftcnt && ftcnt[tile] < 2);
     cnt_ord[order ? tile : n_tiles - 1 - tile] = m == 0 ? 0u : (one ? 1u : (m + seg - 1) / seg);
@@ -1776,7 +1780,7 @@ int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   seg_layout(n_tiles, cap, seg_len(cfg), (char*)seg_ws, &w);
   // with the forward's saved state the segments start from it: no summary pass
   const FState fs = state_of(fwd, n_tiles, 4 + cfg.n_sem, seg_len(cfg)).fs;
-  hipLaunchKernelGGL(k_seg_count, dim3(n_tiles), dim3(256), 0, s, items, n_items, ranges, fwd.n_contrib, n_tiles,
+  hipLaunchKernelGGL(k_seg_count, dim3((unsigned)ceil_div(n_tiles, 4)), dim3(256), 0, s, items, n_items, ranges, fwd.n_contrib, n_tiles,
                      cfg.tile_order, tile_shift(cfg), (uint32_t)seg_len(cfg), fs.tcnt, w.lmax, w.cnt);
   int st = launch_status();
   st = st ? st : scan_u32(w.cnt, w.base, n_tiles, w.partial, w.total, s);
