@@ -373,27 +373,29 @@ __device__ __forceinline__ void head_chunk_backward(const HeadLds& L, const floa
 
 // Sums the block's waves' accumulators in LDS and writes the block's partial.
 template <class LDS>
-__device__ __forceinline__ void head_write_partial(LDS& L, const HeadAcc& acc, float* __restrict__ partial) {
+__device__ __forceinline__ void head_write_partial(LDS& L, const HeadAcc& acc, float* __restrict__ partial, bool add) {
   const int lane = threadIdx.x & 63, l32 = lane & 31;
   float* s_acc = L.buf;
   __syncthreads();
   for (int i = threadIdx.x; i < kPart; i += (int)blockDim.x) s_acc[i] = 0.0f;
   __syncthreads();
+  if (add) {   // (uniform over the wave: it had a chunk)
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
+    for (int cb = 0; cb < 2; ++cb) {
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int c = drow(r, lane) + 32 * cb;   // D[c][h]: h = l32 + 32 hb
+          atomicAdd(&s_acc[c * 64 + l32 + 32 * hb], acc.W2[cb][hb][r]);
+        }
+      atomicAdd(&s_acc[kPartW2 + kPartW1 + l32 + 32 * cb], acc.B2[cb]);
+    }
 #pragma unroll
     for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = drow(r, lane) + 32 * cb;   // D[c][h]: h = l32 + 32 hb
-        atomicAdd(&s_acc[c * 64 + l32 + 32 * hb], acc.W2[cb][hb][r]);
-      }
-    atomicAdd(&s_acc[kPartW2 + kPartW1 + l32 + 32 * cb], acc.B2[cb]);
+      for (int r = 0; r < 16; ++r) atomicAdd(&s_acc[kPartW2 + (drow(r, lane) + 32 * hb) * 32 + l32], acc.W1[hb][r]);
   }
-#pragma unroll
-  for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) atomicAdd(&s_acc[kPartW2 + (drow(r, lane) + 32 * hb) * 32 + l32], acc.W1[hb][r]);
   __syncthreads();
   float* out = partial + (int64_t)blockIdx.x * kPart;
   for (int i = threadIdx.x; i < kPart; i += (int)blockDim.x) out[i] = s_acc[i];
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__
     // every lane is past this chunk's reads of the staged rows before the next chunk writes them
     wave_fence();
   }
-  head_write_partial(L, acc, partial);
+  head_write_partial(L, acc, partial, true);
 }
 
 // Learned-mode loss with the decode fused in (paper eq. 10-13 with the semantic term a
@@ -956,7 +958,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void k_head_loss(const gs_item
                                                       const int32_t* __restrict__ tlabel,
                                                       const uint16_t* __restrict__ W1, const float* __restrict__ b1,
                                                       const uint16_t* __restrict__ W2, const float* __restrict__ b2,
-                                                      float w0, float w2, bool rgb_grad, int n_slots,
+                                                      float w0, float w2, bool rgb_grad, int n_slots, int waves,
                                                       float* __restrict__ loss_slots, float* __restrict__ count_slots,
                                                       float* __restrict__ gcolor, float* __restrict__ partial) {
   __shared__ FusedLds L;
@@ -983,14 +985,14 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void k_head_loss(const gs_item
   cur.item = 0;
   cur.first = 0;
   cur.end = ((int64_t)citems[0].W * citems[0].H + 63) / 64;
-  const int64_t stride = (int64_t)gridDim.x * kFusedWaves;
+  const int64_t stride = (int64_t)gridDim.x * waves;
   // Every iteration issues the same loads whether or not a next chunk exists (past the end
   // the current chunk is loaded again and not used), so the number of loads in flight is
   // the same on every path and each buffer's wait covers exactly its own loads.
   ChunkInfo ca, cb;
-  bool have = chunk_info(citems, n_items, (int64_t)blockIdx.x * kFusedWaves + wave, cur, ca);
+  bool have = wave < waves && chunk_info(citems, n_items, (int64_t)blockIdx.x * waves + wave, cur, ca);
   if (!have) {
-    head_write_partial(L, acc, partial);
+    head_write_partial(L, acc, partial, false);
     return;
   }
   int ya = load_label(ca, tlabel), yb;
@@ -1015,24 +1017,32 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void k_head_loss(const gs_item
   // the last iteration's loads into the unused buffer are complete before the block's LDS
   // is reused below
   __builtin_amdgcn_s_waitcnt(0);
-  head_write_partial(L, acc, partial);
+  head_write_partial(L, acc, partial, true);
 }
 
-// Sums the per-block partials into the head's weight gradients: block = 64 columns,
-// four thread groups over interleaved partials, combined in LDS.
-__global__ __launch_bounds__(256) void k_head_reduce(const float* __restrict__ partial, int n_blocks, int C,
+// Sums the per-block partials into the head's weight gradients: block = 64 columns, sixteen
+// thread groups over interleaved partials, eight loads in flight each, combined in LDS.
+constexpr int kReduceGroups = 16;
+__global__ __launch_bounds__(64 * kReduceGroups) void k_head_reduce(const float* __restrict__ partial, int n_blocks, int C,
                                                      float* __restrict__ gW1, float* __restrict__ gb1,
                                                      float* __restrict__ gW2, float* __restrict__ gb2) {
-  __shared__ float s_sum[4][64];
+  __shared__ float s_sum[kReduceGroups][64];
   const int col = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + col;
   float s = 0.0f;
-  if (i < kPart)
-    for (int b = grp; b < n_blocks; b += 4) s += partial[(int64_t)b * kPart + i];
+  for (int b = grp; b < n_blocks; b += 8 * kReduceGroups) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = partial[(int64_t)min(b + u * kReduceGroups, n_blocks - 1) * kPart + min(i, kPart - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += b + u * kReduceGroups < n_blocks ? v[u] : 0.0f;
+  }
   s_sum[grp][col] = s;
   __syncthreads();
   if (grp != 0 || i >= kPart) return;
-  s = (s_sum[0][col] + s_sum[1][col]) + (s_sum[2][col] + s_sum[3][col]);
+  s = 0.0f;
+#pragma unroll
+  for (int u = 0; u < kReduceGroups; u += 4) s += (s_sum[u][col] + s_sum[u + 1][col]) + (s_sum[u + 2][col] + s_sum[u + 3][col]);
   if (i < kPartW2) {
     const int c = i / 64, h = i % 64;
     if (c < C) gW2[c * kHid + h] = s;
@@ -1074,7 +1084,7 @@ int launch_head_bwd(const gs_item* items, int n_items, int64_t P, int K, const g
   const int blocks = (int)std::min<int64_t>(std::min(kHeadBlocksMax, resident), ceil_div(ceil_div(P, 64) + n_items, 4));
   hipLaunchKernelGGL(k_head_bwd, dim3(blocks), dim3(256), 0, s, items, n_items, K, h.n_classes, color, glogits, h.W1,
                      h.b1, h.W2, gcolor, partial);
-  hipLaunchKernelGGL(k_head_reduce, dim3((unsigned)ceil_div(kPart, 64)), dim3(256), 0, s, partial, blocks, h.n_classes,
+  hipLaunchKernelGGL(k_head_reduce, dim3((unsigned)ceil_div(kPart, 64)), dim3(64 * kReduceGroups), 0, s, partial, blocks, h.n_classes,
                      gW1, gb1, gW2, gb2);
   return launch_status();
 }
@@ -1085,11 +1095,16 @@ int launch_head_loss(const gs_item* items, int n_items, int64_t P, int K, const 
                      hipStream_t s) {
   if (P == 0) return GS_OK;
   const int resident = resident_blocks(k_head_loss, 64 * kFusedWaves, kHeadBlocksMax);
-  const int blocks = (int)std::min<int64_t>(std::min(kHeadBlocksMax, resident), ceil_div(ceil_div(P, 64) + n_items, kFusedWaves));
+  // few chunks: half of a block's waves take them, one per SIMD, on twice the blocks. (36k pixels, 13
+  // classes, the whole loss: 123 us with all eight, 85 with four, no sums from idle waves and the
+  // partials added with loads in flight, 18.8 -> 4.6 us of it.)
+  const int64_t chunks = ceil_div(P, 64) + n_items, most = std::min(kHeadBlocksMax, resident);
+  const int waves = chunks > kFusedWaves / 2 * most ? kFusedWaves : kFusedWaves / 2;
+  const int blocks = (int)std::min<int64_t>(most, ceil_div(chunks, waves));
   hipLaunchKernelGGL(k_head_loss, dim3(blocks), dim3(64 * kFusedWaves), 0, s, items, n_items, K, h.n_classes, color, t.rgb, t.depth,
-                     t.label, h.W1, h.b1, h.W2, h.b2, w0, w2, rgb_grad, n_slots, loss_slots, count_slots, gcolor,
+                     t.label, h.W1, h.b1, h.W2, h.b2, w0, w2, rgb_grad, n_slots, waves, loss_slots, count_slots, gcolor,
                      partial);
-  hipLaunchKernelGGL(k_head_reduce, dim3((unsigned)ceil_div(kPart, 64)), dim3(256), 0, s, partial, blocks, h.n_classes,
+  hipLaunchKernelGGL(k_head_reduce, dim3((unsigned)ceil_div(kPart, 64)), dim3(64 * kReduceGroups), 0, s, partial, blocks, h.n_classes,
                      gW1, gb1, gW2, gb2);
   return launch_status();
 }

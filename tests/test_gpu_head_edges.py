@@ -17,6 +17,7 @@ VIEWS = {
     "63_and_65": [(9, 7, 1), (13, 5, 1)],
     "ragged_pyramid": [(44, 28, 3), (8, 8, 1)],
     "many_chunks": [(200, 136, 3)],
+    "all_waves": [(320, 240, 1)],   # more chunks than four waves on every compute unit
 }
 
 
