@@ -111,7 +111,7 @@ __device__ __forceinline__ void sh_grad_dot(float x, float y, float z, int deg, 
 // Bound by memory, whose floor is 168 us for 200k Gaussians, 52 classes of degree 1, rgb of degree 3
 // and two views: a lane per (Gaussian, channel) had every lane work out its Gaussian's directions,
 // and three rgb channels' degree 3 cost the whole wave: forward 101 us, backward 377. Now 75 and 121.
-constexpr int kShG = 16, kShV = 4, kShWaves = 4;
+constexpr int kShG = 16, kShV = 4, kShWaves = 4, kShBwdWaves = 8;
 // The largest semantic degree that goes this way; past it a step has too many coefficients for
 // loads of several steps in flight, and rows are fetched again for their other channels. Measured
 // with 100k Gaussians, 52 classes, two views, this way and with a lane per channel: forward, degree
@@ -252,34 +252,35 @@ __global__ __launch_bounds__(64 * kShWaves) void k_sh_fwd(gs_gaussians g, gs_sh 
 // feature gradient (times Y_j) over views. The direction's share needs only h_j = sum_c g_c k_jc of
 // each (Gaussian, view), a sum over its channels; lane 4 g + k then takes sum_j h_j dY_j/dd through
 // the normalisation to the mean (summed over the views' four lanes) and to the pose's rho
-// (gpose[v][0..2] += R_v sum), which it keeps in registers over all its Gaussians, so a block adds
-// to each pose once (a grid of few blocks keeps those same-address atomics few). The bands of a
+// (gpose[v][0..2] += R_v sum), which it keeps in double precision over all its Gaussians, so a block adds
+// to each pose once. Every one of these atomics rounds the sum so far, and that is most of a pose
+// gradient's error, so blocks are few and of eight waves. The bands of a
 // later four views are added to the first four's.
 // A gradient of zero has no share, whatever it would be multiplied with (a direction from the
 // camera's own place, an infinite coefficient): such a Gaussian is rare, and done over by its lane.
 template <int RD, int SD>
-__global__ __launch_bounds__(64 * kShWaves, SD <= 1 ? 4 : 2) void k_sh_bwd(
+__global__ __launch_bounds__(64 * kShBwdWaves, SD <= 1 ? 4 : 2) void k_sh_bwd(
     gs_gaussians g, gs_sh sh, int n_sem, const gs_view* __restrict__ views, int n_views,
     const float* __restrict__ grgb, const float* __restrict__ gsem, float* __restrict__ gdc_rgb,
     float* __restrict__ grest_rgb, float* __restrict__ gdc_sem, float* __restrict__ grest_sem,
     float* __restrict__ gmean, float* __restrict__ gpose) {
   constexpr int JR = sh_rest(RD), JS = sh_rest(SD), D = RD > SD ? RD : SD, J = sh_rest(D), MU = sh_steps(SD);
-  __shared__ __align__(16) float s_mem[kShWaves][64 * J + 64 * 3 + 64 * JS + 3 * kShG * JR];
-  __shared__ double s_red[kShWaves][kShV][3];
+  __shared__ __align__(16) float s_mem[kShBwdWaves][64 * J + 64 * 3 + 64 * JS + 3 * kShG * JR];
+  __shared__ double s_red[kShBwdWaves][kShV][3];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, g4 = lane >> 4;
   const int vk = lane & 3;   // the lane's view of the four, as the lane of Gaussian lane / 4
   float* const Y = s_mem[wave];
   float* const G = Y + 64 * J;   // rgb gradients, a row of 64 for each channel
   float* const H = G + 64 * 3;   // h of the semantics
   float* const C = H + 64 * JS;  // the rgb coefficients
-  const int64_t n = g.n, step = (int64_t)gridDim.x * kShWaves * kShG;
+  const int64_t n = g.n, step = (int64_t)gridDim.x * kShBwdWaves * kShG;
   for (int v0 = 0; v0 < n_views; v0 += kShV) {
     const int nv = min(kShV, n_views - v0);
-    float us[3] = {0.0f, 0.0f, 0.0f};   // d L/d mu of the lane's view
+    double us[3] = {0.0, 0.0, 0.0};   // d L/d mu of the lane's view
     const gs_view& V = views[v0 + min(vk, nv - 1)];
     float cam[3];
     sh_camera(V, cam);
-    for (int64_t i0 = ((int64_t)blockIdx.x * kShWaves + wave) * kShG; i0 < n; i0 += step) {
+    for (int64_t i0 = ((int64_t)blockIdx.x * kShBwdWaves + wave) * kShG; i0 < n; i0 += step) {
       const int ng = (int)(n - i0 < kShG ? n - i0 : kShG);
       const int64_t iq = i0 + min(lane >> 2, ng - 1);
       const bool valid = vk < nv && (lane >> 2) < ng;
@@ -456,7 +457,7 @@ __global__ __launch_bounds__(64 * kShWaves, SD <= 1 ? 4 : 2) void k_sh_bwd(
 #pragma unroll
         for (int a = 0; a < 3; ++a) u[a] = share ? u[a] : 0.0f;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) us[a] += u[a];
+        for (int a = 0; a < 3; ++a) us[a] += (double)u[a];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
           u[a] += dpp_xor1(u[a]);
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(64 * kShWaves, SD <= 1 ? 4 : 2) void k_sh_bwd(
       const int t = threadIdx.x;
       if (t < 3 * nv) {
         double S = 0.0;
-        for (int w = 0; w < kShWaves; ++w) S += s_red[w][t / 3][t % 3];
+        for (int w = 0; w < kShBwdWaves; ++w) S += s_red[w][t / 3][t % 3];
         if (S != 0.0) atomicAdd(gpose + 6 * (v0 + t / 3) + t % 3, (float)S);
       }
       __syncthreads();
@@ -499,9 +500,9 @@ template <int RD, int SD>
 int launch_bwd_d(const gs_gaussians& g, const gs_sh& sh, int n_sem, const gs_view* views, int n_views,
                  const float* grgb, const float* gsem, float* gdc_rgb, float* grest_rgb, float* gdc_sem,
                  float* grest_sem, float* gmean, float* gpose, hipStream_t s) {
-  const int64_t blocks = std::min<int64_t>(ceil_div(g.n, kShWaves * kShG),
-                                           resident_blocks(k_sh_bwd<RD, SD>, 64 * kShWaves, 512));
-  hipLaunchKernelGGL((k_sh_bwd<RD, SD>), dim3((unsigned)blocks), dim3(64 * kShWaves), 0, s, g, sh, n_sem, views, n_views,
+  const int64_t blocks = std::min<int64_t>(ceil_div(g.n, kShBwdWaves * kShG),
+                                           resident_blocks(k_sh_bwd<RD, SD>, 64 * kShBwdWaves, 512));
+  hipLaunchKernelGGL((k_sh_bwd<RD, SD>), dim3((unsigned)blocks), dim3(64 * kShBwdWaves), 0, s, g, sh, n_sem, views, n_views,
                      grgb, gsem, gdc_rgb, grest_rgb, gdc_sem, grest_sem, gmean, gpose);
   return launch_status();
 }
