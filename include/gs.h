@@ -89,7 +89,8 @@ typedef struct gs_config {
                               2 = buckets: one counting pass by tile, then each tile's list sorted
                               by (depth, index) in LDS (few launches; made for short lists; up to
                               12288 tiles, else GS_ERR_UNSUPPORTED); 0 = automatic (2 up to 12288
-                              tiles and 2^22 (item, Gaussian) entries, else 1) */
+                              tiles and 2^22 (item, Gaussian) entries, if the lists' mean length
+                              is bounded or no more than 8192 Gaussians are there; else 1) */
 } gs_config;
 
 /* One camera view: world -> camera transform x_c = R x_w + t (OpenCV axes,

@@ -1325,10 +1325,23 @@ BucketWs plan_bucket(int64_t E, int64_t n_tiles, int64_t cap, void* base) {
 // the lists grow with the scene; the radix path's passes cost the same per duplicate whatever
 // the lists. (The autotuner times both methods on the workload itself.)
 constexpr int64_t kBucketMaxEntries = (int64_t)1 << 22;
+// ... and up to a mean list length, where a list can be longer than kLongKeys at all (a Gaussian
+// meets a tile once). One block sorts a list in LDS up to kLongKeys keys and in global memory
+// beyond, and a room frame's lists reach 3 to 4 times the mean. Buckets against radix, us: one
+// item, 2000 a tile (longest 7030) 70 / 173, 2040 71 / 154, 2500 (8864) 192 / 172, 6000 337 / 198,
+// 12244 733 / 199; a view of 136k Gaussians with 2435 a tile 362 / 377. Of several items some are
+// mostly a pyramid's coarse levels, whose lists are the long ones: three levels, 1500 335 / 194,
+// 2250 451 / 214, four, 2955 (72418) 1289 / 249; but the host knows neither levels nor lists
+// here, and views of one level pay up to 100 us if the line is too low. The capacity bounds the
+// duplicates, so entries out of view, which make no list longer, do not count where the caller
+// has sized it to the frame.
+constexpr int64_t kBucketMaxMean = 2048, kBucketMaxMeanOne = 2560;
 
-bool bucket_path(const gs_config& cfg, int64_t E, int n_tiles) {
+bool bucket_path(const gs_config& cfg, int n_items, int64_t n, int n_tiles, int64_t cap) {
   if (n_tiles > kBkMaxTiles) return false;
-  return cfg.sort_mode == 2 || (cfg.sort_mode == 0 && E <= kBucketMaxEntries);
+  if (cfg.sort_mode != 0) return cfg.sort_mode == 2;
+  const int64_t E = (int64_t)n_items * n, mean = n_items == 1 ? kBucketMaxMeanOne : kBucketMaxMean;
+  return E <= kBucketMaxEntries && (n <= kLongKeys || std::min(E, cap) <= mean * std::max(n_tiles, 1));
 }
 
 int launch_bucket_sort(const gs_config& cfg, const gs_projected& proj, const gs_item* items, int n_items, int64_t n,
@@ -1376,7 +1389,7 @@ int launch_bin_sort(const gs_config& cfg, const gs_projected& proj, const gs_ite
                     int64_t* n_dup_dev, int32_t* status_dev, hipStream_t s) {
   const int64_t E = (int64_t)n_items * n;
   if (cfg.sort_mode == 2 && n_tiles > kBkMaxTiles) return GS_ERR_UNSUPPORTED;
-  if (bucket_path(cfg, E, n_tiles))
+  if (bucket_path(cfg, n_items, n, n_tiles, cap))
     return launch_bucket_sort(cfg, proj, items, n_items, n, n_tiles, cap, ws, keys, vals, ranges, n_dup_dev,
                               status_dev, s);
   SortWs w = plan_sort(E, cap, ws);

@@ -52,3 +52,15 @@ def test_many_entries():
              for W, H in sizes]
     hi, lo, rad, depth = (np.concatenate([p[i] for p in parts]) for i in range(4))
     assert _check_sort(views, n, hi, lo, rad, depth, sort_mode=2) > 50_000
+
+
+# the automatic choice: by radix where a list can pass 8192 keys and the mean passes 2560 (2048 of
+# several items)
+@pytest.mark.parametrize("items", [1, 2])
+@pytest.mark.parametrize("n,tiles", [(8192, (1, 1)), (8192, (2, 1)), (8193, (1, 1)), (8193, (2, 2)), (8193, (3, 1)),
+                                     (8193, (5, 1)), (20000, (3, 3)), (20000, (4, 2)), (20000, (5, 2))])
+def test_automatic_choice(n, tiles, items):
+    W, H = 16 * tiles[0], 16 * tiles[1]
+    views = [scenes.identity_view(W, H, levels=1)] * items
+    parts = [projection(n, W, H, lambda r, m: np.full(m, 3), n + W + i) for i in range(items)]
+    assert _check_sort(views, n, *(np.concatenate([p[i] for p in parts]) for i in range(4)), sort_mode=0) >= items * n
