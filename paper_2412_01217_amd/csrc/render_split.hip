@@ -1578,9 +1578,10 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
           const float dalpha = Tq * gf - acc * rom;
           acc = act ? __builtin_fmaf(gf, wq, acc) : acc;
           T = Tq;
-          const float dfree = (act & (araw < amax)) ? dalpha : 0.0f;   // no gradient through the clamp
           W[qq * kPs + lane] = wq;
-          D[qq * kPs + lane] = dfree * araw;   // d L / d power
+          // d L / d power, none through the clamp. (Selected after the product: an opacity that is NaN,
+          // which no pixel takes, must leave zeros in the sums.)
+          D[qq * kPs + lane] = (act & (araw < amax)) ? dalpha * araw : 0.0f;
         }
         wave_sync();
         {
