@@ -515,9 +515,9 @@ __device__ __forceinline__ bool chunk_info(ConstItems items, int n_items, int64_
 // H^T = W1 E^T and logits^T = W2 h^T with the hidden layer in registers (see the top of the file),
 // split once for both class blocks. Bound by the logits' way to memory: at 52 classes 2.07 million
 // pixels read 133 MB and write 431 MB, 0.12 ms at copy rate; a wave per chunk that fetched the
-// weights value by value took 0.36 ms.
-__global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__ items, int n_items, int K, int C,
-                                                     const float* __restrict__ color,
+// weights value by value took 0.36 ms. Pixels from the P-th on (gs_images.n_pixels) are not written.
+__global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__ items, int n_items, int64_t P, int K,
+                                                     int C, const float* __restrict__ color,
                                                      const uint16_t* __restrict__ W1, const float* __restrict__ b1,
                                                      const uint16_t* __restrict__ W2, const float* __restrict__ b2,
                                                      float* __restrict__ logits) {
@@ -560,7 +560,14 @@ __global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__
         for (int j = 0; j < 4; ++j) e[pb][ks][j] = b[(8 * ks + j) * c.HW];
     }
   };
-  if (!chunk_info(citems, n_items, (int64_t)blockIdx.x * 4 + wave, cur, ci)) return;
+  // the chunk's place and its pixels before the P-th; false past them (the chunks come in pixel order)
+  auto place = [&](int64_t chunk, ChunkInfo& c) {
+    if (!chunk_info(citems, n_items, chunk, cur, c)) return false;
+    const int64_t left = P - (c.pixel_base + c.local0);
+    c.nlive = (int)min((int64_t)c.nlive, left);
+    return left > 0;
+  };
+  if (!place((int64_t)blockIdx.x * 4 + wave, ci)) return;
   load(ci);
   for (;;) {
     v4s ehi[2][2], elo[2][2];
@@ -568,7 +575,7 @@ __global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__
     for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) split4(e[pb][ks], ehi[pb][ks], elo[pb][ks]);
-    const bool more = chunk_info(citems, n_items, ci.chunk + stride, cur, cn);
+    const bool more = place(ci.chunk + stride, cn);
     if (more) load(cn);
     float* out = logits + ci.pixel_base * C + ci.local0 + l32;
 #pragma unroll
@@ -1068,8 +1075,8 @@ int launch_head_fwd(const gs_item* items, int n_items, int64_t P, int K, const g
   // at most one 64-pixel chunk per item is partial, so P / 64 + n_items bounds the chunk count
   const int resident = resident_blocks(k_head_fwd, 256, 512);
   const int64_t blocks = std::min<int64_t>(resident, ceil_div(ceil_div(P, 64) + n_items, 4));
-  hipLaunchKernelGGL(k_head_fwd, dim3((unsigned)blocks), dim3(256), 0, s, items, n_items, K, h.n_classes, color, h.W1,
-                     h.b1, h.W2, h.b2, logits);
+  hipLaunchKernelGGL(k_head_fwd, dim3((unsigned)blocks), dim3(256), 0, s, items, n_items, P, K, h.n_classes, color,
+                     h.W1, h.b1, h.W2, h.b2, logits);
   return launch_status();
 }
 
