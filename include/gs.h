@@ -212,7 +212,9 @@ int gs_make_items(const gs_config* cfg, int32_t n_views, gs_view* views, const i
  * on n_items * n_gauss, n_tiles, dup_capacity and cfg->seg_len. Both hold at most one
  * segment per tile more than dup_capacity / seg_len, so a buffer sized for one segment
  * length holds fewer segments of a shorter one. A smaller buffer still works when the
- * lists' segments fit it, and makes every tile one item when they do not. */
+ * lists' segments fit it, and makes every tile one item when they do not. The size of
+ * GS_WS_RENDER_BWD has room to place its double-precision records on a 16-byte boundary:
+ * that workspace may start at any address. */
 int gs_workspace_size(int kind, const gs_config* cfg, int32_t n_items, int64_t n_gauss, int32_t n_tiles,
                       int64_t dup_capacity, int64_t n_pixels, size_t* bytes);
 

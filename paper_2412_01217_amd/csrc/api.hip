@@ -116,6 +116,11 @@ bool cfg_ok(const gs_config* c) {
   return true;
 }
 
+// The reverse pass adds to its gradient records with double-precision atomics, which fault off an
+// 8-byte boundary, and reads them 16 bytes at a time: they start at the workspace's first 16-byte
+// boundary. (The single-precision records before them took any 4-byte boundary.)
+constexpr size_t kRecAlign = 16;
+
 bool gauss_ok(const gs_gaussians* g, bool need_features) {
   if (!g || g->n < 0 || g->n >= (int64_t)1 << 31) return false;
   if (g->n == 0) return true;
@@ -218,7 +223,7 @@ int gs_workspace_size(int kind, const gs_config* cfg, int32_t n_items, int64_t n
       return GS_OK;
     case GS_WS_RENDER_BWD:
       *bytes = align_up(sizeof(double) * kGradRec * (size_t)n_items * (size_t)n_gauss) + align_up(head_bwd_workspace()) +
-               render_seg_workspace(n_tiles, dup_capacity, render_seg_len(*cfg));
+               render_seg_workspace(n_tiles, dup_capacity, render_seg_len(*cfg)) + kRecAlign;
       return GS_OK;
     case GS_WS_LOSS:
       *bytes = align_up(loss_workspace(n_items));
@@ -391,12 +396,15 @@ int gs_render_bwd(const gs_config* cfg, const gs_gaussians* g, const gs_projecte
   }
   const size_t rec_bytes = align_up(sizeof(double) * kGradRec * (size_t)n_items * (size_t)g->n);
   const size_t head_bytes = align_up(head_bwd_workspace());
-  if (!workspace || ws_bytes < rec_bytes + head_bytes) return GS_ERR_WORKSPACE;
+  const size_t skip = (size_t)(-(uintptr_t)workspace % kRecAlign);
+  if (!workspace || ws_bytes < skip + rec_bytes + head_bytes) return GS_ERR_WORKSPACE;
+  char* const ws = (char*)workspace + skip;
+  double* const rec = (double*)ws;
   // the rest holds the segment work list of the reverse pass, sized for a duplicate
   // capacity (0 still works: every tile is then one work item)
-  const int64_t cap = render_seg_capacity(n_tiles, render_seg_len(*cfg), ws_bytes - rec_bytes - head_bytes);
+  const int64_t cap = render_seg_capacity(n_tiles, render_seg_len(*cfg), ws_bytes - skip - rec_bytes - head_bytes);
   if (cap < 0) return GS_ERR_WORKSPACE;
-  void* seg_ws = (char*)workspace + rec_bytes + head_bytes;
+  void* seg_ws = ws + rec_bytes + head_bytes;
   hipStream_t s = (hipStream_t)stream;
   const int64_t n = g->n;
   gs_grads gr = *grads;
@@ -404,21 +412,21 @@ int gs_render_bwd(const gs_config* cfg, const gs_gaussians* g, const gs_projecte
   const int64_t fv = cfg->view_features ? n_views : 1;   // feature blocks (one per view, or shared)
   float* const zp[3] = {gr.rgb, cfg->n_sem > 0 ? gr.sem : nullptr, gr.pose};
   const int64_t zn[3] = {3 * n * fv, (int64_t)cfg->n_sem * n * fv, 6ll * n_views};
-  int st = launch_zero_grads((double*)workspace, proj->radius, (int64_t)n_items * n, zp, zn, 3, s);
+  int st = launch_zero_grads(rec, proj->radius, (int64_t)n_items * n, zp, zn, 3, s);
   if (st) return st;
   if (head) {
     st = launch_head_bwd(items_dev, n_items, fwd->n_pixels, 4 + cfg->n_sem, *head, fwd->color, grad_in->logits,
-                         grad_in->color, (float*)((char*)workspace + rec_bytes), gr.head_W1, gr.head_b1, gr.head_W2,
+                         grad_in->color, (float*)(ws + rec_bytes), gr.head_W1, gr.head_b1, gr.head_W2,
                          gr.head_b2, s);
     if (st) return st;
   }
   if (n == 0) return GS_OK;
   if (render) {
-    st = launch_render_bwd(*cfg, *g, *proj, items_dev, n_items, n_tiles, vals, ranges, *fwd, *grad_in, (double*)workspace,
+    st = launch_render_bwd(*cfg, *g, *proj, items_dev, n_items, n_tiles, vals, ranges, *fwd, *grad_in, rec,
                            gr, seg_ws, cap, s);
     if (st) return st;
   }
-  return launch_preprocess_bwd(*cfg, *g, views_dev, n_views, items_dev, (const double*)workspace, proj->radius, gr, s);
+  return launch_preprocess_bwd(*cfg, *g, views_dev, n_views, items_dev, rec, proj->radius, gr, s);
 }
 
 int gs_adam_step(float* param, const float* grad, float* m, float* v, int64_t n, float lr, float beta1, float beta2,
