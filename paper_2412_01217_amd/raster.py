@@ -34,11 +34,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# (torch's private call for it; the public one serves a torch that lacks it)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device):
-    if device.type != "cuda":
-        return torch.cuda.current_stream(device).cuda_stream   # (refuses it)
+    if device.type != "cuda" or _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream   # (refuses another device)
     index = device.index
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+    return _raw_stream(torch.cuda.current_device() if index is None else index)
 
 
 class Frame:
