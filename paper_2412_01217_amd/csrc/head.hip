@@ -560,14 +560,7 @@ __global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__
         for (int j = 0; j < 4; ++j) e[pb][ks][j] = b[(8 * ks + j) * c.HW];
     }
   };
-  // the chunk's place and its pixels before the P-th; false past them (the chunks come in pixel order)
-  auto place = [&](int64_t chunk, ChunkInfo& c) {
-    if (!chunk_info(citems, n_items, chunk, cur, c)) return false;
-    const int64_t left = P - (c.pixel_base + c.local0);
-    c.nlive = (int)min((int64_t)c.nlive, left);
-    return left > 0;
-  };
-  if (!place((int64_t)blockIdx.x * 4 + wave, ci)) return;
+  if (!chunk_info(citems, n_items, (int64_t)blockIdx.x * 4 + wave, cur, ci)) return;
   load(ci);
   for (;;) {
     v4s ehi[2][2], elo[2][2];
@@ -575,9 +568,10 @@ __global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__
     for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) split4(e[pb][ks], ehi[pb][ks], elo[pb][ks]);
-    const bool more = place(ci.chunk + stride, cn);
+    const bool more = chunk_info(citems, n_items, ci.chunk + stride, cur, cn);
     if (more) load(cn);
     float* out = logits + ci.pixel_base * C + ci.local0 + l32;
+    const int nout = (int)max((int64_t)0, min((int64_t)ci.nlive, P - (ci.pixel_base + ci.local0)));
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb) {
       v16f H[2];
@@ -607,7 +601,7 @@ __global__ __launch_bounds__(256, 2) void k_head_fwd(const gs_item* __restrict__
           Lg[cb] = mfma2(a, lo[0], lo[1], Lg[cb]);
         }
       }
-      if (l32 + 32 * pb < ci.nlive)
+      if (l32 + 32 * pb < nout)
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
