@@ -89,7 +89,6 @@ int launch_distill(const gs_item*, int, int64_t, int, const float*, const float*
                    hipStream_t);
 int launch_agree(const gs_item*, int, int64_t, int, const float*, const float*, unsigned long long*, hipStream_t);
 int launch_fill_f32(float*, int64_t, float, hipStream_t);
-int launch_zero_f32(float* const* p, const int64_t* n, int count, hipStream_t s);
 int launch_zero_grads(double* rec, const int32_t* radius, int64_t entries, float* const* p, const int64_t* n, int count,
                       hipStream_t s);
 

@@ -32,13 +32,6 @@ constexpr int kWtStride = kHid + 8;   // bfloat16 row stride of the transposed w
 
 __device__ __forceinline__ int drow(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
-__device__ __forceinline__ uint16_t bf16_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf16_f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
 // Splits four floats into hi and lo bfloat16 operands (hardware round-to-nearest-even), two
 // values per conversion.
 typedef float f2 __attribute__((ext_vector_type(2)));
@@ -401,12 +394,6 @@ __device__ __forceinline__ void head_write_partial(LDS& L, const HeadAcc& acc, f
   for (int i = threadIdx.x; i < kPart; i += (int)blockDim.x) out[i] = s_acc[i];
 }
 
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__ items, int n_items, int K, int C,
                                                      const float* __restrict__ color,
                                                      const float* __restrict__ glogits,
@@ -444,11 +431,11 @@ __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__
           if (c0 + k < C) sg[(c0 + k) * kGst + lane] = live ? v[k] : 0.0f;
       }
     }
-    wave_fence();
+    wave_sync();
     head_chunk_backward(L, sg, color + it.pixel_base * K + 4 * HW + local0, gcolor + it.pixel_base * K + 4 * HW + local0,
                         HW, nlive, w1a, b1l, acc);
     // every lane is past this chunk's reads of the staged rows before the next chunk writes them
-    wave_fence();
+    wave_sync();
   }
   head_write_partial(L, acc, partial, true);
 }
@@ -855,7 +842,7 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    wave_fence();
+    wave_sync();
     // (5) over the half's pixels p = 8 kk + 4 half + j (registers 4 kk + j):
     //  dW2[c][h] += dlogits[c][p] relu(H)[p][h], A = dlogits (i = class l32 + 32 cb, k = p);
     //  dW1[h][d] += dH[p][h] [E, 1][p][d], A = dH (i = hidden l32 + 32 hb, k = p), B = [E, 1] (j = d l32)
@@ -917,7 +904,7 @@ __device__ __forceinline__ void head_loss_chunk(const FusedLds& L, const uint16_
         acc.W1[hb] = mfma2(alo[0], alo[1], bhi[0], bhi[1], acc.W1[hb]);
       }
     }
-    wave_fence();   // the half's rows are read before the next half writes them
+    wave_sync();   // the half's rows are read before the next half writes them
   }
   // L1 colour and depth, lane = pixel
   const bool live = lane < nlive;
@@ -967,7 +954,6 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void k_head_loss(const gs_item
   __shared__ float b2s[kHid];                                // b2, minus infinity for absent classes
   __shared__ ChunkStage SA[kFusedWaves];
   __shared__ ChunkStage SB[kFusedWaves];
-  const int lane = threadIdx.x & 63;
   // wave-uniform: the chunk walk and the item table reads stay in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int i = threadIdx.x; i < kHid * kHid; i += 64 * kFusedWaves) {

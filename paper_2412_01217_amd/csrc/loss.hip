@@ -20,16 +20,6 @@ __global__ void k_fill_f32(float* p, int64_t n, float v) {
 // kernel folds the slots afterwards.
 constexpr int kSlots = 64;
 
-// out[i * stride + c] = sum over slots of in[(i * ncomp + c) * kSlots + slot].
-__global__ void k_fold_slots(const float* __restrict__ in, int n_items, int ncomp, float* __restrict__ out) {
-  for (int i = threadIdx.x; i < n_items * ncomp; i += blockDim.x) {
-    const float* src = in + (int64_t)i * kSlots;
-    float s = 0.0f;
-    for (int k = 0; k < kSlots; ++k) s += src[k];
-    out[i] = s;
-  }
-}
-
 __device__ __forceinline__ float sgn(float d) { return (float)((d > 0.0f) - (d < 0.0f)); }
 
 // Item of each lane's pixel. Items are ordered by pixel_base: the lanes read 64 bases at a
@@ -636,21 +626,13 @@ __global__ void k_argmax_labels(const gs_item* __restrict__ items, int n_items, 
 
 }  // namespace
 
-// Zeroes up to four arrays in one launch (grid-stride over their concatenation).
+// Zeroes up to four arrays in one launch (grid-stride over their concatenation), and the gradient
+// records of the visible entries, radius > 0: no other record is added to or read. Four lanes a
+// record, 16 bytes each.
 struct ZeroList {
   float* p[4];
   int64_t end[4];   // running totals of the lengths
 };
-__global__ __launch_bounds__(256) void k_zero_multi(ZeroList z) {
-  const int64_t tot = z.end[3];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x) {
-    const int k = (i >= z.end[0]) + (i >= z.end[1]) + (i >= z.end[2]);
-    z.p[k][i - (k > 0 ? z.end[k - 1] : 0)] = 0.0f;
-  }
-}
-
-// The same, and the gradient records of the visible entries, radius > 0: no other record is added
-// to or read. Four lanes a record, 16 bytes each.
 __global__ __launch_bounds__(256) void k_zero_grads(ZeroList z, float4* __restrict__ rec,
                                                     const int32_t* __restrict__ radius, int64_t entries) {
   constexpr int kPer = kGradRec / 2;
@@ -674,14 +656,6 @@ static ZeroList zero_list(float* const* p, const int64_t* n, int count) {
     z.end[k] = run;
   }
   return z;
-}
-
-int launch_zero_f32(float* const* p, const int64_t* n, int count, hipStream_t s) {
-  const ZeroList z = zero_list(p, n, count);
-  if (z.end[3] == 0) return GS_OK;
-  const int64_t blocks = std::min<int64_t>(ceil_div(z.end[3], 256), 4096);
-  hipLaunchKernelGGL(k_zero_multi, dim3((unsigned)blocks), dim3(256), 0, s, z);
-  return launch_status();
 }
 
 int launch_zero_grads(double* rec, const int32_t* radius, int64_t entries, float* const* p, const int64_t* n, int count,

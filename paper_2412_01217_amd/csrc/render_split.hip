@@ -1238,8 +1238,7 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
     gs_config cfg, FeatSrc src, const float* __restrict__ rec, int64_t n, const gs_item* __restrict__ items, int n_items,
     const uint32_t* __restrict__ vals, const uint32_t* __restrict__ ranges, const float* __restrict__ Tfin,
     const uint32_t* __restrict__ ncin, const float* __restrict__ gcolor, GradDst out, const uint2* __restrict__ work,
-    uint32_t* __restrict__ ctl, const uint32_t* __restrict__ tile_lmax, const float* __restrict__ segP,
-    const float* __restrict__ segGC, FState fs) {
+    uint32_t* __restrict__ ctl, const float* __restrict__ segP, const float* __restrict__ segGC, FState fs) {
   using B = BShape<NS>;
   constexpr bool EMB = MODE == kEmbVec;
   constexpr int KP = SShape<NS>::KP, CB = SShape<NS>::CB, FROW = B::FROW, AROW = B::AROW;
@@ -1530,7 +1529,6 @@ __global__ __launch_bounds__(256, 2) void k_render_bwd_main(
         if (done > 0) flush(done - 1, kGrp);
         if (ready > issued) gather(issued++);
         wave_sync();
-        const int cnt = min(kGrp, tail - kGrp * done);
         const float* R = Q + 8 * kGrp * (done & (kRing / kGrp - 1));
         // g . f: A = F (i = Gaussian l16 of the group, k = channel); D lane (row g4, l16): Gaussians
         // 4 g4 + r of pixel 16 pb + l16. The transpose gives every lane its own pixel's values:
@@ -1799,8 +1797,8 @@ int launch_bwd_s(const gs_config& cfg, const gs_gaussians& g, const gs_projected
   }
   const FeatSrc src{g.rgb, g.sem, p.depth, g.emb, cfg.n_sem};
   hipLaunchKernelGGL((k_render_bwd_main<NS, MODE>), dim3(grid_main), dim3(256), 0, s, cfg, src, p.rec, g.n, items, n_items,
-                     vals, ranges, fwd.T, fwd.n_contrib, gin.color, GradDst{gr.rgb, gr.sem, g2d}, w.work, w.ctl, w.lmax,
-                     w.P, w.GC, fs);
+                     vals, ranges, fwd.T, fwd.n_contrib, gin.color, GradDst{gr.rgb, gr.sem, g2d}, w.work, w.ctl, w.P,
+                     w.GC, fs);
   return launch_status();
 }
 
