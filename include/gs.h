@@ -88,9 +88,12 @@ typedef struct gs_config {
                               1 = radix passes (entries by (item, depth), then duplicates by tile);
                               2 = buckets: one counting pass by tile, then each tile's list sorted
                               by (depth, index) in LDS (few launches; made for short lists; up to
-                              12288 tiles, else GS_ERR_UNSUPPORTED); 0 = automatic (2 up to 12288
-                              tiles and 2^22 (item, Gaussian) entries, if the lists' mean length
-                              is bounded or no more than 8192 Gaussians are there; else 1) */
+                              12288 tiles, else GS_ERR_UNSUPPORTED); 0 = automatic: 2 up to 12288
+                              tiles and 2^22 (item, Gaussian) entries, unless more than 8192
+                              Gaussians are there and both the entries and dup_capacity pass 2560
+                              a tile (2048 with several items), which suggests lists too long for
+                              2; else 1. It cannot see the lists: where they are even, or most
+                              Gaussians out of view, 2 may be the faster one past that line */
 } gs_config;
 
 /* One camera view: world -> camera transform x_c = R x_w + t (OpenCV axes,

@@ -1326,15 +1326,21 @@ BucketWs plan_bucket(int64_t E, int64_t n_tiles, int64_t cap, void* base) {
 // the lists. (The autotuner times both methods on the workload itself.)
 constexpr int64_t kBucketMaxEntries = (int64_t)1 << 22;
 // ... and up to a mean list length, where a list can be longer than kLongKeys at all (a Gaussian
-// meets a tile once). One block sorts a list in LDS up to kLongKeys keys and in global memory
-// beyond, and a room frame's lists reach 3 to 4 times the mean. Buckets against radix, us: one
-// item, 2000 a tile (longest 7030) 70 / 173, 2040 71 / 154, 2500 (8864) 192 / 172, 6000 337 / 198,
-// 12244 733 / 199; a view of 136k Gaussians with 2435 a tile 362 / 377. Of several items some are
-// mostly a pyramid's coarse levels, whose lists are the long ones: three levels, 1500 335 / 194,
-// 2250 451 / 214, four, 2955 (72418) 1289 / 249; but the host knows neither levels nor lists
-// here, and views of one level pay up to 100 us if the line is too low. The capacity bounds the
-// duplicates, so entries out of view, which make no list longer, do not count where the caller
-// has sized it to the frame.
+// meets a tile once): one block sorts a list, in LDS up to kLongKeys keys and in global memory
+// beyond, which is where the radix path overtakes. The host knows neither the lists nor the levels,
+// so the line is a guess from the entries and the capacity, both of which have to pass it.
+// It is right for rooms, whose duplicates are about as many as the entries and whose longest list
+// is 3.6 times the mean at one level and 7 to 28 times in a pyramid. Buckets / radix, us:
+//   one level, mean 2238 (longest 8160) 68 / 162, 2839 (11720) 197 / 191, 4180 (14706) 199 / 164,
+//   6097 (24023) 337 / 191, 12012 (44200) 725 / 196; four one-level views, 2357 (14310) 211 / 212;
+//   two levels, 1916 (16091) 218 / 209; three, 2635 (24058) 334 / 169; four, 3489 (96529) 1687 / 287.
+// A line of 2048 for several items still leaves pyramids below it to the buckets (four levels, 1881
+// (48166) 749 / 209); a lower one would cost views of one level up to 100 us.
+// It is wrong for even lists past it (one level, 4505 (5931) 62 / 177) and for a map mostly out of
+// view whose capacity was not sized to the frame (5 % of 400k in view, 760 (1014) 28 / 154).
+// Large footprints have few entries, and even lists: 100k entries, 300 tiles, 6544 (7730) 106 / 188,
+// 14060 (17757) 397 / 236; 200k, 1200 tiles, 5488 (6196) 248 / 448; so the capacity alone, large for
+// them, is no reason for the radix path. Whoever knows the lists names the method (sort_mode).
 constexpr int64_t kBucketMaxMean = 2048, kBucketMaxMeanOne = 2560;
 
 bool bucket_path(const gs_config& cfg, int n_items, int64_t n, int n_tiles, int64_t cap) {
