@@ -456,7 +456,8 @@ __global__ __launch_bounds__(256, 1) void k_head_bwd(const gs_item* __restrict__
 // loads never waits for the other's. Labels come one chunk ahead in a register, colour, depth and
 // their targets during the chunk. (One wave per SIMD with every input staged, logit gradients
 // staged and read back as three operands, ReLU masks as bits: 2.80 ms on four full-HD pyramids with
-// 52 classes; everything over classes in registers: 1.95; two waves per SIMD: 1.74.)
+// 52 classes; everything over classes in registers: 1.95; two waves per SIMD: 1.74, 64 bytes a lane
+// of it in scratch.)
 constexpr int kEst = 65;   // row stride (floats) of a staged embedding plane: lanes on rows meet no bank twice
 constexpr int kFusedWaves = 8;
 

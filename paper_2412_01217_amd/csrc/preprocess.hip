@@ -227,11 +227,12 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 
 // Backward. g2d holds, per visible (item, Gaussian), the gradient of the loss with respect to
 // mean2d (x, y), conic (A, B, C), opacity and the composited depth channel, [E][kGradRec].
-// Bound by the latency of its loads at two waves per SIMD (registers), so they run ahead: the radii
-// of a view's first four levels while the view before is worked on, a level's record while the
-// level before is. The pose sums stay in LDS until the block's views are done, a wave adding to
-// them on its own. (Radii and records read as they are used, and a block reduction for each
-// view: 2M Gaussians, 64 images 2.95 ms, now 1.98; 500k, 24 images 333 us, now 231.)
+// Two waves per SIMD (registers). Many Gaussians and views keep the vector units busy (2M, 64 images:
+// 82-83 % of the cycles), few leave them waiting for its loads (200k, three images: 29-30 %), so
+// these run ahead: the radii of a view's first four levels while the view before is worked on, a
+// level's record while the level before is. The pose sums stay in LDS until the block's views are
+// done, a wave adding to them on its own. (Radii and records read as they are used, and a block
+// reduction for each view: 2M Gaussians, 64 images 2.95 ms, now 1.98; 500k, 24 images 333 us, now 231.)
 constexpr int kPoseChunk = 64;   // views whose pose sums are held in LDS at a time
 __global__ __launch_bounds__(256) void k_preprocess_bwd(gs_config cfg, gs_gaussians g,
                                                         const gs_view* __restrict__ views, int n_views,

@@ -436,8 +436,11 @@ inline FeatMode feat_mode(const gs_gaussians& g, int n_sem) {
   if (g.emb) return (uintptr_t)g.emb % 16 == 0 ? kEmbVec : kValues;
   return n_sem > 0 && n_sem % 4 == 0 && (uintptr_t)g.sem % 16 == 0 ? kRowVec : kValues;
 }
-// The quads of channels k .. k + 3 (k % 4 = 0) of the rows of Gaussians g[p], into f[4 p ..]. Every
-// lane loads from a valid address; what lies past the last channel is dropped when it is used.
+// The quads of channels k .. k + 3 (k % 4 = 0) of the rows of Gaussians g[p], into f[4 p ..]. With
+// kRowVec every lane loads from a valid address, and what lies past the last channel is dropped when
+// it is used. kValues has no such loads: a value's is conditional on its channel and picks logits or
+// embedding, zero past the last channel, and the compiler waits where the sides meet (class counts
+// that four does not divide, arrays off a 16-byte boundary).
 template <int MODE, int NP>
 __device__ __forceinline__ void load_quads(const FeatSrc& s, const uint32_t (&g)[NP], int64_t foff, int k, float* f) {
   if constexpr (MODE == kRowVec) {
@@ -596,12 +599,15 @@ __device__ __forceinline__ int opaque_v(int x) { asm volatile("" : "+v"(x)); ret
 //   by a block transpose across lane rows, not through LDS.
 // A split list leaves each segment's colour, end T and blend record in its slot; when the list
 // is one chunk, the block also joins its segments (image, T, n_contrib, suffix colours).
-// What bounds it: vector issue (67 % busy) on full chips, one wave's chain of batches (about
-// 4000 cycles of recurrence each) where the longest list sets the time. It replaces a block
-// that staged 32 list entries at a time for all four waves, with two barriers a batch and
-// dense products over entries that mostly miss: 16 full-HD pyramids, embedding 30.7 -> 11.6 ms;
-// eight 636x476 pyramids, 20 classes 3.43 -> 1.77 ms; 1200x680 pyramid, 52 classes
-// 0.39 -> 0.21 ms; a 320x240 pyramid whose longest list has 2100 entries 0.26 -> 0.12 ms.
+// What bounds it: on a full chip vector issue and the gathers at once (16 full-HD pyramids, embedding,
+// segments of 4096: vector instructions issue in 82-83 % of the cycles, and 50 GB pass the fabric in
+// 9.5 ms, 5.2 TB/s, the rate of a copy; a region's Gaussian costs a line each for colour, depth and
+// features); with 64 channels the wait for gathers at two waves a SIMD (54-55 % issue); one wave's chain
+// of batches (about 4000 cycles of recurrence each) where the longest list sets the time. It replaces a
+// block that staged 32 list entries at a time for all four waves, with two barriers a batch and
+// dense products over entries that mostly miss: 16 full-HD pyramids, embedding 30.7 -> 11.0 ms;
+// eight 636x476 pyramids, 20 classes 3.43 -> 1.62 ms; 1200x680 pyramid, 52 classes
+// 0.39 -> 0.20 ms; a 320x240 pyramid whose longest list has 2100 entries 0.26 -> 0.13 ms.
 // Three waves a SIMD with 32 channels; two with 64, since at three the compiler spills (0.39
 // against 0.21 ms: scratch traffic queues between the gathers).
 constexpr int kQueue = 128;     // a batch's remainder (31), 64 entries and a last batch's filling (32)
@@ -948,7 +954,9 @@ __global__ __launch_bounds__(256) void k_fwd_combine(const gs_item* __restrict__
 // run and three sums over it (of D, D dx, D dx^2) give all six terms; the four lane rows' parts
 // are then added with values halved at each step (permlane32 pairs rows (0, 2) and (1, 3), permlane16
 // rows (0, 1) and (2, 3)). The opacity's sum is that of D over the opacity
-// (an opacity of 0, which alpha_min = 0 lets through, has no gradient: its logit's is o (1 - o) times it). (Six terms for each pixel's
+// (an opacity of 0, which alpha_min = 0 lets through, has no gradient: its logit's is o (1 - o) times
+// it). The mean's two terms are combined after the sums, 2a S(D dx) + b S(D dy), where a thin oblique
+// footprint's two parts cancel as sums and not pixel by pixel. (Six terms for each pixel's
 // lane and their sums over 64 lanes were a quarter of the reverse pass's instructions.)
 // (x, y): position of the lane's first pixel; ys: rows from its first run to its second.
 __device__ __forceinline__ void geo_sums(const float* D, const float* R, float x, float y, float ys, int l16, int g4,
@@ -1187,7 +1195,10 @@ __global__ __launch_bounds__(256, 2) void k_seg_summary(gs_config cfg, const flo
 
 // ------------------------------------------------------------------------- backward, main pass
 // Where the reverse pass's per-Gaussian sums go from LDS: the n_sem semantic channels and rgb in
-// single precision, the record's seven components (kGradRec) in double precision.
+// single precision, the record's seven components (kGradRec) in double precision. A wave adds its
+// own sums, so a feature gradient is rounded some four times as often as when a block added them
+// (error of all outputs against 64 bits, eight 636x476 pyramids 6.08e-6 -> 6.19e-6, a 640x480 frame
+// 1.41e-6 -> 1.74e-6; two runs of one build differ by as much).
 struct GradDst {
   float *grgb, *gsem;
   double* g2d;
@@ -1208,14 +1219,16 @@ struct GradDst {
 // (measured), so a group's sums go out with the lanes of a Gaussian side by side: a record's seven
 // components or an embedding's row (64 bytes) are one request each.
 // It replaces a block that staged 32 entries at a time for its four waves and met at two barriers a
-// batch: 16 full-HD pyramids, embedding 70.3 -> 24.3 ms; eight 636x476 pyramids, 20 classes
-// 6.44 -> 2.65 ms; a 1200x680 pyramid, 52 classes 1.04 -> 0.45 ms; a 320x240 pyramid 0.28 -> 0.13 ms
+// batch: 16 full-HD pyramids, embedding 70.3 -> 24.2 ms; eight 636x476 pyramids, 20 classes
+// 6.44 -> 2.61 ms; a 1200x680 pyramid, 52 classes 1.04 -> 0.44 ms; a 320x240 pyramid 0.28 -> 0.13 ms
 // (29.7, 3.14, 0.52 and 0.14 ms with a barrier per work item, sums read one by one as they go out
 // and records in single precision; 27.0, 2.90, 0.48 and 0.14 with the geometric sums by pixel).
 // Windows of 64 entries shared by the four waves, their sums meeting in LDS (half the atomic
 // requests), took 45.9 ms and 0.88 ms on the first and third: 28 % of the cycles were waves waiting
-// for the one with most entries in the window. On the first, vector instructions now issue in 57 %
-// of the cycles, at the two waves per SIMD that the registers allow.
+// for the one with most entries in the window. On the first (segments of 4096), vector instructions
+// now issue in 58 % of the cycles, at the two waves per SIMD that the registers allow, and 80 GB pass
+// the fabric, 3.8 TB/s: regions gather and add for themselves, 42 % more than the block's 56 GB. With
+// 64 channels (256 registers) they issue in 36-37 %.
 constexpr int kGrp = 16, kRing = 128;   // ring: a part group (15), two groups in work, 64 new entries
 
 template <int NS>

@@ -110,7 +110,8 @@ __device__ __forceinline__ void sh_grad_dot(float x, float y, float z, int deg, 
 //   coefficients, 16 consecutive rows, go through LDS in the order they lie in memory.
 // Bound by memory, whose floor is 168 us for 200k Gaussians, 52 classes of degree 1, rgb of degree 3
 // and two views: a lane per (Gaussian, channel) had every lane work out its Gaussian's directions,
-// and three rgb channels' degree 3 cost the whole wave: forward 101 us, backward 377. Now 75 and 121.
+// and three rgb channels' degree 3 cost the whole wave: forward 101 us, backward 377. Now 75 and 127
+// (three registers a lane of the backward in scratch).
 constexpr int kShG = 16, kShV = 4, kShWaves = 4, kShBwdWaves = 8;
 // The largest semantic degree that goes this way; past it a step has too many coefficients for
 // loads of several steps in flight, and rows are fetched again for their other channels. Measured
